@@ -556,7 +556,7 @@ static int band_layout(const qcm_model *m, const qcm_basis *gs, const qcm_band_o
     const size_t vs = o->prec == QCM_FP64 ? 8 : 4;
     QCM_TRY(upload_model(m, cv, &B->md, s));
     SpinTables dn = spin_from_basis(gs, 1);
-    QCM_TRY(build_hop_tables(B->md, dn, cv, &B->hd, s, count_bonds(m)));
+    QCM_TRY(build_hop_tables(B->md, dn, cv, &B->hd, s, count_bonds(m), 1));
     B->ops = cv.take<int32_t>(2 * (size_t)p);
     B->zd = cv.take<double>(2 * (size_t)(n_z > 0 ? n_z : 1));
     for (int part = 0; part < 2; ++part) {

@@ -234,7 +234,7 @@ static int job_layout(const qcm_engine_opts &o, Job &j, Carver &cv, hipStream_t 
     const int prec = o.prec;
     QCM_TRY(upload_model(m, cv, &j.md, s));
     QCM_TRY(build_spin_tables(L, j.d.n_dn, cv, &j.dn, s));
-    QCM_TRY(build_hop_tables(j.md, j.dn, cv, &j.hd, s, nb));
+    QCM_TRY(build_hop_tables(j.md, j.dn, cv, &j.hd, s, nb, 1));
     QCM_TRY(build_spin_tables(L, j.d.n_up, cv, &j.gs.up, s));
     QCM_TRY(build_hop_tables(j.md, j.gs.up, cv, &j.gs.hu, s, nb));
     j.gs.valid = 1;
@@ -434,7 +434,8 @@ static void rotate(Engine &e) {
 }
 
 template <typename T>
-static int launch_round(qcm_engine *E, int ng, int na, int nc, size_t lds, const TabLayout &tl,
+static int launch_round(qcm_engine *E, int ng, int n1, int na, int nc, const size_t (&lds)[2], bool big,
+                        const TabLayout &tl,
                         const int64_t *hvb, const int64_t *chb, const int64_t *cnb,
                         const int64_t *acb) {
     hipStream_t s = E->s;
@@ -448,7 +449,17 @@ static int launch_round(qcm_engine *E, int ng, int na, int nc, size_t lds, const
     if (na > 0 && acb[na] > 0) ks_accum<T, TabSrc><<<(unsigned)acb[na], 256, 0, s>>>(ac);
     if (ng > 0) {
         const unsigned nh = (unsigned)hvb[ng], nk = (unsigned)chb[ng], nn = (unsigned)cnb[ng];
-        ks_hv<T, TabSrc><<<nh, 256, lds, s>>>(hv);
+        // groups of blocks with several rows, then (from group n1) of single rows
+        const TabSrc h0{G, hv.begin, n1}, h1{G + n1, hv.begin + n1, ng - n1, hvb[n1]};
+        const unsigned w0 = (unsigned)hvb[n1], w1 = nh - w0;
+        if (w0 && big)
+            ks_hv<T, TabSrc, false, true><<<w0, kHvThreads, lds[0], s>>>(h0);
+        else if (w0)
+            ks_hv<T, TabSrc, false, false><<<w0, kHvThreads, lds[0], s>>>(h0);
+        if (w1 && big)
+            ks_hv<T, TabSrc, true, true><<<w1, kHvThreads, lds[1], s>>>(h1);
+        else if (w1)
+            ks_hv<T, TabSrc, true, false><<<w1, kHvThreads, lds[1], s>>>(h1);
         // alpha and beta from the product's dots; the direct norm pass only
         // for chains whose beta the dots cannot resolve
         ks_finish<TabSrc><<<nn, 256, 0, s>>>(cn, 3);
@@ -493,20 +504,18 @@ static int run_round(qcm_engine *E) {
     BCtl *C = (BCtl *)(E->h_tab + tl.ctl);
     const int lim = gs_limit(o);
     int ng = 0, na = 0, nc = 0;
-    size_t lds = 0;
+    size_t lds[2] = {0, 0};
+    bool big = false;   // a vector of 2 GB or more in the round
     hvb[0] = chb[0] = cnb[0] = acb[0] = 0;
+    // the round's groups: those whose product blocks hold several rows first
+    struct Item {
+        const Job *j;
+        const Part *p;
+        bool replay;
+    };
+    std::vector<Item> items[2];
     auto add_group = [&](const Job &j, const Part &p, bool replay) {
-        G[ng] = engine_group(p.e, j.n);
-        if (replay) {
-            G[ng].psi = j.psi;
-            G[ng].svec = j.svec;
-        }
-        lds = std::max(lds, fused_lds(p.up.d, p.e.rows, o.prec, j.md.nbytes, j.md.u_uniform,
-                                      2 * j.md.nbond));
-        hvb[ng + 1] = hvb[ng] + (int64_t)p.e.nvec * p.e.nblk;
-        chb[ng + 1] = chb[ng] + (int64_t)p.e.nvec * p.e.nchunks;
-        cnb[ng + 1] = cnb[ng] + p.e.nvec;
-        ++ng;
+        items[hv_one(p.up.d, p.e.rows) ? 1 : 0].push_back({&j, &p, replay});
     };
     for (Job *jp : E->active) {
         Job &j = *jp;
@@ -549,11 +558,29 @@ static int run_round(qcm_engine *E) {
             }
         }
     }
+    for (int k = 0; k < 2; ++k)
+        for (const Item &it : items[k]) {
+            const Job &j = *it.j;
+            const Engine &e = it.p->e;
+            G[ng] = engine_group(e, j.n);
+            if (it.replay) {
+                G[ng].psi = j.psi;
+                G[ng].svec = j.svec;
+            }
+            big = big || hv_big(e.dim, o.prec == QCM_FP64 ? 8 : 4);
+            lds[k] = std::max(lds[k], hv_lds(it.p->up.d, e.rows, e.rg, o.prec, j.md.nbytes,
+                                             j.md.u_uniform, 2 * j.md.nbond));
+            hvb[ng + 1] = hvb[ng] + (int64_t)e.nvec * e.wgs;
+            chb[ng + 1] = chb[ng] + (int64_t)e.nvec * e.nchunks;
+            cnb[ng + 1] = cnb[ng] + e.nvec;
+            ++ng;
+        }
+    const int n1 = (int)items[0].size();
     QCM_HIP(hipMemcpyAsync(E->d_tab, E->h_tab, tl.bytes, hipMemcpyHostToDevice, E->s));
     if (o.prec == QCM_FP64)
-        QCM_TRY(launch_round<double>(E, ng, na, nc, lds, tl, hvb, chb, cnb, acb));
+        QCM_TRY(launch_round<double>(E, ng, n1, na, nc, lds, big, tl, hvb, chb, cnb, acb));
     else
-        QCM_TRY(launch_round<float>(E, ng, na, nc, lds, tl, hvb, chb, cnb, acb));
+        QCM_TRY(launch_round<float>(E, ng, n1, na, nc, lds, big, tl, hvb, chb, cnb, acb));
     QCM_HIP(hipMemcpyAsync(E->h_stat, E->d_stat, sizeof(BStat) * nc, hipMemcpyDeviceToHost, E->s));
     QCM_HIP(hipStreamSynchronize(E->s));
     ++E->rounds;

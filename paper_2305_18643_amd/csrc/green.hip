@@ -383,7 +383,7 @@ static int green_common(const qcm_model *m, const qcm_basis *gs, int n, int stri
     const int npairs = n * (n + 1) / 2;
     QCM_TRY(upload_model(m, cv, &c->md, s));
     SpinTables dn = spin_from_basis(gs, 1);
-    QCM_TRY(build_hop_tables(c->md, dn, cv, &c->hd, s, count_bonds(m)));
+    QCM_TRY(build_hop_tables(c->md, dn, cv, &c->hd, s, count_bonds(m), 1));
     c->coef = cv.take<double>((size_t)npairs * 2 * stride);
     c->lenv = cv.take<int32_t>((size_t)npairs * 2);
     c->ops_d = cv.take<int32_t>((size_t)npairs * 2);

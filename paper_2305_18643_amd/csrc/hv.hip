@@ -123,6 +123,7 @@ int upload_model(const qcm_model *m, Carver &cv, ModelDev *md, hipStream_t s) {
     return QCM_OK;
 }
 
+__host__ __device__ inline int pk_width(int W);
 size_t hop_tables_bytes(const qcm_model *m, int64_t d) {
     int W = count_bonds(m);
     if (W < 1) W = 1;
@@ -131,9 +132,12 @@ size_t hop_tables_bytes(const qcm_model *m, int64_t d) {
     cv.take<int32_t>((size_t)W * d);
     cv.take<double>((size_t)W * d);
     cv.take<double>(d);
-    if (d < 65536) cv.take<uint32_t>((size_t)W * d);
+    if (d < 65536) cv.take<uint32_t>((size_t)pk_width(W) * d);
     return cv.off + 256;
 }
+
+// slots of a packed list: read four at a time
+__host__ __device__ inline int pk_width(int W) { return (W + 3) / 4 * 4; }
 
 // Hopping list of every string of one spin.  For a bond (a, b) at most one
 // direction is allowed: the occupied end moves to the empty end.  The entry
@@ -148,8 +152,9 @@ __global__ void k_build_hops(int64_t d, int rowmajor, int W, int L, int l_lo, in
                              int32_t *__restrict__ nh, int32_t *__restrict__ col,
                              double *__restrict__ coef, double *__restrict__ ediag,
                              uint32_t *__restrict__ pk) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= d) return;
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const bool in = i0 < d;
+    const int64_t i = in ? i0 : d - 1;   // the last wave's idle lanes redo the last state
     uint32_t x = states[i];
     int n = 0;
     for (int k = 0; k < nbond; ++k) {
@@ -164,10 +169,16 @@ __global__ void k_build_hops(int64_t d, int rowmajor, int W, int L, int l_lo, in
         const int32_t c = spin_rank(rlo, rhi, l_lo, l_hi, y);
         col[at] = c;
         coef[at] = (m & 1) ? -bt[k] : bt[k];
-        if (pk) pk[at] = (uint32_t)c | ((uint32_t)(2 * k + (m & 1)) << 16);
+        if (pk) pk[at] = (uint32_t)c | ((uint32_t)(2 * k + (m & 1)) << 16) | ((uint32_t)(m & 1) << 31);
         ++n;
     }
-    nh[i] = n;
+    // the hop count, and above it the largest count of the 64 states of the wave
+    int mx = n;
+    for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o));
+    nh[i] = rowmajor ? n : (n | (mx << 16));
+    // packed entries past the hops: the zero slot after a row
+    if (pk)
+        for (int s = n; s < pk_width(W); ++s) pk[(int64_t)s * d + i] = (uint32_t)d;
     double e = 0.0;
     for (int byte = 0; byte < nbytes; ++byte) e += tlut[byte * 256 + ((x >> (8 * byte)) & 255u)];
     ediag[i] = e;
@@ -185,7 +196,7 @@ int build_hop_tables(const ModelDev &md, const SpinTables &st, Carver &cv, HopTa
     ht->ediag = cv.take<double>(st.d);
     // packed entries (column | index of +-t_ab in the model's ctab << 16) when
     // labels fit 16 bits; slot-major layout only
-    ht->pk = (!rowmajor && st.d < 65536) ? cv.take<uint32_t>((size_t)W * st.d) : nullptr;
+    ht->pk = (!rowmajor && st.d < 65536) ? cv.take<uint32_t>((size_t)pk_width(W) * st.d) : nullptr;
     if (!cv.base) return QCM_OK;
     const int B = 256;
     k_build_hops<<<ceil_div(st.d, B), B, 0, s>>>(st.d, ht->rowmajor, W, st.L, st.l_lo, st.l_hi, st.states,
@@ -259,7 +270,7 @@ __global__ void __launch_bounds__(1024) k_hv_rows(HvArgs a, const T *__restrict_
             const double vi = kRowLds ? (double)row[iu] : (double)vrow[iu];
             double acc = diag * vi;
             // inside-row term: K_up
-            const int nhu = a.nhu[iu];
+            const int nhu = a.nhu[iu] & 0xffff;
             for (int s = 0; s < nhu; ++s) {
                 const int64_t e = (int64_t)s * a.d_up + iu;
                 const int32_t j = a.colu[e];
@@ -268,7 +279,7 @@ __global__ void __launch_bounds__(1024) k_hv_rows(HvArgs a, const T *__restrict_
             }
             // row-mixing term: K_dn
             for (int s = 0; s < nhd; ++s) {
-                const int64_t e = (int64_t)s * a.d_dn + idn;
+                const int64_t e = idn * a.wd + s;
                 const int32_t jd = a.cold[e];
                 acc = fma(a.cfd[e], (double)v[(int64_t)jd * a.d_up + iu], acc);
             }
@@ -290,35 +301,26 @@ static int hv_launch_t(const HvOp &op, const void *v, void *w, int nvec, hipStre
         const size_t lds = fused_lds(op.up.d, rows, prec, op.md.nbytes, op.md.u_uniform,
                                      2 * op.md.nbond);
         if (op.hu.pk && lds <= kFusedLds) {
+            // no partial sums to lay out: fewer blocks than CUs are cut shorter, down to a
+            // set of rows, so that more of the chip takes part
+            while (rows > kSide && (int64_t)nvec * ((op.dn.d + rows - 1) / rows) < 256)
+                rows = (rows / 2 + kSide - 1) / kSide * kSide;
+            nblk = (int32_t)((op.dn.d + rows - 1) / rows);
             BGroup g;
             memset(&g, 0, sizeof g);
-            g.d_up = op.up.d;
-            g.d_dn = op.dn.d;
-            g.dim = op.dim;
-            g.su = op.up.states;
-            g.sd = op.dn.states;
-            g.eu = op.hu.ediag;
-            g.ed = op.hd.ediag;
-            g.nhu = op.hu.nh;
-            g.nhd = op.hd.nh;
-            g.colu = op.hu.col;
-            g.cold = op.hd.col;
-            g.cfu = op.hu.coef;
-            g.cfd = op.hd.coef;
-            g.ulut = op.md.ulut;
-            g.pku = op.hu.pk;
-            g.ctab = op.md.ctab;
-            g.nctab = 2 * op.md.nbond;
-            g.u_uniform = op.md.u_uniform;
-            g.nbytes = op.md.nbytes;
+            group_tables(op, &g);
             g.rows = rows;
             g.nblk = nblk;
+            g.rg = side_rows(op.up.d, rows, prec);
+            g.wgs = (nblk + g.rg - 1) / g.rg;
             g.nvec = nvec;
             g.vp = v;   // not read: no subtraction
             g.v = v;
             g.w = w;
-            const OneSrc src{g};
-            ks_hv<T, OneSrc><<<(unsigned)((int64_t)nvec * nblk), 256, lds, s>>>(src);
+            hv_step_launch<T>(OneSrc{g}, (unsigned)((int64_t)nvec * g.wgs),
+                              hv_lds(op.up.d, rows, g.rg, prec, op.md.nbytes, op.md.u_uniform,
+                                     2 * op.md.nbond),
+                              s);
             QCM_LAUNCH_CHECK();
             return QCM_OK;
         }
@@ -388,7 +390,7 @@ int hv_setup(const qcm_model *m, const qcm_basis *b, Carver &cv, HvOp *op, hipSt
     op->dim = b->dim;
     int nb = count_bonds(m);
     QCM_TRY(build_hop_tables(op->md, op->up, cv, &op->hu, s, nb));
-    QCM_TRY(build_hop_tables(op->md, op->dn, cv, &op->hd, s, nb));
+    QCM_TRY(build_hop_tables(op->md, op->dn, cv, &op->hd, s, nb, 1));
     op->split = 0;
     if (split_applies(m, b->n_up, b->d_up, b->d_dn)) QCM_TRY(split_prepare(m, *op, cv, s));
     return QCM_OK;

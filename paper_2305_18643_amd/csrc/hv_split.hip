@@ -55,12 +55,12 @@ __global__ void k_pack_tiles(int64_t d, const int32_t *__restrict__ nh,
                              uint32_t *__restrict__ out32, const uint32_t neg) {
     const int tt = blockIdx.x, lane = threadIdx.x;
     const int64_t i = (int64_t)tt * 64 + lane;
-    const int n = i < d ? nh[i] : 0;
+    const int n = i < d ? nh[i] & 0xffff : 0;
     const uint32_t pad = (uint32_t)(8 * d);
     for (int s = 0; s < tnt[tt]; ++s) {
         uint32_t e = pad, e32 = (uint32_t)(4 * d);
         if (s < n) {
-            const uint32_t p = pk[(int64_t)s * d + i], col = p & 0xffffu, idx = p >> 16;
+            const uint32_t p = pk[(int64_t)s * d + i], col = p & 0xffffu, idx = (p >> 16) & 0x7fffu;
             e = (col << 3) | (idx << 17) | ((idx & 1u) << 31);
             e32 = (col << 2) + ((idx & 1u) ? neg : 0u);
         }
@@ -704,7 +704,7 @@ int split_prepare(const qcm_model *m, HvOp &op, Carver &cv, hipStream_t s) {
     op.tile_ent32 = op.md.t_is_uniform ? cv.take<uint32_t>((size_t)op.ntile * wr * 64) : nullptr;
     op.tile_nt = cv.take<int32_t>(op.ntile);
     op.tile_off = cv.take<int32_t>(op.ntile);
-    QCM_TRY(build_hop_tables(op.md, op.dn, cv, &op.hd_rm, s, count_bonds(m), 1));
+    op.hd_rm = op.hd;   // row-major already
     QCM_TRY(build_row_offsets(op.hd_rm, op.up.d, cv, s));
     // rows grouped by the popcount of the high half of the down string, so
     // that the rows in flight and their in-class neighbours share L2
@@ -734,7 +734,7 @@ int split_prepare(const qcm_model *m, HvOp &op, Carver &cv, hipStream_t s) {
         int32_t o = 0;
         for (int tt = 0; tt < op.ntile; ++tt) {
             int mx = 0;
-            for (int l = 0; l < 64 && tt * 64 + l < du; ++l) mx = std::max(mx, nh[tt * 64 + l]);
+            for (int l = 0; l < 64 && tt * 64 + l < du; ++l) mx = std::max(mx, nh[tt * 64 + l] & 0xffff);
             tnt[tt] = (mx + 3) / 4 * 4;
             toff[tt] = o;
             o += tnt[tt] * 64;

@@ -165,6 +165,8 @@ int engine_init(Engine &e, const HvOp &op, int prec, int nvec, int maxs, double 
     e.nchunks = (int)ceil_div(e.dim, kChunk);
     if (e.nchunks < 1) e.nchunks = 1;
     row_shape(op.up.d, op.dn.d, prec, &e.rows, &e.nblk);
+    e.rg = side_rows(op.up.d, e.rows, prec);
+    e.wgs = (int32_t)((e.nblk + e.rg - 1) / e.rg);
     e.fused = !op.split && !op.csr.rowptr && op.up.d < 65536 &&
               fused_lds(op.up.d, e.rows, prec, op.md.nbytes, op.md.u_uniform,
                         2 * op.md.nbond) <= kFusedLds;
@@ -217,29 +219,36 @@ int engine_reset(Engine &e, hipStream_t s) {
     return QCM_OK;
 }
 
+void group_tables(const HvOp &op, BGroup *g) {
+    g->d_up = op.up.d;
+    g->d_dn = op.dn.d;
+    g->dim = op.dim;
+    g->su = op.up.states;
+    g->sd = op.dn.states;
+    g->eu = op.hu.ediag;
+    g->ed = op.hd.ediag;
+    g->nhu = op.hu.nh;
+    g->nhd = op.hd.nh;
+    g->cold = op.hd.col;
+    g->cfd = op.hd.coef;
+    g->wu = (op.hu.width + 3) / 4 * 4;   // slots of the packed list
+    g->wd = op.hd.width;
+    g->ulut = op.md.ulut;
+    g->pku = op.hu.pk;
+    g->ctab = op.md.ctab;
+    g->nctab = 2 * op.md.nbond;
+    g->t_uniform = op.md.t_is_uniform && op.md.nbond > 0;
+    g->u_uniform = op.md.u_uniform;
+    g->nbytes = op.md.nbytes;
+}
+
 BGroup engine_group(const Engine &e, int n) {
     BGroup g;
     memset(&g, 0, sizeof g);
-    const HvOp &op = e.op;
-    g.d_up = op.up.d;
-    g.d_dn = op.dn.d;
+    group_tables(e.op, &g);
     g.dim = e.dim;
-    g.su = op.up.states;
-    g.sd = op.dn.states;
-    g.eu = op.hu.ediag;
-    g.ed = op.hd.ediag;
-    g.nhu = op.hu.nh;
-    g.nhd = op.hd.nh;
-    g.colu = op.hu.col;
-    g.cold = op.hd.col;
-    g.cfu = op.hu.coef;
-    g.cfd = op.hd.coef;
-    g.ulut = op.md.ulut;
-    g.pku = op.hu.pk;
-    g.ctab = op.md.ctab;
-    g.nctab = 2 * op.md.nbond;
-    g.u_uniform = op.md.u_uniform;
-    g.nbytes = op.md.nbytes;
+    g.rg = e.rg;
+    g.wgs = e.wgs;
     g.rows = e.rows;
     g.nblk = e.nblk;
     g.nvec = e.nvec;
@@ -264,9 +273,10 @@ static int step_t(Engine &e, int n, hipStream_t s) {
     const OneSrc src{engine_group(e, n)};
     const unsigned nk = (unsigned)e.nvec * e.nchunks;
     if (e.fused) {
-        const size_t lds = fused_lds(e.op.up.d, e.rows, e.prec, e.op.md.nbytes,
-                                     e.op.md.u_uniform, 2 * e.op.md.nbond);
-        ks_hv<T, OneSrc><<<(unsigned)e.nvec * e.nblk, 256, lds, s>>>(src);
+        hv_step_launch<T>(src, (unsigned)e.nvec * e.wgs,
+                          hv_lds(e.op.up.d, e.rows, e.rg, e.prec, e.op.md.nbytes,
+                                 e.op.md.u_uniform, 2 * e.op.md.nbond),
+                          s);
     } else if (e.op.split) {
         // the first pass (w -= beta' vp, partial <v, w>) inside the row-mixing
         // pass; a deferred update of the previous step inside the in-row pass

@@ -25,6 +25,14 @@ template <typename T>
 __device__ __forceinline__ gptr<T> gp(T *p) {
     return (gptr<T>)p;
 }
+// Tables read with a wave-uniform index: through the constant address space
+// they become scalar loads.
+template <typename T>
+using cptr = __attribute__((address_space(4))) const T *;
+template <typename T>
+__device__ __forceinline__ cptr<T> cp(const T *p) {
+    return (cptr<T>)p;
+}
 template <typename T>
 __device__ __forceinline__ double ldd(gptr<const T> p) {
     return (double)*p;

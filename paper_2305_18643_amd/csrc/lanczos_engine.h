@@ -41,6 +41,7 @@ struct Engine {
     double *pa;        // [nvec][na]: alpha partials of a step
     double *pn;        // [nvec][3][nchunks]: norm partials of a step
     int32_t na, rows, nblk;
+    int32_t rg, wgs;   // fused product: rows side by side, workgroups per vector
     int32_t fused;     // product fused with the first pass (rows fit LDS)
     // Deferred update (two-pass product only): with lazy set, a step leaves
     // the unnormalised w_n in the buffer of v_{n+1} (pending) and the next

@@ -27,6 +27,9 @@
 // the sector shape, not on the launch or on other groups sharing it.
 #pragma once
 
+#include <algorithm>
+#include <type_traits>
+
 #include "lanczos_device.h"
 
 namespace qcm {
@@ -36,20 +39,28 @@ constexpr int64_t kTileElems = 2048;
 // LDS a fused product block may use (row tile + lookup tables).
 constexpr size_t kFusedLds = 144 * 1024;
 
+// Vectors above this many bytes are taken one chain at a time by all XCDs, each
+// a contiguous range of rows; smaller ones stay on one XCD each (its 4 MB L2).
+constexpr int64_t kXcdChain = (int64_t)4 << 20;
+
 // Everything a step kernel needs about one group.
 struct BGroup {
     // sector and Hamiltonian (fused product)
     int64_t d_up, d_dn, dim;
     const uint32_t *su, *sd;
     const double *eu, *ed;
-    const int32_t *nhu, *nhd, *colu, *cold;
-    const double *cfu, *cfd;
+    const int32_t *nhu, *nhd, *cold;
+    const double *cfd;     // down hops, row-major: hop s of row i at i * wd + s
     const double *ulut;
-    const uint32_t *pku;   // packed up hops: column | (ctab index << 16), slot-major
+    const uint32_t *pku;   // packed up hops (HopTables::pk)
     const double *ctab;    // hop coefficients by index (+-t_ab)
     double u_uniform;
     int32_t nbytes;
     int32_t nctab;
+    int32_t wu, wd;    // widths of the hop lists
+    int32_t rg;        // rows a product workgroup takes side by side (hv_one; else 1)
+    int32_t wgs;       // product workgroups per vector
+    int32_t t_uniform; // every bond has the same t (a coefficient is +-ctab[0])
     int32_t rows;      // rows of V per product block
     int32_t nblk;      // product blocks per vector
     int32_t nvec, nchunks;
@@ -70,7 +81,7 @@ __device__ __forceinline__ int find_group(const int64_t *__restrict__ begin, int
     int lo = 0, hi = ng - 1;
     while (lo < hi) {
         int mid = (lo + hi + 1) >> 1;
-        if (begin[mid] <= x)
+        if (cp(begin)[mid] <= x)
             lo = mid;
         else
             hi = mid - 1;
@@ -84,10 +95,12 @@ struct TabSrc {
     const BGroup *G;
     const int64_t *begin;
     int ng;
+    int64_t base = 0;   // work item of workgroup 0
     __device__ __forceinline__ const BGroup &at(int64_t x, int64_t *local) const {
+        x += base;
         const int g = find_group(begin, ng, x);
-        *local = x - begin[g];
-        return G[g];
+        *local = x - cp(begin)[g];
+        return *(const BGroup *)cp(G + g);   // through the constant space: scalar loads
     }
 };
 struct OneSrc {
@@ -108,6 +121,8 @@ inline void row_shape(int64_t d_up, int64_t d_dn, int prec, int32_t *rows, int32
     *nblk = (int32_t)((d_dn + r - 1) / r);
 }
 
+// LDS of a fused product block as its sector's path is decided: rows plus
+// lookup tables.
 inline size_t fused_lds(int64_t d_up, int32_t rows, int prec, int nbytes, double u_uniform,
                         int nctab) {
     const size_t lut = u_uniform >= 0.0 ? 0 : sizeof(double) * 256 * (size_t)nbytes;
@@ -115,206 +130,503 @@ inline size_t fused_lds(int64_t d_up, int32_t rows, int prec, int nbytes, double
            (prec == QCM_FP64 ? 8 : 4) * (size_t)rows * (size_t)d_up;
 }
 
+constexpr int kSide = 2;
+
+// Sectors of rows so long that a product block is one row (a sector with a
+// single short row counts with the short ones).
+inline bool hv_one(int64_t d_up, int32_t rows) { return rows == 1 && d_up > kTileElems / 2; }
+
+// Rows of a one-row-per-block sector that a product workgroup takes side by
+// side: their hop entries, coefficients and up-string data are then read once
+// for all of them.  Bounded by LDS, so that two workgroups share a CU.
+inline int32_t side_rows(int64_t d_up, int32_t rows, int prec) {
+    if (!hv_one(d_up, rows)) return 1;
+    const int64_t row = (d_up + 1) * (prec == QCM_FP64 ? 8 : 4);
+    return kSide * row <= 64 * 1024 ? kSide : 1;
+}
+
+// LDS of a product workgroup: lookup tables, the rows (interleaved in sets of
+// rg, or kSide for blocks of several rows, each set with a zero slot), and for
+// blocks of several rows the products awaiting the dots.
+inline size_t hv_lds(int64_t d_up, int32_t rows, int32_t rg, int prec, int nbytes, double u_uniform,
+                     int nctab) {
+    const size_t s = prec == QCM_FP64 ? 8 : 4;
+    const size_t lut = u_uniform >= 0.0 ? 0 : sizeof(double) * 256 * (size_t)nbytes;
+    size_t t = (lut + sizeof(double) * (size_t)nctab + 15) & ~(size_t)15;
+    const size_t dots = rg * 5 * 256 * sizeof(double);
+    if (hv_one(d_up, rows)) return t + std::max(dots, s * (size_t)rg * (size_t)(d_up + 1));
+    const size_t sets = (size_t)(rows + kSide - 1) / kSide;
+    return t + std::max(dots, s * sets * kSide * (size_t)(d_up + 1) + s * (size_t)rows * (size_t)d_up);
+}
+
 // The group of chains of an engine at step n (vectors from its rotation).
 BGroup engine_group(const Engine &e, int n);
+// the sector and Hamiltonian fields of a group
+void group_tables(const HvOp &op, BGroup *g);
 
-// pass 1, fused: w = H v - beta' vp for `rows` rows of V held in LDS; one
-// thread per element.  The in-row term gathers inside the LDS rows through
-// the packed up-hop entries (coefficients from a small LDS table); the
-// row-mixing term streams neighbour rows from global memory; the diagonal
-// comes from the two strings.  Hop loads are issued four at a time so that
-// several are in flight per thread.  Sum order per element: diagonal, up hops
-// in list order, down hops in list order, then -beta' vp; all FP64, rounded
-// once.  pa != NULL: partial <v, w> per block.
-template <typename T, class Src>
-__global__ void __launch_bounds__(256) ks_hv(Src src) {
+// Workgroup x of n, renumbered so that each XCD (x mod 8) takes a contiguous
+// range.
+__device__ __forceinline__ int64_t xcd_chunk(int64_t x, int64_t n) {
+    const int64_t k = x & 7, e = n >> 3, r = n & 7;
+    return k * e + (k < r ? k : r) + (x >> 3);
+}
+
+// A wave-uniform value whose origin the compiler no longer sees: what derives
+// from it (products, comparisons held as lane masks, loads through it) is
+// formed where it is used instead of being kept in scalar registers, and
+// spilled, over a loop.
+template <typename X>
+__device__ __forceinline__ X afresh(X x) {
+    if constexpr (sizeof(X) == 4) {
+        int y = __builtin_amdgcn_readfirstlane((int)x);
+        asm volatile("" : "+s"(y));
+        return (X)y;
+    } else {
+        const uint64_t b = (uint64_t)x;
+        uint64_t y = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b) |
+                     (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(b >> 32)) << 32;
+        asm volatile("" : "+s"(y));
+        return (X)y;
+    }
+}
+
+template <typename T, int RG>
+struct alignas(sizeof(T) * RG) RowSet {
+    T x[RG];
+};
+// adjacent columns of a row, aligned as one
+template <typename T, int CW>
+struct Cols {
+    T x[CW];
+};
+template <typename C, typename P>
+__device__ __forceinline__ C ld_cols(P p) {
+    C c;
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(C) / sizeof(c.x[0])); ++k) c.x[k] = p[k];
+    return c;
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void *p, int64_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, (int)bytes, 0x00020000);
+}
+template <typename T>
+__device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+    if constexpr (sizeof(T) == 16)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+    else if constexpr (sizeof(T) == 8)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
+    else
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
+}
+typedef int i32x4_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef double f64x4_t __attribute__((ext_vector_type(4), aligned(8)));
+
+// pass 1, fused: w = H v - beta' vp for rows of V held in LDS.
+//
+// A wave takes 64 lanes x CW adjacent columns of RG rows at a time.  The rows
+// lie interleaved in LDS ([column][row]), so one hop entry, one coefficient
+// and one LDS gather serve RG rows, and one neighbour address serves CW
+// columns.  The in-row loop runs to the largest hop count of the tile's
+// strings (wave-uniform, no masking; groups of four): entries past a string's
+// own hops read a zero slot after the row.  Row-mixing lists are wave-uniform
+// (scalar loads of four columns and coefficients); the neighbours of a row's
+// first eight hops and of its last one to three are in flight together for
+// all RG rows.
+//
+// What bounds it: instruction issue and latency first (the earlier form, one
+// element per thread with hop counts per lane, ran at 65 Gelements/s whatever
+// the size or storage type, 142 VALU and 107 SALU instructions per 64
+// elements; a variant whose neighbours all came from L2 ran no faster), then,
+// for FP64 rows of 14 orbitals, the traffic of the neighbour rows between L2
+// and memory.  Measured: 14-site chain (7,7) FP64 177 -> 99 us a product,
+// ten chains of its (7,6) sector in FP32 1117 -> 538 us; 12-site ladder (6,6)
+// 40 -> 11.6 us; ten chains of a 10-orbital impurity in FP32 21 -> 10 us.
+// Kept out: four rows side by side, neighbours loaded before the in-row hops
+// (loads return in order, so the entries then wait for them; and the
+// registers cost more in occupancy than the overlap gains in FP32).
+//
+// Sum order per element: diagonal, up hops in list order, down hops in list
+// order, then -beta' vp; all FP64, rounded once.  pa != NULL: partial <v, w>,
+// <w, w>, <v, v> (<vp, w>, <vp, v>) per block of q.rows rows, summed as 256
+// threads taking the block's elements in turn, so that they do not depend on
+// how the tiles are dealt out.
+// ONE: sectors of one row per block, q.rg blocks per workgroup (their products
+// are read back for the dots); otherwise one block of several rows per
+// workgroup, in sets of kSide (products kept in LDS for the dots).
+constexpr int kHvThreads = 512;
+
+// Waves per SIMD the product is compiled for, and adjacent columns per lane in
+// blocks of several rows.  One group (a single solve): two columns, which
+// halve the scalar work and the loads per element (3x4 (6,6) product 13.8 ->
+// 11.7 us, 10 chains of 8 orbitals 11.4 -> 9.6 us); a batched round mixes
+// short and long rows and is faster with one column and as many waves as fit
+// (24 solves of 6 to 12 orbitals: 101 ms against 115).
+template <typename T, class S, bool ONE>
+constexpr int hv_waves() {
+    return ONE ? (sizeof(T) == 8 ? 4 : 5) : (std::is_same<S, OneSrc>::value ? 4 : 8);
+}
+
+template <typename T, class Src, bool ONE, bool BIG>
+__global__ void __launch_bounds__(kHvThreads, (hv_waves<T, Src, ONE>())) ks_hv(Src src) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    __shared__ double sh[256];
     int64_t local;
     const BGroup &q = src.at(blockIdx.x, &local);
-    const int64_t vec = local / q.nblk;
-    const int64_t rb = local - vec * q.nblk;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int NT = kHvThreads, NW = NT / 64;
+    const int du = (int)q.d_up;
     const int64_t d_up = q.d_up, d_dn = q.d_dn;
-    const int64_t row0 = rb * q.rows;
-    const int64_t nr = min((int64_t)q.rows, d_dn - row0);
+    int64_t vec, wg;
+    if (q.dim * (int64_t)sizeof(T) > kXcdChain) {
+        // one chain at a time, each XCD a contiguous range of its rows
+        vec = local / q.wgs;
+        wg = xcd_chunk(local - vec * q.wgs, q.wgs);
+    } else {
+        // each XCD its own chains
+        local = xcd_chunk(local, (int64_t)q.wgs * q.nvec);
+        vec = local / q.wgs;
+        wg = local - vec * q.wgs;
+    }
     const int nlut = q.u_uniform >= 0.0 ? 0 : q.nbytes * 256;
     double *lut = reinterpret_cast<double *>(smem_raw);
     double *ct = lut + nlut;
-    T *row = reinterpret_cast<T *>(ct + q.nctab);
+    T *tile = reinterpret_cast<T *>(smem_raw + ((8 * (size_t)(nlut + q.nctab) + 15) & ~(size_t)15));
+    // the partials of the dots, in the place of the rows once these are done
+    double *sh = reinterpret_cast<double *>(tile);
     const auto v = gp((const T *)q.v) + vec * q.dim;
-    const auto vp = gp((const T *)q.vp) + vec * q.dim;
-    const auto w = gp((T *)q.w) + vec * q.dim;
-    const auto su = gp(q.su), pku = gp(q.pku), sd = gp(q.sd);
-    const auto nhu = gp(q.nhu), nhd = gp(q.nhd), cold = gp(q.cold);
-    const auto eu = gp(q.eu), ed = gp(q.ed), cfd = gp(q.cfd);
-    const bool sub = q.n > 0 && q.pa;
+    const int sub = q.n > 0 && q.pa;
+    const bool reo = q.reorth, dots = q.pa != nullptr;
     const double b = sub ? q.cs.beta[vec * q.cs.maxs + q.n - 1] : 0.0;
-    for (int k = threadIdx.x; k < nlut; k += 256) lut[k] = gp(q.ulut)[k];
-    for (int k = threadIdx.x; k < q.nctab; k += 256) ct[k] = gp(q.ctab)[k];
-    const int64_t nel = nr * d_up;
-    const auto vblk = v + row0 * d_up;
-    for (int64_t k = threadIdx.x; k < nel; k += 256) row[k] = vblk[k];
-    __syncthreads();
-    const uint32_t du = (uint32_t)d_up;
-    double pa = 0.0, pww = 0.0, pvv = 0.0, ppw = 0.0, ppv = 0.0;
-    // one element: diagonal, in-row hops through the packed entries, row-mixing
-    // hops from global memory, -beta vp, rounded once
-    // diagonal and in-row part of one element: returns the partial sum and v_i
-    auto in_row = [&](uint32_t r, uint32_t iu, uint32_t sdn, double edn, double *vi_out) -> double {
-        const uint32_t dbl = su[iu] & sdn;
-        double diag = eu[iu] + edn;
-        if (q.u_uniform >= 0.0) {
-            diag += q.u_uniform * (double)__popc(dbl);
+    for (int k = tid; k < nlut; k += NT) lut[k] = gp(q.ulut)[k];
+    for (int k = tid; k < q.nctab; k += NT) ct[k] = gp(q.ctab)[k];
+    const double tu = q.t_uniform ? q.ctab[0] : 0.0;
+    // the vector's rows: through a buffer descriptor, a row's byte offset as the
+    // scalar offset; vectors of 2 GB and more (BIG) through 64-bit row addresses
+    const uint32_t rstep = (uint32_t)(du * (int)sizeof(T));
+    const int64_t vbytes = q.dim * (int64_t)sizeof(T);
+    const auto rv = buf_rsrc((const T *)q.v + vec * q.dim, BIG ? 0 : vbytes);
+    auto row_at = [&](auto cw_, uint32_t i, int vo) {
+        typedef Cols<T, decltype(cw_)::value> C;
+        if constexpr (BIG)
+            return ld_cols<C>((gptr<const T>)((gptr<const char>)v + (uint64_t)i * rstep + (uint32_t)vo));
+        else
+            return buf_load<C>(rv, vo, (int)(i * rstep));
+    };
+    const auto rpk = buf_rsrc(q.pku, (int64_t)q.wu * du * 4);
+    const auto su = gp(q.su);
+    const auto eu = gp(q.eu);
+    const auto nhu = cp(q.nhu);
+    const auto vpb = (gptr<const char>)gp((const T *)q.vp) + vec * vbytes;
+    const auto wb = (gptr<char>)gp((T *)q.w) + vec * vbytes;
+    const int W = q.wd;
+    const double uu = q.u_uniform;
+    const int tun = q.t_uniform, upc = __builtin_amdgcn_readfirstlane(uu >= 0.0);
+    // the products of 64 CW up strings (tile tt; CW adjacent columns per lane)
+    // in RG rows, held interleaved at rs; out(r, iu, w) takes element iu of row r
+    auto tile_rows = [&](auto rg_, auto cw_, int tt, const auto &ri, const T *rs, auto &&out) {
+        constexpr int RG = decltype(rg_)::value, CW = decltype(cw_)::value;
+        typedef RowSet<T, RG> Set;
+        typedef Cols<T, CW> C;
+        const Set *row = reinterpret_cast<const Set *>(rs);
+        // a lane past the row's end redoes the row's last columns
+        const int iu = tt * (64 * CW) + lane * CW;
+        const bool in = iu < du;
+        const int ic = min(iu, du - CW);
+        const int vo = ic * (int)sizeof(T);
+        // the largest hop count of the tile's strings
+        int nh = nhu[tt * (64 * CW)] >> 16;
+        if constexpr (CW == 2) nh = max(nh, nhu[min(tt * 128 + 64, du - 1)] >> 16);
+        const int du4 = afresh(du * 4);
+        constexpr int kAhead = 8;   // entries loaded together
+        Cols<uint32_t, CW> pe[kAhead];
+        auto entries = [&](int s, int n) {
+#pragma unroll
+            for (int g = 0; g < kAhead; g += 4)
+                if (s + g < n)
+#pragma unroll
+                    for (int u = g; u < g + 4; ++u)
+                        pe[u] = buf_load<Cols<uint32_t, CW>>(rpk, ic * 4, (s + u) * du4);
+        };
+        entries(0, nh);
+        const auto bu = ld_cols<Cols<uint32_t, CW>>(su + (uint32_t)ic);
+        const auto eui = ld_cols<Cols<double, CW>>(eu + (uint32_t)ic);
+        double acc[RG][CW];
+#pragma unroll
+        for (int c = 0; c < CW; ++c) {
+            const Set own = row[ic + c];
+#pragma unroll
+            for (int r = 0; r < RG; ++r) {
+                const uint32_t dbl = bu.x[c] & ri.bd[r];
+                double diag = eui.x[c] + ri.ed[r];
+                if (afresh(upc)) {
+                    diag += uu * (double)__popc(dbl);
+                } else {
+                    for (int byte = 0; byte < q.nbytes; ++byte)
+                        diag += lut[byte * 256 + ((dbl >> (8 * byte)) & 255u)];
+                }
+                acc[r][c] = diag * (double)own.x[r];
+            }
+        }
+        // four hops: gathers, then sums in slot order; entries past a string's
+        // own read the zero slot after the row
+        auto group = [&](const Cols<uint32_t, CW> *p, auto tun_) {
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                Set x[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[u] = row[p[u].x[c] & 0xffffu];
+                double cf[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if constexpr (decltype(tun_)::value)
+                        cf[u] = __hiloint2double(
+                            __double2hiint(tu) ^ (int)(p[u].x[c] & 0x80000000u), __double2loint(tu));
+                    else
+                        cf[u] = ct[(p[u].x[c] >> 16) & 0x3ffu];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int r = 0; r < RG; ++r)
+                        acc[r][c] = fma(cf[u], (double)x[u].x[r], acc[r][c]);
+            }
+        };
+        auto hops = [&](auto tun_) {
+            const int n = afresh(nh);
+            for (int s = 0; s < n; s += kAhead) {
+                if (s > 0) entries(s, n);
+#pragma unroll
+                for (int g = 0; g < kAhead; g += 4)
+                    if (s + g < n) group(pe + g, tun_);
+            }
+        };
+        if (afresh(tun))
+            hops(std::true_type{});
+        else
+            hops(std::false_type{});
+        // row-mixing neighbours: whole groups of four hops, the first kGr of
+        // them and the last one to three hops loaded together for all rows
+        constexpr int kGr = 2;
+        C xm[RG][4 * kGr], xt[RG][3], pv[RG];
+        cptr<int32_t> cl[RG];
+        cptr<double> cf[RG];
+#pragma unroll
+        for (int r = 0; r < RG; ++r) {
+            cl[r] = afresh(ri.cl[r]);
+            cf[r] = afresh(ri.cf[r]);
+            const int nhr = afresh(ri.nh[r]), nt = nhr & ~3;
+#pragma unroll
+            for (int t = 0; t < 4 * kGr; t += 4)
+                if (t < nt) {
+                    const i32x4_t c = *(cptr<i32x4_t>)(cl[r] + t);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) xm[r][t + u] = row_at(cw_, (uint32_t)c[u], vo);
+                }
+            if (nhr & 2) {
+                xt[r][0] = row_at(cw_, (uint32_t)cl[r][nt], vo);
+                xt[r][1] = row_at(cw_, (uint32_t)cl[r][nt + 1], vo);
+            }
+            if (nhr & 1) xt[r][2] = row_at(cw_, (uint32_t)cl[r][nhr - 1], vo);
+            if (afresh(sub))
+                pv[r] = ld_cols<C>((gptr<const T>)(vpb + (uint64_t)(uint32_t)ri.idn[r] * rstep + (uint32_t)vo));
+        }
+#pragma unroll
+        for (int r = 0; r < RG; ++r) {
+            auto add = [&](double c, const C &x) {
+#pragma unroll
+                for (int k = 0; k < CW; ++k) {
+                    T xk = x.x[k];
+                    // widened here, not where it was loaded
+                    if constexpr (sizeof(T) == 4) asm("" : "+v"(xk));
+                    acc[r][k] = fma(c, (double)xk, acc[r][k]);
+                }
+            };
+            const int nhr = afresh(ri.nh[r]), nt = nhr & ~3;
+#pragma unroll
+            for (int t = 0; t < 4 * kGr; t += 4)
+                if (t < nt) {
+                    const f64x4_t c = *(cptr<f64x4_t>)(cf[r] + t);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) add(c[u], xm[r][t + u]);
+                }
+            for (int t = 4 * kGr; t < nt; t += 4) {
+                const i32x4_t cc = *(cptr<i32x4_t>)(cl[r] + t);
+                const f64x4_t c = *(cptr<f64x4_t>)(cf[r] + t);
+                C x[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[u] = row_at(cw_, (uint32_t)cc[u], vo);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) add(c[u], x[u]);
+            }
+            if (nhr & 2) {
+                add(cf[r][nt], xt[r][0]);
+                add(cf[r][nt + 1], xt[r][1]);
+            }
+            if (nhr & 1) add(cf[r][nhr - 1], xt[r][2]);
+            // -beta vp, round once, store
+            if (afresh(sub)) add(-b, pv[r]);
+            if (in && r < ri.nr) {
+                C wt;
+                const auto pw = (gptr<T>)(wb + (uint64_t)(uint32_t)ri.idn[r] * rstep + (uint32_t)vo);
+#pragma unroll
+                for (int k = 0; k < CW; ++k) {
+                    wt.x[k] = (T)acc[r][k];
+                    pw[k] = wt.x[k];
+                }
+                out(r, ic, wt);
+            }
+        }
+    };
+    // what the tiles need of the nr (<= RG) rows from idn0
+    auto row_info = [&](auto rg_, int idn0, int nr) {
+        constexpr int RG = decltype(rg_)::value;
+        struct {
+            int nr, idn[RG], nh[RG];
+            uint32_t bd[RG];
+            double ed[RG];
+            cptr<int32_t> cl[RG];
+            cptr<double> cf[RG];
+        } ri;
+        ri.nr = nr;
+#pragma unroll
+        for (int r = 0; r < RG; ++r) {
+            const int i = idn0 + min(r, nr - 1);
+            ri.idn[r] = i;
+            ri.nh[r] = cp(q.nhd)[i];
+            ri.bd[r] = cp(q.sd)[i];
+            ri.ed[r] = cp(q.ed)[i];
+            ri.cl[r] = cp(q.cold) + (int64_t)i * W;
+            ri.cf[r] = cp(q.cfd) + (int64_t)i * W;
+        }
+        return ri;
+    };
+    // sets of RG rows side by side: one set, each of whose rows is a block of
+    // its own (ONE), or one block of several sets
+    auto sets = [&](auto rg_) {
+        constexpr int RG = decltype(rg_)::value;
+        const int rows = ONE ? RG : q.rows;
+        const int64_t row0 = wg * rows;
+        const int nr = (int)min((int64_t)rows, d_dn - row0);
+        const int nset = (nr + RG - 1) / RG;
+        const int SR = RG * (du + 1);   // elements of a set
+        T *wt_s = tile + (rows + RG - 1) / RG * SR;
+        for (int r = 0; r < nset * RG; ++r) {
+            T *t = tile + (r / RG) * SR + r % RG;
+            const auto vr = v + (row0 + min(r, nr - 1)) * d_up;
+            if (ONE || du >= NT) {
+                for (int k = tid; k < du; k += NT) t[k * RG] = vr[k];
+            }
+            if (tid == 0) t[du * RG] = T(0);
+        }
+        // e / du for e < 2^16: M = ceil(2^32 / du), and du = 1 apart
+        const uint32_t M = 0xffffffffu / (uint32_t)du + 1u;
+        auto row_of = [&](int e) { return du == 1 ? e : (int)__umulhi((uint32_t)e, M); };
+        const int nel = nr * du;
+        if (!(ONE || du >= NT))
+            for (int e = tid; e < nel; e += NT) {
+                const int r = row_of(e), iu = e - r * du;
+                tile[(r / RG) * SR + iu * RG + (r % RG)] = (v + row0 * d_up)[e];
+            }
+        __syncthreads();
+        if constexpr (ONE) {
+            const auto ri = row_info(rg_, (int)row0, nr);
+            const int nt = (du + 127) >> 7;
+            for (int tt = wave; tt < nt; tt += NW)
+                tile_rows(rg_, std::integral_constant<int, 2>{}, tt, ri, tile, [](int, int, auto) {});
         } else {
-            for (int byte = 0; byte < q.nbytes; ++byte)
-                diag += lut[byte * 256 + ((dbl >> (8 * byte)) & 255u)];
-        }
-        const T *rr = row + (int64_t)r * d_up;
-        const double vi = (double)rr[iu];
-        *vi_out = vi;
-        double acc = diag * vi;
-        const int nh_u = nhu[iu];
-        const auto pp = pku + iu;
-        int s = 0;
-        for (; s + 4 <= nh_u; s += 4) {
-            const uint32_t p0 = pp[(int64_t)s * d_up], p1 = pp[(int64_t)(s + 1) * d_up];
-            const uint32_t p2 = pp[(int64_t)(s + 2) * d_up], p3 = pp[(int64_t)(s + 3) * d_up];
-            const double x0 = (double)rr[p0 & 0xffffu], x1 = (double)rr[p1 & 0xffffu];
-            const double x2 = (double)rr[p2 & 0xffffu], x3 = (double)rr[p3 & 0xffffu];
-            acc = fma(ct[p0 >> 16], x0, acc);
-            acc = fma(ct[p1 >> 16], x1, acc);
-            acc = fma(ct[p2 >> 16], x2, acc);
-            acc = fma(ct[p3 >> 16], x3, acc);
-        }
-        for (; s < nh_u; ++s) {
-            const uint32_t p0 = pp[(int64_t)s * d_up];
-            acc = fma(ct[p0 >> 16], (double)rr[p0 & 0xffffu], acc);
-        }
-        return acc;
-    };
-    // -beta vp, round once, store, and the partials <v, w>, <w, w>, <v, v>
-    // (with reorthogonalisation also <vp, w>, <vp, v>)
-    auto finish = [&](int64_t i, double acc, double vi) {
-        const double pv = sub ? ldd(vp + i) : 0.0;
-        if (sub) acc = fma(-b, pv, acc);
-        const T wt = (T)acc;
-        w[i] = wt;
-        const double wd = (double)wt;
-        pa = fma(vi, wd, pa);
-        pww = fma(wd, wd, pww);
-        pvv = fma(vi, vi, pvv);
-        if (q.reorth) {
-            ppw = fma(pv, wd, ppw);
-            ppv = fma(pv, vi, ppv);
-        }
-    };
-    // one element: diagonal, in-row hops through the packed entries, row-mixing
-    // hops from global memory, -beta vp, rounded once
-    auto element = [&](uint32_t r, uint32_t iu, int64_t idn, uint32_t sdn, double edn, int nh_d,
-                       gptr<const int32_t> cold_r, gptr<const double> cfd_r) {
-        double vi;
-        double acc = in_row(r, iu, sdn, edn, &vi);
-        // row-mixing term (hop s of row idn at cold_r[s * d_dn])
-        const auto vc = v + iu;
-        int s = 0;
-        for (; s + 4 <= nh_d; s += 4) {
-            const int64_t e0 = (int64_t)s * d_dn, e1 = e0 + d_dn;
-            const int64_t e2 = e1 + d_dn, e3 = e2 + d_dn;
-            const double x0 = (double)vc[(int64_t)cold_r[e0] * d_up];
-            const double x1 = (double)vc[(int64_t)cold_r[e1] * d_up];
-            const double x2 = (double)vc[(int64_t)cold_r[e2] * d_up];
-            const double x3 = (double)vc[(int64_t)cold_r[e3] * d_up];
-            acc = fma(cfd_r[e0], x0, acc);
-            acc = fma(cfd_r[e1], x1, acc);
-            acc = fma(cfd_r[e2], x2, acc);
-            acc = fma(cfd_r[e3], x3, acc);
-        }
-        for (; s < nh_d; ++s) {
-            const int64_t e0 = (int64_t)s * d_dn;
-            acc = fma(cfd_r[e0], (double)vc[(int64_t)cold_r[e0] * d_up], acc);
-        }
-        finish(idn * d_up + iu, acc, vi);
-    };
-    if (d_up >= 1024) {
-        // long rows: the rows one after another, so the row index and its
-        // down-hop list are wave-uniform (scalar loads) and no division is
-        // needed.  Each thread takes two elements of the row at a time (iu and
-        // iu + 256): they share the down-hop list, so their row-mixing gathers
-        // are issued together; each element's sum keeps its own order.
-        for (uint32_t r = 0; r < (uint32_t)nr; ++r) {
-            const int64_t idn = row0 + r;
-            const uint32_t sdn = sd[idn];
-            const double edn = ed[idn];
-            const int nh_d = nhd[idn];
-            const auto cold_r = cold + idn;
-            const auto cfd_r = cfd + idn;
-            for (uint32_t iu = threadIdx.x; iu < du; iu += 512) {
-                const uint32_t iu2 = iu + 256;
-                if (iu2 >= du) {
-                    element(r, iu, idn, sdn, edn, nh_d, cold_r, cfd_r);
-                    continue;
+            auto tiles = [&](auto cw_) {
+                constexpr int CW = decltype(cw_)::value;
+                const int nt = (du + 64 * CW - 1) / (64 * CW);
+                for (int u = wave; u < nset * nt; u += NW) {
+                    const int g = u / nt, tt = u - g * nt;
+                    const int rr = g * RG;
+                    tile_rows(rg_, cw_, tt, row_info(rg_, (int)row0 + rr, min(RG, nr - rr)),
+                              tile + g * SR, [&](int r, int iu, const auto &wt) {
+                                  if (dots)
+#pragma unroll
+                                      for (int k = 0; k < CW; ++k)
+                                          wt_s[(rr + r) * du + iu + k] = wt.x[k];
+                              });
                 }
-                double vi1, vi2;
-                double a1 = in_row(r, iu, sdn, edn, &vi1);
-                double a2 = in_row(r, iu2, sdn, edn, &vi2);
-                const auto vc1 = v + iu, vc2 = v + iu2;
-                int s = 0;
-                for (; s + 4 <= nh_d; s += 4) {
-                    const int64_t e0 = (int64_t)s * d_dn, e1 = e0 + d_dn;
-                    const int64_t e2 = e1 + d_dn, e3 = e2 + d_dn;
-                    const int64_t o0 = (int64_t)cold_r[e0] * d_up, o1 = (int64_t)cold_r[e1] * d_up;
-                    const int64_t o2 = (int64_t)cold_r[e2] * d_up, o3 = (int64_t)cold_r[e3] * d_up;
-                    const double x0 = (double)vc1[o0], y0 = (double)vc2[o0];
-                    const double x1 = (double)vc1[o1], y1 = (double)vc2[o1];
-                    const double x2 = (double)vc1[o2], y2 = (double)vc2[o2];
-                    const double x3 = (double)vc1[o3], y3 = (double)vc2[o3];
-                    const double c0 = cfd_r[e0], c1 = cfd_r[e1], c2 = cfd_r[e2], c3 = cfd_r[e3];
-                    a1 = fma(c0, x0, a1);
-                    a2 = fma(c0, y0, a2);
-                    a1 = fma(c1, x1, a1);
-                    a2 = fma(c1, y1, a2);
-                    a1 = fma(c2, x2, a1);
-                    a2 = fma(c2, y2, a2);
-                    a1 = fma(c3, x3, a1);
-                    a2 = fma(c3, y3, a2);
+            };
+            if (std::is_same<Src, OneSrc>::value && du > 1)
+                tiles(std::integral_constant<int, std::is_same<Src, OneSrc>::value ? 2 : 1>{});
+            else
+                tiles(std::integral_constant<int, 1>{});
+        }
+        if (!dots) return;
+        // the dots: 256 threads per block take its elements in turn, the
+        // products from LDS, or (one row per block) read back
+        __syncthreads();
+        const int t = tid & 255, blk = tid >> 8;   // thread and block
+        double pa = 0.0, pww = 0.0, pvv = 0.0, ppw = 0.0, ppv = 0.0;
+        const bool on = ONE ? blk < nr : blk == 0;
+        if (on) {
+            const int64_t e0 = (row0 + blk) * d_up;
+            const int ne = ONE ? du : nel;
+#pragma unroll 4
+            for (int e = t; e < ne; e += 256) {
+                double wd, vi;
+                if (ONE) {
+                    wd = (double)(gp((const T *)q.w) + vec * q.dim + e0)[e];
+                    vi = (double)tile[e * RG + blk];
+                } else {
+                    const int r = row_of(e), iu = e - r * du;
+                    wd = (double)wt_s[e];
+                    vi = (double)tile[(r / RG) * SR + iu * RG + (r % RG)];
                 }
-                for (; s < nh_d; ++s) {
-                    const int64_t e0 = (int64_t)s * d_dn;
-                    const int64_t o0 = (int64_t)cold_r[e0] * d_up;
-                    a1 = fma(cfd_r[e0], (double)vc1[o0], a1);
-                    a2 = fma(cfd_r[e0], (double)vc2[o0], a2);
+                pa = fma(vi, wd, pa);
+                pww = fma(wd, wd, pww);
+                pvv = fma(vi, vi, pvv);
+                if (reo) {
+                    const double pv = sub ? (double)(gp((const T *)q.vp) + vec * q.dim + e0)[e] : 0.0;
+                    ppw = fma(pv, wd, ppw);
+                    ppv = fma(pv, vi, ppv);
                 }
-                finish(idn * d_up + iu, a1, vi1);
-                finish(idn * d_up + iu2, a2, vi2);
             }
         }
-    } else {
-        for (int64_t e = threadIdx.x; e < nel; e += 256) {
-            const uint32_t r = (uint32_t)e / du;
-            const uint32_t iu = (uint32_t)e - r * du;
-            const int64_t idn = row0 + r;
-            element(r, iu, idn, sd[idn], ed[idn], nhd[idn], cold + idn, cfd + idn);
+        __syncthreads();
+        if (on) {
+            double *x = sh + blk * 5 * 256 + t;
+            x[0] = pa;
+            x[256] = pww;
+            x[512] = pvv;
+            x[768] = ppw;
+            x[1024] = ppv;
         }
-    }
-    if (q.pa) {
-        double *o = q.pa + vec * q.na + rb;
-        const double t0 = block_sum(pa, sh);
-        const double t1 = block_sum(pww, sh);
-        const double t2 = block_sum(pvv, sh);
-        if (threadIdx.x == 0) {
-            o[0] = t0;
-            o[q.pstride] = t1;
-            o[2 * q.pstride] = t2;
+        __syncthreads();
+        // a tree over LDS (t + 128, t + 64, ..., t + 1), one wave per sum
+        const int na = reo ? 5 : 3, nb = ONE ? nr : 1;
+        for (int k = wave; k < na * nb; k += NW) {
+            const int j = k / na, a = k - j * na;
+            const double *x = sh + (j * 5 + a) * 256;
+            double sum = (x[lane] + x[lane + 128]) + (x[lane + 64] + x[lane + 192]);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) sum += __shfl_down(sum, o);
+            if (lane == 0) q.pa[vec * q.na + (ONE ? row0 + j : wg) + a * q.pstride] = sum;
         }
-        if (q.reorth) {
-            const double t3 = block_sum(ppw, sh);
-            const double t4 = block_sum(ppv, sh);
-            if (threadIdx.x == 0) {
-                o[3 * q.pstride] = t3;
-                o[4 * q.pstride] = t4;
-            }
-        }
-    }
+    };
+    if (ONE && q.rg == 1)
+        sets(std::integral_constant<int, 1>{});
+    else
+        sets(std::integral_constant<int, kSide>{});
+}
+
+// Vectors whose byte offsets leave the 31 bits of a buffer load's offset.
+inline bool hv_big(int64_t dim, size_t s) { return dim * (int64_t)s >= ((int64_t)1 << 31); }
+
+// The fused product of one group.
+template <typename T>
+inline void hv_step_launch(const OneSrc &src, unsigned wgs, size_t lds, hipStream_t s) {
+    const bool big = hv_big(src.g.dim, sizeof(T)), one = hv_one(src.g.d_up, src.g.rows);
+    if (one && !big)
+        ks_hv<T, OneSrc, true, false><<<wgs, kHvThreads, lds, s>>>(src);
+    else if (one)
+        ks_hv<T, OneSrc, true, true><<<wgs, kHvThreads, lds, s>>>(src);
+    else if (!big)
+        ks_hv<T, OneSrc, false, false><<<wgs, kHvThreads, lds, s>>>(src);
+    else
+        ks_hv<T, OneSrc, false, true><<<wgs, kHvThreads, lds, s>>>(src);
 }
 
 // chunk of a chunked pass

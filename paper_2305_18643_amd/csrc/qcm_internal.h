@@ -119,11 +119,14 @@ struct HopTables {
     int64_t d;
     int32_t width;        // ELL width (max hops per state)
     int32_t rowmajor;     // 0: entry s of state i at [s * d + i]; 1: at [i * width + s]
-    int32_t *nh;          // [d] number of hops of each state
+    int32_t *nh;          // [d] number of hops of each state (slot-major layout: in the low 16
+                          // bits, the largest count of its 64 consecutive states above)
     int32_t *col;         // [width * d]
     double *coef;         // [width * d]  sign * t_ab
     double *ediag;        // [d]  sum_k t_kk n_k
-    uint32_t *pk = nullptr;  // [width * d] col | (ctab index << 16), slot-major; d < 65536
+    // slot-major, width rounded up to 4 slots, d < 65536: col | (ctab index
+    // << 16) | (1 << 31 for a coefficient -t); past a state's hops col = d
+    uint32_t *pk = nullptr;
     int64_t *off = nullptr;  // row-major layout only: col * (length of the other spin)
 };
 
