@@ -219,8 +219,15 @@ typedef struct qcm_gs_result {
  * eqs. (Krylov), (LanczosRecursion), (tridiag)), in normalised form:
  * v_0 = x/|x|; w = H v_n - beta_{n-1} v_{n-1}; alpha_n = <v_n, w>;
  * w -= alpha_n v_n; beta_n = |w|; v_{n+1} = w / beta_n.  beta_n^2 is the
- * paper's b_{n+1}^2.  The ground-state vector is rebuilt by a second
- * identical pass, psi = sum_n s_n v_n, and normalised.
+ * paper's b_{n+1}^2.  The ground-state vector psi = sum_n s_n v_n is summed
+ * from the vectors of the recurrence as far as the workspace keeps them (every
+ * dim elements, rounded up to 256 bytes, beyond *ws_needed hold one more; at
+ * least four, or none are kept) and otherwise rebuilt by a second identical
+ * pass, with the same result bit for bit; it is then normalised.
+ *   The residual tests run on a side stream (default priority, waiting on
+ * `stream` through events) beside the next step, with a little pinned host
+ * memory; one such set per device is created the first time it is needed (one
+ * more per concurrent caller) and kept for the life of the process.
  *   Start vector when d_v0 == NULL: x_i = 2 (u_i >> 11) 2^-53 - 1, u_i the
  *   output number i of SplitMix64 seeded with `seed`.
  *   h_alpha, h_beta: host [max(max_iter, fixed_steps)] or NULL; receive

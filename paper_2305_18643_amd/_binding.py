@@ -411,6 +411,27 @@ class HvPlan:
             pass
 
 
+# Vectors a ground-state call offers to keep, and the most bytes it offers
+_KEEP_VECTORS, _KEEP_BYTES = 160, 4 << 30
+
+
+def _gs_workspace(torch, need, o, dim, device):
+    """The workspace of a ground-state call: what it needs and, with a vector
+    wanted, room to keep the recurrence's vectors (the call then sums the ground
+    state from them instead of running the recurrence twice).  Without memory
+    for that, the bare workspace."""
+    if o.want_vector:
+        vec = -(-dim * (8 if o.prec == QCM_FP64 else 4) // 256) * 256
+        n = min(max(o.fixed_steps if o.fixed_steps > 0 else o.max_iter, 0) + 1, _KEEP_VECTORS)
+        n = min(n, _KEEP_BYTES // vec)
+        if n >= 4:
+            try:
+                return _workspace(torch, need + 256 + n * vec, device)
+            except torch.OutOfMemoryError:
+                pass
+    return _workspace(torch, need, device)
+
+
 def lanczos_gs(model, basis: SectorBasis, *, max_iter=600, fixed_steps=0, want_vector=True,
                reorth=0, prec="fp64", check_every=1, tol=1e-12, btol=1e-13, seed=1, v0=None,
                stream=None, ws=None) -> dict:
@@ -431,7 +452,7 @@ def lanczos_gs(model, basis: SectorBasis, *, max_iter=600, fixed_steps=0, want_v
     _check(lib.qcm_lanczos_gs(ctypes.byref(m.c), ctypes.byref(basis.c), ctypes.byref(o), None,
                               None, None, None, None, 0, ctypes.byref(need), None))
     if ws is None or ws.numel() < need.value:
-        ws = _workspace(torch, need.value, basis.device)
+        ws = _gs_workspace(torch, need.value, o, basis.dim, basis.device)
     n = max(max_iter, fixed_steps)
     alpha = np.zeros(n)
     beta = np.zeros(n)
@@ -989,7 +1010,7 @@ def sym_lanczos_gs(H: SymHamiltonian, *, max_iter=600, fixed_steps=0, want_vecto
     _check(lib.qcm_sym_lanczos_gs(ctypes.byref(H.c), ctypes.byref(o), None, None, None, None,
                                   None, 0, ctypes.byref(need), None))
     if ws is None or ws.numel() < need.value:
-        ws = _workspace(torch, need.value, H.device)
+        ws = _gs_workspace(torch, need.value, o, H.dim, H.device)
     n = max(max_iter, fixed_steps)
     alpha = np.zeros(n)
     beta = np.zeros(n)

@@ -593,72 +593,6 @@ static int band_layout(const qcm_model *m, const qcm_basis *gs, const qcm_band_o
     return QCM_OK;
 }
 
-// The stream (default priority), events and pinned result of the stopping
-// tests, which run beside the recurrence.  They are created once and kept in
-// a process-wide pool for the life of the process: a call leases a free set
-// of its device (creating one only when none is free, so concurrent calls from
-// other host threads get sets of their own) and returns it, after its side
-// stream has drained, on every way out of band_run.  Later calls therefore
-// create and destroy nothing (stream and pinned-memory teardown can wait for
-// the whole device).
-struct SideRes {
-    int dev = -1;
-    hipStream_t s = nullptr;
-    hipEvent_t copied = nullptr, done = nullptr;
-    double *h_theta = nullptr;
-};
-static std::mutex g_side_mu;
-static std::vector<SideRes *> g_side_free;
-
-struct SideTest {
-    hipStream_t s = nullptr;
-    hipEvent_t copied = nullptr, done = nullptr;
-    double *h_theta = nullptr;
-    SideRes *r = nullptr;
-    int lease() {
-        int dev = -1;
-        QCM_HIP(hipGetDevice(&dev));
-        {
-            std::lock_guard<std::mutex> lock(g_side_mu);
-            for (size_t k = 0; k < g_side_free.size(); ++k)
-                if (g_side_free[k]->dev == dev) {
-                    r = g_side_free[k];
-                    g_side_free.erase(g_side_free.begin() + k);
-                    break;
-                }
-        }
-        if (!r) {
-            SideRes *n = new SideRes();
-            n->dev = dev;
-            hipError_t e = hipStreamCreateWithFlags(&n->s, hipStreamNonBlocking);
-            if (e == hipSuccess) e = hipEventCreateWithFlags(&n->copied, hipEventDisableTiming);
-            if (e == hipSuccess) e = hipEventCreateWithFlags(&n->done, hipEventDisableTiming);
-            if (e == hipSuccess)
-                e = hipHostMalloc((void **)&n->h_theta, sizeof(double), hipHostMallocDefault);
-            if (e != hipSuccess) {
-                if (n->h_theta) (void)hipHostFree(n->h_theta);
-                if (n->done) (void)hipEventDestroy(n->done);
-                if (n->copied) (void)hipEventDestroy(n->copied);
-                if (n->s) (void)hipStreamDestroy(n->s);
-                delete n;
-                return fail(QCM_EHIP, "band Lanczos side stream: %s", hipGetErrorString(e));
-            }
-            r = n;
-        }
-        s = r->s;
-        copied = r->copied;
-        done = r->done;
-        h_theta = r->h_theta;
-        return QCM_OK;
-    }
-    ~SideTest() {
-        if (!r) return;
-        (void)hipStreamSynchronize(r->s);
-        std::lock_guard<std::mutex> lock(g_side_mu);
-        g_side_free.push_back(r);
-    }
-};
-
 template <typename T>
 static int band_run(const qcm_band_opts *o, BandPart &P, const double *d_gs, int64_t d_src_up,
                     const SpinTables &src_up, int kind, const int32_t *ops, hipStream_t s) {
@@ -693,7 +627,7 @@ static int band_run(const qcm_band_opts *o, BandPart &P, const double *d_gs, int
     // convergence the part ends at R = j_t, exactly as if it had stopped
     // there: later steps only add rows and columns to T and rho, so their
     // leading j_t block is final once step j_t is done.
-    SideTest side;
+    SideLease side;   // the stopping tests run beside the recurrence
     int pend_j = 0;   // basis size of the test in flight (0: none)
     int stop_at = 0;  // basis size a finished test stopped the part at
     bool near = false;
@@ -703,13 +637,13 @@ static int band_run(const qcm_band_opts *o, BandPart &P, const double *d_gs, int
     auto settle = [&](bool wait) -> int {
         if (!pend_j) return QCM_OK;
         if (wait) {
-            QCM_HIP(hipEventSynchronize(side.done));
+            QCM_HIP(hipEventSynchronize(side.done[0]));
         } else {
-            const hipError_t q = hipEventQuery(side.done);
+            const hipError_t q = hipEventQuery(side.done[0]);
             if (q == hipErrorNotReady) return QCM_OK;
             QCM_HIP(q);
         }
-        const double th = *side.h_theta;
+        const double th = *(const double *)side.pinned;
         if (have_prev && fabs(th - theta_prev) <= o->etol * std::max(1.0, fabs(th)))
             stop_at = pend_j;
         // when the change, shrinking at its last rate, would meet the
@@ -867,13 +801,13 @@ static int band_run(const qcm_band_opts *o, BandPart &P, const double *d_gs, int
             if (stop_at) break;
             QCM_HIP(hipMemcpy2DAsync(P.Tc, sizeof(double) * ldt, P.Tm, sizeof(double) * ldt,
                                      sizeof(double) * j, j, hipMemcpyDeviceToDevice, s));
-            QCM_HIP(hipEventRecord(side.copied, s));
-            QCM_HIP(hipStreamWaitEvent(side.s, side.copied, 0));
+            QCM_HIP(hipEventRecord(side.ready[0], s));
+            QCM_HIP(hipStreamWaitEvent(side.s, side.ready[0], 0));
             kbl_lowest<<<1, kJacT, 0, side.s>>>(P.Tc, ldt, j, P.info);
             QCM_LAUNCH_CHECK();
-            QCM_HIP(hipMemcpyAsync(side.h_theta, P.info + 2, sizeof(double),
+            QCM_HIP(hipMemcpyAsync(side.pinned, P.info + 2, sizeof(double),
                                    hipMemcpyDeviceToHost, side.s));
-            QCM_HIP(hipEventRecord(side.done, side.s));
+            QCM_HIP(hipEventRecord(side.done[0], side.s));
             pend_j = j;
         }
     }

@@ -435,6 +435,7 @@ static void rotate(Engine &e) {
 
 template <typename T>
 static int launch_round(qcm_engine *E, int ng, int n1, int na, int nc, const size_t (&lds)[2], bool big,
+                        bool norms,
                         const TabLayout &tl,
                         const int64_t *hvb, const int64_t *chb, const int64_t *cnb,
                         const int64_t *acb) {
@@ -462,9 +463,11 @@ static int launch_round(qcm_engine *E, int ng, int n1, int na, int nc, const siz
             ks_hv<T, TabSrc, true, false><<<w1, kHvThreads, lds[1], s>>>(h1);
         // alpha and beta from the product's dots; the direct norm pass only
         // for chains whose beta the dots cannot resolve
-        ks_finish<TabSrc><<<nn, 256, 0, s>>>(cn, 3);
-        ks_norm<T, TabSrc><<<nk, 256, 0, s>>>(ch, 1);
-        ks_finish<TabSrc><<<nn, 256, 0, s>>>(cn, 4);
+        ks_finish_fused<T, TabSrc><<<nn, 256, 0, s>>>(cn);
+        if (norms) {
+            ks_norm<T, TabSrc><<<nk, 256, 0, s>>>(ch, 1);
+            ks_finish<TabSrc><<<nn, 256, 0, s>>>(cn, 4);
+        }
         ks_update<T, TabSrc><<<nk, 256, 0, s>>>(ch);
     }
     if (nc > 0) kb_control<<<nc, 256, 0, s>>>(C, E->d_stat);
@@ -506,6 +509,7 @@ static int run_round(qcm_engine *E) {
     int ng = 0, na = 0, nc = 0;
     size_t lds[2] = {0, 0};
     bool big = false;   // a vector of 2 GB or more in the round
+    bool norms = false; // a vector too long for the finishing kernel's norm
     hvb[0] = chb[0] = cnb[0] = acb[0] = 0;
     // the round's groups: those whose product blocks hold several rows first
     struct Item {
@@ -567,6 +571,7 @@ static int run_round(qcm_engine *E) {
                 G[ng].psi = j.psi;
                 G[ng].svec = j.svec;
             }
+            norms = norms || e.nchunks > kFinishChunks;
             big = big || hv_big(e.dim, o.prec == QCM_FP64 ? 8 : 4);
             lds[k] = std::max(lds[k], hv_lds(it.p->up.d, e.rows, e.rg, o.prec, j.md.nbytes,
                                              j.md.u_uniform, 2 * j.md.nbond));
@@ -578,9 +583,9 @@ static int run_round(qcm_engine *E) {
     const int n1 = (int)items[0].size();
     QCM_HIP(hipMemcpyAsync(E->d_tab, E->h_tab, tl.bytes, hipMemcpyHostToDevice, E->s));
     if (o.prec == QCM_FP64)
-        QCM_TRY(launch_round<double>(E, ng, n1, na, nc, lds, big, tl, hvb, chb, cnb, acb));
+        QCM_TRY(launch_round<double>(E, ng, n1, na, nc, lds, big, norms, tl, hvb, chb, cnb, acb));
     else
-        QCM_TRY(launch_round<float>(E, ng, n1, na, nc, lds, big, tl, hvb, chb, cnb, acb));
+        QCM_TRY(launch_round<float>(E, ng, n1, na, nc, lds, big, norms, tl, hvb, chb, cnb, acb));
     QCM_HIP(hipMemcpyAsync(E->h_stat, E->d_stat, sizeof(BStat) * nc, hipMemcpyDeviceToHost, E->s));
     QCM_HIP(hipStreamSynchronize(E->s));
     ++E->rounds;

@@ -15,6 +15,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
 
 #include "lanczos_step.h"
 
@@ -142,8 +143,116 @@ __global__ void __launch_bounds__(256) k_tridiag_status(const double *__restrict
                                                         const double *__restrict__ beta, int M,
                                                         double tol, double *__restrict__ work,
                                                         double *__restrict__ svec,
-                                                        GsStatus *__restrict__ status, int want1) {
-    tridiag_status_block(alpha, beta, M, tol, work, svec, status, want1 != 0);
+                                                        GsStatus *status) {
+    tridiag_status_block(alpha, beta, M, tol, work, svec, status, true);
+}
+
+// The tests between steps (no theta_1), each in two halves of about the same
+// length that need not follow one another in one workgroup: workgroup 0 takes
+// theta_0 of T_M (the next test's hint), workgroup 1 the residual estimate of
+// the test before (T_Mv, theta_0 in *prev) and leaves its record, with whether
+// the chain had stopped after step Mv - 1, in pinned host memory.  Mv = 0: no
+// test before; M = 0: none after.
+struct GsTest {
+    GsStatus st;
+    int32_t done, len;   // (len: steps recorded, when done)
+};
+__global__ void __launch_bounds__(256) k_tridiag_test(const double *__restrict__ alpha,
+                                                      const double *__restrict__ beta, int M, int Mv,
+                                                      double tol, double *work, double *work2,
+                                                      double *svec, GsStatus *prev,
+                                                      GsStatus *status, const int32_t *dlog,
+                                                      const int32_t *len, GsTest *host) {
+    if (blockIdx.x == 0) {
+        if (M > 0) tridiag_theta_block(alpha, beta, M, work2, prev, status);
+        return;
+    }
+    // (theta_0 of *prev is read by both workgroups, its estimate written here)
+    tridiag_est_block(alpha, beta, Mv, tol, work, svec, prev);
+    if (threadIdx.x == 0) {
+        host->st = *prev;
+        host->done = dlog[Mv - 1];
+        host->len = *len;   // of a stopped chain: no later step changes it
+    }
+}
+
+// psi_i = sum over n < M of svec[n] v_n[i] (FP64, in order of n) from kept
+// vectors, vec elements apart
+template <typename T>
+__global__ void __launch_bounds__(256) k_psi(double *__restrict__ psi, const T *__restrict__ v,
+                                             int64_t vec, int64_t n_el, int M,
+                                             const double *__restrict__ svec) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n_el) return;
+    const auto s = cp(svec);
+    const auto p = gp(v) + i;
+    double acc = 0.0;
+    int n = 0;
+    for (; n + 8 <= M; n += 8) {
+        T x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = __builtin_nontemporal_load(p + (int64_t)(n + u) * vec);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc = fma(s[n + u], (double)x[u], acc);
+    }
+    for (; n < M; ++n) acc = fma(s[n], (double)p[(int64_t)n * vec], acc);
+    psi[i] = acc;
+}
+
+// ---------------------------------------------------------------- side stream
+
+struct SideRes {
+    int dev = -1;
+    hipStream_t s = nullptr;
+    hipEvent_t ev[2 * SideLease::kEv] = {};
+    void *pinned = nullptr;
+};
+static std::mutex g_side_mu;
+static std::vector<SideRes *> g_side_free;
+
+int SideLease::lease() {
+    int dev = -1;
+    QCM_HIP(hipGetDevice(&dev));
+    {
+        std::lock_guard<std::mutex> lock(g_side_mu);
+        for (size_t k = 0; k < g_side_free.size(); ++k)
+            if (g_side_free[k]->dev == dev) {
+                r = g_side_free[k];
+                g_side_free.erase(g_side_free.begin() + k);
+                break;
+            }
+    }
+    if (!r) {
+        SideRes *n = new SideRes();
+        n->dev = dev;
+        hipError_t e = hipStreamCreateWithFlags(&n->s, hipStreamNonBlocking);
+        for (int k = 0; k < 2 * kEv && e == hipSuccess; ++k)
+            e = hipEventCreateWithFlags(&n->ev[k], hipEventDisableTiming);
+        if (e == hipSuccess) e = hipHostMalloc(&n->pinned, kSidePinned, hipHostMallocDefault);
+        if (e != hipSuccess) {
+            if (n->pinned) (void)hipHostFree(n->pinned);
+            for (int k = 0; k < 2 * kEv; ++k)
+                if (n->ev[k]) (void)hipEventDestroy(n->ev[k]);
+            if (n->s) (void)hipStreamDestroy(n->s);
+            delete n;
+            return fail(QCM_EHIP, "side stream: %s", hipGetErrorString(e));
+        }
+        r = n;
+    }
+    s = r->s;
+    for (int k = 0; k < kEv; ++k) {
+        ready[k] = r->ev[k];
+        done[k] = r->ev[kEv + k];
+    }
+    pinned = r->pinned;
+    return QCM_OK;
+}
+
+SideLease::~SideLease() {
+    if (!r) return;
+    (void)hipStreamSynchronize(r->s);
+    std::lock_guard<std::mutex> lock(g_side_mu);
+    g_side_free.push_back(r);
 }
 
 // ---------------------------------------------------------------- engine
@@ -197,11 +306,13 @@ int engine_init(Engine &e, const HvOp &op, int prec, int nvec, int maxs, double 
     e.cs.len = ic;
     e.cs.done = ic + nvec;
     e.cs.renorm = ic + 2 * nvec;
+    e.cs.dlog = cv.take<int32_t>(maxs);
     e.ivp = 0;
     e.iv = 1;
     e.iw = 2;
     e.lazy = 0;
     e.pending = 0;
+    e.vpold = nullptr;
     return QCM_OK;
 }
 
@@ -290,9 +401,9 @@ static int step_t(Engine &e, int n, hipStream_t s) {
         sp.reorth = e.reorth;
         LazyUpd lz;
         if (e.pending) {
-            // after the rotation: v_n is in ivp, v_{n-1} in iw (where W goes)
+            // after the rotation: v_n is in ivp, v_{n-1} in iw (where W goes) or vpold
             lz.vold = e.vbuf[e.ivp];
-            lz.vpold = e.vbuf[e.iw];
+            lz.vpold = e.vpold ? e.vpold : e.vbuf[e.iw];
             lz.apre = e.cs.apre;
             lz.corr = e.cs.corr;
             lz.corr2 = e.cs.corr2;
@@ -315,9 +426,11 @@ static int step_t(Engine &e, int n, hipStream_t s) {
     if (e.fused) {
         // alpha and beta from the fused product's dots; the direct norm pass
         // only for chains whose beta the dots cannot resolve
-        ks_finish<OneSrc><<<e.nvec, 256, 0, s>>>(src, 3);
-        ks_norm<T, OneSrc><<<nk, 256, 0, s>>>(src, 1);
-        ks_finish<OneSrc><<<e.nvec, 256, 0, s>>>(src, 4);
+        ks_finish_fused<T, OneSrc><<<e.nvec, 256, 0, s>>>(src);
+        if (e.nchunks > kFinishChunks) {
+            ks_norm<T, OneSrc><<<nk, 256, 0, s>>>(src, 1);
+            ks_finish<OneSrc><<<e.nvec, 256, 0, s>>>(src, 4);
+        }
     } else if (!e.op.split) {
         ks_finish<OneSrc><<<e.nvec, 256, 0, s>>>(src, 0);
         ks_norm<T, OneSrc><<<nk, 256, 0, s>>>(src, 0);
@@ -346,7 +459,7 @@ int engine_step(Engine &e, int n, hipStream_t s) {
 template <typename T>
 static int settle_t(Engine &e, hipStream_t s) {
     BGroup g = engine_group(e, 0);
-    g.vp = e.vbuf[e.iw];
+    g.vp = e.vpold ? e.vpold : e.vbuf[e.iw];
     g.v = e.vbuf[e.ivp];
     g.w = e.vbuf[e.iv];
     const OneSrc src{g};
@@ -407,8 +520,8 @@ int engine_accum(Engine &e, double *psi, const double *coef, int n, hipStream_t 
 }
 
 int tridiag_status(const double *alpha, const double *beta, int M, double tol, double *work,
-                   double *svec, GsStatus *status, hipStream_t s, int want1) {
-    k_tridiag_status<<<1, 256, 0, s>>>(alpha, beta, M, tol, work, svec, status, want1);
+                   double *svec, GsStatus *status, hipStream_t s) {
+    k_tridiag_status<<<1, 256, 0, s>>>(alpha, beta, M, tol, work, svec, status);
     QCM_LAUNCH_CHECK();
     return QCM_OK;
 }
@@ -468,6 +581,7 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
     if (dim < 1) return fail(QCM_EARG, "%s: empty sector", fn);
     const int limit = o->fixed_steps > 0 ? o->fixed_steps : o->max_iter;
     const int every = o->check_every > 0 ? o->check_every : 1;
+    constexpr int kTests = SideLease::kEv;
     // the workspace is laid out by one function, run first without a base to
     // size it (no launch) and then on the workspace
     HvOp op;
@@ -479,7 +593,7 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
         QCM_TRY(engine_init(e, op, o->prec, 1, limit, o->btol, o->reorth, cv));
         svec = cv.take<double>(limit);
         work = cv.take<double>((size_t)limit * 6);
-        status = cv.take<GsStatus>(1);
+        status = cv.take<GsStatus>(kTests);
         dscal = cv.take<double>(64);
         return QCM_OK;
     };
@@ -494,49 +608,115 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
     Carver cv(d_ws);
     QCM_TRY(layout(cv, s));
 
+    // Workspace beyond what is needed keeps the first pass's vectors v_0, v_1,
+    // ..., so that the ground-state vector is summed from them instead of
+    // running the recurrence again (12 orbitals, 72 steps: 4 ms of 26).
+    const size_t vb = ((o->prec == QCM_FP64 ? 8 : 4) * (size_t)dim + 255) / 256 * 256;
+    const size_t at = (cv.off + 255) / 256 * 256;
+    int nkeep = 0;
+    if (o->want_vector && d_gs && ws_bytes > at)
+        nkeep = (int)std::min<size_t>((ws_bytes - at) / vb, (size_t)limit + 1);
+    if (nkeep < 4) nkeep = 0;
+    char *const keep = (char *)d_ws + at;
+    void *const ring[3] = {e.vbuf[0], e.vbuf[1], e.vbuf[2]};
+    auto slot = [&](int n) -> void * { return n < nkeep ? keep + (size_t)n * vb : ring[n % 3]; };
+    // v_n is in slot(n); the product of step n goes where v_{n+1} will be.  The
+    // ring's three buffers hold whatever comes after the kept vectors.
+    auto aim = [&](int n) {
+        e.vpold = e.vbuf[e.iw];
+        e.vbuf[e.iw] = slot(n + 1);
+    };
+
     // first pass: coefficients; the status starts empty (M = 0: no hint for
     // the first test, as in the batched engine)
-    QCM_HIP(hipMemsetAsync(status, 0, sizeof(GsStatus), s));
+    QCM_HIP(hipMemsetAsync(status, 0, kTests * sizeof(GsStatus), s));
     QCM_TRY(engine_reset(e, s));
+    if (nkeep) e.vbuf[e.iv] = slot(0);
     QCM_TRY(engine_seed(e, o->seed, o->d_v0, s));
     QCM_TRY(engine_normalize(e, s));
     // the first pass needs the coefficients only: updates may be deferred
     e.lazy = 1;
     GsStatus hs{};
     int M = 0, conv = 0, brk = 0;
-    int32_t done = 0;
-    for (int n = 0; n < limit; ++n) {
-        QCM_TRY(engine_step(e, n, s));
-        M = n + 1;
-        bool last = (n + 1 == limit);
-        bool check = o->fixed_steps > 0 ? false : ((n + 1) % every == 0 || last);
-        // breakdown is checked together with the residual test; with fixed steps
-        // every `every` steps as well
-        if (o->fixed_steps > 0 && ((n + 1) % every == 0 || last)) check = true;
-        if (check) {
-            QCM_HIP(hipMemcpyAsync(&done, e.cs.done, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-            if (o->fixed_steps <= 0) {
-                QCM_TRY(tridiag_status(e.cs.alpha, e.cs.beta, M, o->tol, work, svec, status, s, 0));
-                QCM_HIP(hipMemcpyAsync(&hs, status, sizeof hs, hipMemcpyDeviceToHost, s));
+    // The tests run on a side stream beside the steps, two of which may be
+    // enqueued past the step whose verdict is known: such a step is wasted if
+    // the verdict ends the recurrence, but changes nothing (its coefficients
+    // are not read).  Test t has status record t mod kTests; launch t takes
+    // its theta_0 and test t - 1's estimate.
+    SideLease side;
+    if (o->fixed_steps <= 0) QCM_TRY(side.lease());
+    int ntest = 0, seen = 0, nlaunch = 0, tm[kTests] = {0};
+    bool stop = false;
+    auto launch_test = [&](int Mt) -> int {
+        const int k = nlaunch % kTests, kp = (nlaunch + kTests - 1) % kTests;
+        QCM_HIP(hipEventRecord(side.ready[k], s));
+        QCM_HIP(hipStreamWaitEvent(side.s, side.ready[k], 0));
+        k_tridiag_test<<<nlaunch > 0 ? 2 : 1, 256, 0, side.s>>>(
+            e.cs.alpha, e.cs.beta, Mt, nlaunch > 0 ? tm[kp] : 0, o->tol, work,
+            work + 5 * (size_t)limit, svec, status + kp, status + k, e.cs.dlog, e.cs.len,
+            (GsTest *)side.pinned + kp);
+        QCM_LAUNCH_CHECK();
+        QCM_HIP(hipEventRecord(side.done[k], side.s));
+        tm[k] = Mt;
+        ++nlaunch;
+        if (Mt > 0) ++ntest;
+        return QCM_OK;
+    };
+    // the verdicts of the tests up to t, in order, until one ends the recurrence
+    auto verdicts = [&](int t) -> int {
+        for (; seen <= t && !stop; ++seen) {
+            const hipEvent_t ev = side.done[(seen + 1) % kTests];
+            hipError_t q;
+            while ((q = hipEventQuery(ev)) == hipErrorNotReady) {
             }
-            QCM_HIP(hipStreamSynchronize(s));
-            if (done) {
-                brk = 1;
-                conv = 1;
+            QCM_HIP(q);
+            const GsTest *g = (const GsTest *)side.pinned + seen % kTests;
+            hs = g->st;
+            M = hs.M;
+            if (g->done) {
                 // the chain stopped at len; steps after it carry zero vectors
-                int32_t len = 0;
-                QCM_HIP(hipMemcpy(&len, e.cs.len, sizeof len, hipMemcpyDeviceToHost));
-                M = len;
-                break;
-            }
-            if (o->fixed_steps <= 0 && hs.converged) {
+                M = g->len;
+                brk = conv = 1;
+                stop = true;
+            } else if (hs.converged) {
                 conv = 1;
-                break;
+                stop = true;
             }
         }
+        return QCM_OK;
+    };
+    for (int n = 0; n < limit && !stop; ++n) {
+        if (nkeep) aim(n);
+        QCM_TRY(engine_step(e, n, s));
+        const bool last = n + 1 == limit, check = (n + 1) % every == 0 || last;
+        if (!check) continue;
+        if (o->fixed_steps > 0) {
+            // a chain that stops early goes on with zero vectors, which its
+            // length leaves out; now and then, see whether it has
+            if (last || (n + 1) % 64 == 0) {
+                int32_t ds[2] = {0, 0};
+                QCM_HIP(hipMemcpyAsync(&ds[0], e.cs.done, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+                QCM_HIP(hipMemcpyAsync(&ds[1], e.cs.len, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+                QCM_HIP(hipStreamSynchronize(s));
+                M = ds[0] ? ds[1] : n + 1;
+                if (ds[0]) brk = conv = 1;
+                stop = ds[0] != 0;
+            }
+            continue;
+        }
+        QCM_TRY(launch_test(n + 1));
+        if (last) {
+            QCM_TRY(launch_test(0));
+            QCM_TRY(verdicts(ntest - 1));
+        } else {
+            QCM_TRY(verdicts(ntest - 3));
+        }
     }
-    QCM_TRY(tridiag_status(e.cs.alpha, e.cs.beta, M, o->tol, work, svec, status, s));
-    QCM_HIP(hipMemcpyAsync(&hs, status, sizeof hs, hipMemcpyDeviceToHost, s));
+    // the record of the test that ended the recurrence (its theta_0 is the hint)
+    GsStatus *const fin = status + (seen > 0 ? (seen - 1) % kTests : 0);
+    if (nlaunch > 0) QCM_HIP(hipStreamWaitEvent(s, side.done[(nlaunch - 1) % kTests], 0));
+    QCM_TRY(tridiag_status(e.cs.alpha, e.cs.beta, M, o->tol, work, svec, fin, s));
+    QCM_HIP(hipMemcpyAsync(&hs, fin, sizeof hs, hipMemcpyDeviceToHost, s));
     QCM_HIP(hipStreamSynchronize(s));
     if (o->fixed_steps <= 0 && !brk) conv = hs.converged;
 
@@ -556,17 +736,52 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
     if (h_beta) QCM_HIP(hipMemcpy(h_beta, e.cs.beta, sizeof(double) * M, hipMemcpyDeviceToHost));
 
     if (o->want_vector && d_gs) {
-        // second pass: identical recurrence, psi = sum_n s_n v_n
+        // psi = sum_n s_n v_n: over the kept vectors, then (second pass) over
+        // those of the identical recurrence, run again from where they end or
+        // from the start
         double *psi = (double *)d_gs;
-        QCM_HIP(hipMemsetAsync(psi, 0, sizeof(double) * dim, s));
         e.lazy = 0;
-        QCM_TRY(engine_reset(e, s));
-        QCM_TRY(engine_seed(e, o->seed, o->d_v0, s));
-        QCM_TRY(engine_normalize(e, s));
-        for (int n = 0; n < M; ++n) {
-            QCM_TRY(engine_accum(e, psi, svec, n, s));
-            if (n + 1 < M) QCM_TRY(engine_step(e, n, s));
+        e.pending = 0;
+        const int have = std::min(nkeep, M);
+        if (have) {
+            const unsigned g = (unsigned)ceil_div((size_t)dim, 256);
+            const int64_t el = (int64_t)(vb / (o->prec == QCM_FP64 ? 8 : 4));
+            if (o->prec == QCM_FP64)
+                k_psi<double><<<g, 256, 0, s>>>(psi, (const double *)keep, el, dim, have, svec);
+            else
+                k_psi<float><<<g, 256, 0, s>>>(psi, (const float *)keep, el, dim, have, svec);
+            QCM_LAUNCH_CHECK();
+            if (have < M) {
+                // from v_{have-2}, v_{have-1}: no step before M - 1 stopped
+                // the chain, so its flags start clear
+                QCM_HIP(hipMemsetAsync(e.cs.amax, 0, sizeof(double), s));
+                QCM_HIP(hipMemsetAsync(e.cs.done, 0, sizeof(int32_t), s));
+                e.ivp = 0;
+                e.iv = 1;
+                e.iw = 2;
+                e.vbuf[0] = slot(have - 2);
+                e.vbuf[1] = slot(have - 1);
+                e.vbuf[2] = ring[have % 3];
+                e.vpold = nullptr;
+                for (int n = have - 1; n + 1 < M; ++n) {
+                    e.vbuf[e.iw] = ring[(n + 1) % 3];
+                    QCM_TRY(engine_step(e, n, s));
+                    QCM_TRY(engine_accum(e, psi, svec, n + 1, s));
+                }
+            }
+        } else {
+            QCM_HIP(hipMemsetAsync(psi, 0, sizeof(double) * dim, s));
+            QCM_TRY(engine_reset(e, s));
+            QCM_TRY(engine_seed(e, o->seed, o->d_v0, s));
+            QCM_TRY(engine_normalize(e, s));
+            for (int n = 0; n < M; ++n) {
+                QCM_TRY(engine_accum(e, psi, svec, n, s));
+                if (n + 1 < M) QCM_TRY(engine_step(e, n, s));
+            }
         }
+        e.vbuf[0] = ring[0];
+        e.vbuf[1] = ring[1];
+        e.vbuf[2] = ring[2];
         // normalise psi and take the true residual, all FP64
         QCM_TRY(psi_finalize(e, psi, s));
         double *w64 = (double *)e.vbuf[0];  // 8*dim bytes: the first two FP32 or one FP64 vector

@@ -386,6 +386,12 @@ __device__ inline void tridiag_vector(int M, const double *__restrict__ a, const
 // then reads LDS instead of waiting on a cache round trip).
 constexpr int kTriLds = 640;
 
+__device__ __forceinline__ void tridiag_verdict(double bM, double xM, double tol, GsStatus *status) {
+    const double est = bM * fabs(xM);
+    status->est = est;
+    status->converged = est <= tol * fmax(1.0, fabs(status->theta0)) ? 1 : 0;
+}
+
 // The test is a serial chain of FP64 operations (about 20 cycles each): what
 // it costs is the length of that chain, not work.  Measured on T_M of a
 // 12-orbital sector, M = 72: multisection 78 k cycles before the eight-step
@@ -396,13 +402,14 @@ constexpr int kTriLds = 640;
 // theta_1 (only when want1; the convergence test does not need it, so the
 // tests between steps skip it and the final one takes it), the eigenvector
 // of theta_0 in svec, residual estimate beta[M-1] |s[M-1]| and the
-// convergence flag, written to *status.  Up to kTriLds steps the work happens
+// convergence flag, written to *status (which holds the previous test's
+// result before).  Up to kTriLds steps the work happens
 // in LDS; longer T_M use `work` (5 M doubles) and beta^2 in work + 5 M (M
 // doubles).
 __device__ inline void tridiag_status_block(const double *__restrict__ alpha,
                                             const double *__restrict__ beta, int M, double tol,
                                             double *__restrict__ work, double *__restrict__ svec,
-                                            GsStatus *__restrict__ status, bool want1 = true) {
+                                            GsStatus *status, bool want1) {
     __shared__ double la[kTriLds], lb[kTriLds], lb2[kTriLds], lx[kTriLds], lw[5 * kTriLds];
     // (written out for LDS and for global memory: through one pointer to either
     // every access would be a flat one)
@@ -415,12 +422,10 @@ __device__ inline void tridiag_status_block(const double *__restrict__ alpha,
         double th1 = (want1 && M > 1) ? tridiag_kth(M, a, b, b2, 1) : NAN;
         if (threadIdx.x < 64) tridiag_vector(M, a, b, th0, x, w, w + S, w + 2 * S, w + 3 * S, w + 4 * S);
         if (threadIdx.x == 0) {
-            double est = beta[M - 1] * fabs(x[M - 1]);
             status->theta0 = th0;
             status->theta1 = th1;
-            status->est = est;
-            status->converged = est <= tol * fmax(1.0, fabs(th0)) ? 1 : 0;
             status->M = M;
+            tridiag_verdict(beta[M - 1], x[M - 1], tol, status);
         }
     };
     if (M <= kTriLds) {
@@ -436,6 +441,59 @@ __device__ inline void tridiag_status_block(const double *__restrict__ alpha,
         double *b2 = work + 5 * (size_t)M;
         for (int i = threadIdx.x; i < M; i += blockDim.x) b2[i] = beta[i] * beta[i];
         test(alpha, beta, b2, svec, work, M);
+    }
+}
+
+// The same test as two independent parts, each one workgroup's: theta_0 of
+// T_M into *status (from *prev, the previous test's record, as the hint) ...
+__device__ inline void tridiag_theta_block(const double *__restrict__ alpha,
+                                           const double *__restrict__ beta, int M,
+                                           double *__restrict__ work, const GsStatus *prev,
+                                           GsStatus *status) {
+    __shared__ double la[kTriLds], lb[kTriLds], lb2[kTriLds];
+    const double hint = (prev->M >= 1 && prev->M <= M) ? prev->theta0 : NAN;
+    double th0;
+    if (M <= kTriLds) {
+        for (int i = threadIdx.x; i < M; i += blockDim.x) {
+            la[i] = alpha[i];
+            lb[i] = beta[i];
+            lb2[i] = beta[i] * beta[i];
+        }
+        __syncthreads();
+        th0 = tridiag_kth(M, la, lb, lb2, 0, hint);
+    } else {
+        for (int i = threadIdx.x; i < M; i += blockDim.x) work[i] = beta[i] * beta[i];
+        __syncthreads();
+        th0 = tridiag_kth(M, alpha, beta, work, 0, hint);
+    }
+    if (threadIdx.x == 0) {
+        status->theta0 = th0;
+        status->theta1 = NAN;
+        status->M = M;
+    }
+}
+// ... and the residual estimate of a T_M whose theta_0 stands in *status
+// (work: 5 M doubles, svec: M, used where T_M does not fit LDS).
+__device__ inline void tridiag_est_block(const double *__restrict__ alpha,
+                                         const double *__restrict__ beta, int M, double tol,
+                                         double *__restrict__ work, double *__restrict__ svec,
+                                         GsStatus *status) {
+    __shared__ double la[kTriLds], lb[kTriLds], lx[kTriLds], lw[5 * kTriLds];
+    if (threadIdx.x >= 64) return;
+    const double th0 = status->theta0;
+    auto est = [&](const double *a, const double *b, double *x, double *w, int S) {
+        tridiag_vector(M, a, b, th0, x, w, w + S, w + 2 * S, w + 3 * S, w + 4 * S);
+        if (threadIdx.x == 0) tridiag_verdict(beta[M - 1], x[M - 1], tol, status);
+    };
+    if (M <= kTriLds) {
+        for (int i = threadIdx.x; i < M; i += 64) {
+            la[i] = alpha[i];
+            lb[i] = beta[i];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        est(la, lb, lx, lw, kTriLds);
+    } else {
+        est(alpha, beta, svec, work, M);
     }
 }
 

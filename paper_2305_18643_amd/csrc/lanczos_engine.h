@@ -24,6 +24,7 @@ struct ChainState {
     int32_t *len;   // number of steps recorded
     int32_t *done;  // chain stopped (breakdown or empty start)
     int32_t *renorm;  // this step's beta needs the direct norm pass (see ks_finish)
+    int32_t *dlog;    // [maxs] chain 0: whether it had stopped after each step
 };
 
 struct GsStatus {
@@ -48,6 +49,9 @@ struct Engine {
     // step's in-row pass forms v_{n+1} while it stages the rows; whatever
     // reads the vectors in between calls engine_settle first.
     int32_t lazy, pending;
+    // v_{n-1} of the pending update when it is not the buffer the next product
+    // writes into (a caller that keeps its vectors moves that buffer on)
+    const void *vpold;
     double *scratch;
     ChainState cs;
 };
@@ -75,9 +79,31 @@ int green_store(const Engine *e, int npairs, int part, double *coef, int32_t *le
                 hipStream_t s);
 int green_eval(const double *coef, const int32_t *len, int n, int maxs, int nz, const double *zd,
                double e0, const int32_t *pidx, double *F, double *G, hipStream_t s);
-// want1 = 0: skip theta_1 (status->theta1 = NaN); the tests between steps
 int tridiag_status(const double *alpha, const double *beta, int M, double tol, double *work,
-                   double *svec, GsStatus *status, hipStream_t s, int want1 = 1);
+                   double *svec, GsStatus *status, hipStream_t s);
+
+// A stream (default priority), events and a little pinned memory for tests
+// that run beside a recurrence.  They are created once and kept in a
+// process-wide pool for the life of the process: a call leases a free set of
+// its device (creating one only when none is free, so concurrent calls from
+// other host threads get sets of their own) and returns it, after its side
+// stream has drained, on every way out.  Later calls therefore create and
+// destroy nothing (stream and pinned-memory teardown can wait for the whole
+// device).
+struct SideRes;
+struct SideLease {
+    hipStream_t s = nullptr;
+    static constexpr int kEv = 4;
+    hipEvent_t ready[kEv] = {}, done[kEv] = {};
+    void *pinned = nullptr;   // kSidePinned bytes
+    SideRes *r = nullptr;
+    SideLease() = default;
+    SideLease(const SideLease &) = delete;
+    SideLease &operator=(const SideLease &) = delete;
+    int lease();
+    ~SideLease();
+};
+constexpr size_t kSidePinned = 256;
 // The ground-state solver of qcm_lanczos_gs over any product: setup carves
 // the product's tables (or, without a base, only sizes them) and fills op.
 using GsSetup = std::function<int(Carver &, hipStream_t, HvOp *)>;

@@ -671,24 +671,20 @@ __global__ void __launch_bounds__(256) ks_sub_prev(Src src) {
     if (threadIdx.x == 0) q.pa[at.vec * q.na + at.c] = s;
 }
 
-// pass 2: partial |x|^2 (and <v, x>, <vp, x>) with x = w - alpha_n v; with
-// cond, only for chains whose dot-based finish asked for it (cs.renorm)
-template <typename T, class Src>
-__global__ void __launch_bounds__(256) ks_norm(Src src, int cond) {
-    __shared__ double sh[256];
-    int64_t local;
-    const BGroup &q = src.at(blockIdx.x, &local);
-    const ChunkAt at = chunk_of(q, local);
-    if (cond && !q.cs.renorm[at.vec]) return;
-    const double a = q.cs.alpha[at.vec * q.cs.maxs + q.n];
-    const int64_t off = at.vec * q.dim;
+// the direct norm pass of one chunk by one workgroup: |x|^2, <v, x>, <vp, x>
+// with x = w - alpha_n v, summed over the 256 threads (every thread gets the sums)
+template <typename T>
+__device__ __forceinline__ void chunk_norm(const BGroup &q, int64_t vec, int64_t base, double *sh,
+                                           double *t) {
+    const double a = q.cs.alpha[vec * q.cs.maxs + q.n];
+    const int64_t off = vec * q.dim;
     const auto w = gp((const T *)q.w) + off;
     const auto v = gp((const T *)q.v) + off;
     const auto vp = gp((const T *)q.vp) + off;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0;
     if (q.reorth) {
         for (int k = threadIdx.x; k < kChunk; k += 256) {
-            const int64_t i = at.base + k;
+            const int64_t i = base + k;
             if (i < q.dim) {
                 const double vi = ldd(v + i);
                 const double x = fma(-a, vi, ldd(w + i));
@@ -699,22 +695,35 @@ __global__ void __launch_bounds__(256) ks_norm(Src src, int cond) {
         }
     } else {
         for (int k = threadIdx.x; k < kChunk; k += 256) {
-            const int64_t i = at.base + k;
+            const int64_t i = base + k;
             if (i < q.dim) {
                 const double x = fma(-a, ldd(v + i), ldd(w + i));
                 s0 = fma(x, x, s0);
             }
         }
     }
-    double *pn = q.pn + at.vec * 3 * q.nchunks + at.c;
-    const double t0 = block_sum(s0, sh);
-    if (threadIdx.x == 0) pn[0] = t0;
-    if (q.reorth) {
-        const double t1 = block_sum(s1, sh);
-        const double t2 = block_sum(s2, sh);
-        if (threadIdx.x == 0) {
-            pn[q.nchunks] = t1;
-            pn[2 * q.nchunks] = t2;
+    t[0] = block_sum(s0, sh);
+    t[1] = q.reorth ? block_sum(s1, sh) : 0.0;
+    t[2] = q.reorth ? block_sum(s2, sh) : 0.0;
+}
+
+// pass 2: partial |x|^2 (and <v, x>, <vp, x>) with x = w - alpha_n v; with
+// cond, only for chains whose dot-based finish asked for it (cs.renorm)
+template <typename T, class Src>
+__global__ void __launch_bounds__(256) ks_norm(Src src, int cond) {
+    __shared__ double sh[256];
+    int64_t local;
+    const BGroup &q = src.at(blockIdx.x, &local);
+    const ChunkAt at = chunk_of(q, local);
+    if (cond && !q.cs.renorm[at.vec]) return;
+    double t[3];
+    chunk_norm<T>(q, at.vec, at.base, sh, t);
+    if (threadIdx.x == 0) {
+        double *pn = q.pn + at.vec * 3 * q.nchunks + at.c;
+        pn[0] = t[0];
+        if (q.reorth) {
+            pn[q.nchunks] = t[1];
+            pn[2 * q.nchunks] = t[2];
         }
     }
 }
@@ -757,15 +766,20 @@ __device__ __forceinline__ void finish_beta(const ChainState &cs, int c, int n, 
         cs.len[c] = n + 1;
     }
     cs.inv[c] = cs.done[c] ? 0.0 : 1.0 / b;
+    if (c == 0) cs.dlog[n] = cs.done[c];
 }
+
+// Vectors of at most this many chunks take the direct norm pass, when a chain
+// asks for it, inside the finishing kernel: a step is then three launches
+// instead of five (2.4 + 3.6 us less on a 12-orbital sector), and the rare step
+// that needs the pass reads the vector with one workgroup per chain.
+constexpr int kFinishChunks = 32;
 
 // per-chain sums of the partials and the recurrence bookkeeping
 // mode 0: alpha_n; mode 1: reorthogonalisation terms, beta_n, breakdown, from
 // the norm pass; mode 2: the same from the dots of the two-pass product
 // (pa: <v,w>, <w,w>, <v,v>, and with reorthogonalisation <vp,w>, <vp,v>);
-// mode 3: modes 0 and 2 together, from the fused product's dots (same
-// layout, q.na partials per chain), unless the dots cannot resolve beta
-// (cs.renorm); mode 4: mode 1 for the chains so marked.
+// mode 4: mode 1 for the chains marked cs.renorm.
 template <class Src>
 __global__ void __launch_bounds__(256) ks_finish(Src src, int mode) {
     __shared__ double sh[256];
@@ -784,28 +798,6 @@ __global__ void __launch_bounds__(256) ks_finish(Src src, int mode) {
             const double a = fabs(s);
             if (a > cs.amax[c]) cs.amax[c] = a;
         }
-        return;
-    }
-    if (mode == 3) {
-        const double *p = q.pa + (int64_t)c * q.na;
-        const double vw = block_sum(strided_sum(p, q.na), sh);
-        const double ww = block_sum(strided_sum(p + q.pstride, q.na), sh);
-        const double vv = block_sum(strided_sum(p + 2 * q.pstride, q.na), sh);
-        double pw = 0.0, pv = 0.0;
-        if (q.reorth) {
-            pw = block_sum(strided_sum(p + 3 * q.pstride, q.na), sh);
-            pv = block_sum(strided_sum(p + 4 * q.pstride, q.na), sh);
-        }
-        if (threadIdx.x != 0) return;
-        cs.alpha[(int64_t)c * cs.maxs + n] = vw;
-        cs.apre[c] = vw;
-        if (fabs(vw) > cs.amax[c]) cs.amax[c] = fabs(vw);
-        const double a = vw;
-        const double s0 = fma(a * a, vv, fma(-2.0 * a, a, ww));
-        const double s1 = q.reorth ? fma(-a, vv, a) : 0.0;
-        const double s2 = q.reorth ? fma(-a, pv, pw) : 0.0;
-        cs.renorm[c] = !(s0 > kDotRel * ww);
-        if (!cs.renorm[c]) finish_beta(cs, c, n, q.reorth, s0, s1, s2);
         return;
     }
     if (mode == 2) {
@@ -836,6 +828,59 @@ __global__ void __launch_bounds__(256) ks_finish(Src src, int mode) {
     }
     if (threadIdx.x != 0) return;
     finish_beta(cs, c, n, q.reorth, s0, s1, s2);
+}
+
+// modes 0 and 2 together, from the fused product's dots (same layout, q.na
+// partials per chain), unless the dots cannot resolve beta: then the direct
+// norm here (kFinishChunks), or by the norm pass for chains marked cs.renorm.
+// The array sums are block_sum's trees, one wave per array.
+template <typename T, class Src>
+__global__ void __launch_bounds__(256) ks_finish_fused(Src src) {
+    __shared__ double sh[5 * 256];
+    __shared__ double tot[5];
+    __shared__ int direct;
+    int64_t local;
+    const BGroup &q = src.at(blockIdx.x, &local);
+    const int c = (int)local;
+    const ChainState &cs = q.cs;
+    const int n = q.n, t = threadIdx.x, lane = t & 63;
+    const double *p = q.pa + (int64_t)c * q.na;
+    const int na = q.reorth ? 5 : 3;
+    for (int a = 0; a < na; ++a) sh[a * 256 + t] = strided_sum(p + a * q.pstride, q.na);
+    __syncthreads();
+    for (int a = t >> 6; a < na; a += 4) {
+        const double *x = sh + a * 256;
+        double s = (x[lane] + x[lane + 128]) + (x[lane + 64] + x[lane + 192]);
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o);
+        if (lane == 0) tot[a] = s;
+    }
+    __syncthreads();
+    if (t == 0) {
+        const double vw = tot[0], ww = tot[1], vv = tot[2];
+        const double pw = q.reorth ? tot[3] : 0.0, pv = q.reorth ? tot[4] : 0.0;
+        cs.alpha[(int64_t)c * cs.maxs + n] = vw;
+        cs.apre[c] = vw;
+        if (fabs(vw) > cs.amax[c]) cs.amax[c] = fabs(vw);
+        const double a = vw;
+        const double s0 = fma(a * a, vv, fma(-2.0 * a, a, ww));
+        const double s1 = q.reorth ? fma(-a, vv, a) : 0.0;
+        const double s2 = q.reorth ? fma(-a, pv, pw) : 0.0;
+        const bool rn = !(s0 > kDotRel * ww);
+        direct = rn && q.nchunks <= kFinishChunks;
+        cs.renorm[c] = rn && !direct;
+        if (!rn) finish_beta(cs, c, n, q.reorth, s0, s1, s2);
+    }
+    __syncthreads();
+    if (!direct) return;
+    // thread k keeps the sums of chunk k (nchunks <= 256), as strided_sum would
+    double r[3] = {0.0, 0.0, 0.0}, x[3];
+    for (int k = 0; k < q.nchunks; ++k) {
+        chunk_norm<T>(q, c, (int64_t)k * kChunk, sh, x);
+        if (t == k)
+            for (int a = 0; a < 3; ++a) r[a] += x[a];
+    }
+    for (int a = 0; a < 3; ++a) x[a] = a == 0 || q.reorth ? block_sum(r[a], sh) : 0.0;
+    if (t == 0) finish_beta(cs, c, n, q.reorth, x[0], x[1], x[2]);
 }
 
 // The two-pass product's partial arrays (three, five with
