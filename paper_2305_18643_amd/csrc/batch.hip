@@ -468,7 +468,7 @@ static int launch_round(qcm_engine *E, int ng, int n1, int na, int nc, const siz
             ks_norm<T, TabSrc><<<nk, 256, 0, s>>>(ch, 1);
             ks_finish<TabSrc><<<nn, 256, 0, s>>>(cn, 4);
         }
-        ks_update<T, TabSrc><<<nk, 256, 0, s>>>(ch);
+        ks_update<T, TabSrc><<<nk * kUpdParts, 256, 0, s>>>(ch);
     }
     if (nc > 0) kb_control<<<nc, 256, 0, s>>>(C, E->d_stat);
     QCM_LAUNCH_CHECK();

@@ -439,7 +439,7 @@ static int step_t(Engine &e, int n, hipStream_t s) {
     if (e.op.split && e.lazy)
         e.pending = 1;   // the next step's in-row pass forms v_{n+1}
     else
-        ks_update<T, OneSrc><<<nk, 256, 0, s>>>(src);
+        ks_update<T, OneSrc><<<nk * kUpdParts, 256, 0, s>>>(src);
     QCM_LAUNCH_CHECK();
     // rotate: v_{n-1} <- v_n, v_n <- the new vector, next w <- old v_{n-1}
     int t = e.ivp;
@@ -463,7 +463,7 @@ static int settle_t(Engine &e, hipStream_t s) {
     g.v = e.vbuf[e.ivp];
     g.w = e.vbuf[e.iv];
     const OneSrc src{g};
-    ks_update<T, OneSrc><<<(unsigned)e.nvec * e.nchunks, 256, 0, s>>>(src);
+    ks_update<T, OneSrc><<<(unsigned)e.nvec * e.nchunks * kUpdParts, 256, 0, s>>>(src);
     QCM_LAUNCH_CHECK();
     return QCM_OK;
 }
