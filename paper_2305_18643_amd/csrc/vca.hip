@@ -2,12 +2,12 @@
 // formula (paper: subsection "Practical calculation of the Potthoff
 // functional", eq. (omega4)).
 //
-//  * k_vca_k, one workgroup per wave-vector: V(k) (L x L), W = V(k) Q, then
-//    L(k) = diag(w') + Q^T W (R x R, complex Hermitian) written in LDS as the
-//    real symmetric 2R x 2R matrix [[Re, -Im], [Im, Re]], whose spectrum is
-//    that of L(k) with every eigenvalue twice; a cyclic parallel Jacobi
-//    method (round-robin pairing, R disjoint rotations per round) diagonalises
-//    it, and half the sum of its negative eigenvalues is the k term.
+//  * k_vca_k, one wave per wave-vector: V(k) (L x L), W = V(k) Q, then
+//    L(k) = diag(w') + Q^T W (R x R, complex Hermitian) in LDS; Householder
+//    reflections reduce it to tridiagonal form, whose moduli form a real
+//    tridiagonal matrix of the same spectrum; its negative eigenvalues come
+//    from Sturm counts (several points per eigenvalue and round, all at once)
+//    and their sum is the k term.
 //  * k_vca_sum, one workgroup: the fixed-order average over k and the
 //    functional E0 + 2 (average - sum of the negative poles of G').
 //
@@ -41,7 +41,6 @@ namespace qcm {
 
 constexpr int kVL = 8;                       // cluster sites
 constexpr int kVR = QCM_VCA_MAX_R;           // poles
-constexpr int kVN = 2 * kVR;                 // order of the real form
 constexpr int kVQR = QCM_VCA_QUAD_MAX_R;      // poles, frequency-integral route
 
 // Gauss-Kronrod (7, 15) on [-1, 1] (Kronrod's extension of the 7-point
@@ -69,135 +68,191 @@ struct VBond {
     double s0, s1, s2, t;
 };
 
-// Eigenvalues of the symmetric n x n matrix M (LDS, row stride n) by the
-// cyclic parallel Jacobi method; on return the diagonal holds them.  All
-// threads of the workgroup (256) take part.
-__device__ void jacobi_values_lds(double *M, int n, int max_sweeps, double *cs, double *sn, int *pa,
-                                  int *pb, double *red) {
-    const int t = threadIdx.x, T = blockDim.x;
-    const int m = (n % 2 == 0) ? n : n + 1;  // a dummy index n when n is odd
-    const int np = m / 2;
-    for (int sweep = 0; sweep < max_sweeps; ++sweep) {
-        double a0 = 0.0, a1 = 0.0;
-        for (int e = t; e < n * n; e += T) {
-            const double v = M[e];
-            if (e / n != e % n) a0 += v * v;
-            a1 += v * v;
-        }
-        const double off = block_sum(a0, red), tot = block_sum(a1, red);
-        if (!(off > 1e-30 * tot)) break;
-        for (int rd = 0; rd < m - 1; ++rd) {
-            for (int k = t; k < np; k += T) {
-                int a, b;
-                if (k == 0) {
-                    a = m - 1;
-                    b = rd;
-                } else {
-                    a = (rd + k) % (m - 1);
-                    b = (rd - k + (m - 1)) % (m - 1);
-                }
-                const int p = a < b ? a : b, q = a < b ? b : a;
-                double c = 1.0, s = 0.0;
-                if (q < n) {
-                    const double app = M[p * n + p], aqq = M[q * n + q], apq = M[p * n + q];
-                    if (fabs(apq) > 1e-300 && fabs(apq) > 1e-18 * (fabs(app) + fabs(aqq))) {
-                        const double th = (aqq - app) / (2.0 * apq);
-                        const double tt = (th >= 0.0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-                        c = 1.0 / sqrt(tt * tt + 1.0);
-                        s = tt * c;
-                    }
-                }
-                pa[k] = p;
-                pb[k] = q;
-                cs[k] = c;
-                sn[k] = s;
-            }
-            __syncthreads();
-            for (int e = t; e < np * n; e += T) {  // rows p, q
-                const int k = e / n, col = e % n, p = pa[k], q = pb[k];
-                if (q >= n || sn[k] == 0.0) continue;
-                const double c = cs[k], s = sn[k];
-                const double xp = M[p * n + col], xq = M[q * n + col];
-                M[p * n + col] = c * xp - s * xq;
-                M[q * n + col] = s * xp + c * xq;
-            }
-            __syncthreads();
-            for (int e = t; e < n * np; e += T) {  // columns p, q
-                const int row = e / np, k = e % np, p = pa[k], q = pb[k];
-                if (q >= n || sn[k] == 0.0) continue;
-                const double c = cs[k], s = sn[k];
-                const double xp = M[row * n + p], xq = M[row * n + q];
-                M[row * n + p] = c * xp - s * xq;
-                M[row * n + q] = s * xp + c * xq;
-            }
-            __syncthreads();
-        }
-    }
+// One wave per wave-vector, lane r holding row r of L(k) (R <= 64).
+//
+// The chip is far from full (1,024 wave-vectors: one wave per SIMD), so what
+// bounds it is the wave's own chain: sums over a column are taken by every
+// lane from LDS (broadcast reads that can be in flight together) instead of
+// by six dependent shuffles, and the eigenvalues, wanted only where negative,
+// share the lanes: with n of them, 64 / n points of each bracket per Sturm
+// count.  R = 24, 1,024 wave-vectors: 2.7 ms as a parallel Jacobi method on
+// the real 48 x 48 form in one workgroup each.
+struct alignas(16) c64 {
+    double re, im;
+};
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
-__global__ void __launch_bounds__(256) k_vca_k(int L, int R, const double *__restrict__ poles,
-                                               const double *__restrict__ Q,
-                                               const double *__restrict__ dt,
-                                               const VBond *__restrict__ bonds, int nbonds,
-                                               const double *__restrict__ ks,
-                                               double *__restrict__ per_k) {
-    extern __shared__ __align__(16) double Ms[];  // [2R][2R]
-    __shared__ double Vr[kVL * kVL], Vi[kVL * kVL];
-    __shared__ double Wr[kVL * kVR], Wi[kVL * kVR];
-    __shared__ double cs[kVN / 2 + 1], sn[kVN / 2 + 1], red[256];
-    __shared__ int pa[kVN / 2 + 1], pb[kVN / 2 + 1];
-    const int t = threadIdx.x, T = blockDim.x, k = blockIdx.x, n = 2 * R;
-    if (t == 0) {
-        for (int e = 0; e < L * L; ++e) {
-            Vr[e] = dt[e];
-            Vi[e] = 0.0;
-        }
-        const double k0 = ks[3 * k], k1 = ks[3 * k + 1], k2 = ks[3 * k + 2];
-        for (int q = 0; q < nbonds; ++q) {
-            const VBond b = bonds[q];
+__global__ void __launch_bounds__(64) k_vca_k(int L, int R, const double *__restrict__ poles,
+                                              const double *__restrict__ Q,
+                                              const double *__restrict__ dt,
+                                              const VBond *__restrict__ bonds, int nbonds,
+                                              const double *__restrict__ ks,
+                                              double *__restrict__ per_k) {
+    extern __shared__ __align__(16) unsigned char vca_lds[];
+    __shared__ c64 V[kVL * kVL], Wm[kVL * kVR], xs[kVR], ws[kVR];
+    __shared__ double dd[kVR + 8], ee[kVR + 8], bc[64], bs[64];
+    const int t = threadIdx.x, k = blockIdx.x, S = R + 1;
+    c64 *A = reinterpret_cast<c64 *>(vca_lds);   // [R][S]
+    // V(k) = dt + bonds (Hermitian partner added), each entry's bonds in order
+    c64 ve = {t < L * L ? dt[t] : 0.0, 0.0};
+    const double k0 = ks[3 * k], k1 = ks[3 * k + 1], k2 = ks[3 * k + 2];
+    for (int q0 = 0; q0 < nbonds; q0 += 64) {
+        const int nq = min(64, nbonds - q0);
+        if (t < nq) {
+            const VBond b = bonds[q0 + t];
             const double ph = 2.0 * M_PI * (k0 * b.s0 + k1 * b.s1 + k2 * b.s2);
-            const double c = cos(ph), s = sin(ph);
-            Vr[b.i * L + b.j] += b.t * c;
-            Vi[b.i * L + b.j] += b.t * s;
-            Vr[b.j * L + b.i] += b.t * c;
-            Vi[b.j * L + b.i] -= b.t * s;
+            bc[t] = cos(ph);
+            bs[t] = sin(ph);
         }
+        wave_lds_sync();
+        for (int q = 0; q < nq; ++q) {
+            const VBond b = bonds[q0 + q];
+            if (t == b.i * L + b.j) {
+                ve.re += b.t * bc[q];
+                ve.im += b.t * bs[q];
+            }
+            if (t == b.j * L + b.i) {
+                ve.re += b.t * bc[q];
+                ve.im -= b.t * bs[q];
+            }
+        }
+        wave_lds_sync();
     }
-    __syncthreads();
-    for (int e = t; e < L * R; e += T) {  // W = V Q
+    if (t < L * L) V[t] = ve;
+    wave_lds_sync();
+    for (int e = t; e < L * R; e += 64) {  // W = V Q
         const int i = e / R, s = e % R;
-        double wr = 0.0, wi = 0.0;
+        c64 w = {0.0, 0.0};
         for (int j = 0; j < L; ++j) {
             const double q = Q[j * R + s];
-            wr += Vr[i * L + j] * q;
-            wi += Vi[i * L + j] * q;
+            w.re += V[i * L + j].re * q;
+            w.im += V[i * L + j].im * q;
         }
-        Wr[e] = wr;
-        Wi[e] = wi;
+        Wm[e] = w;
     }
-    __syncthreads();
-    for (int e = t; e < R * R; e += T) {  // L(k) = diag(w') + Q^T W, real form
+    wave_lds_sync();
+    for (int e = t; e < R * R; e += 64) {  // L(k) = diag(w') + Q^T W
         const int r = e / R, s = e % R;
-        double lr = r == s ? poles[r] : 0.0, li = 0.0;
+        c64 l = {r == s ? poles[r] : 0.0, 0.0};
         for (int i = 0; i < L; ++i) {
             const double q = Q[i * R + r];
-            lr += q * Wr[i * R + s];
-            li += q * Wi[i * R + s];
+            l.re += q * Wm[i * R + s].re;
+            l.im += q * Wm[i * R + s].im;
         }
-        Ms[r * n + s] = lr;
-        Ms[(r + R) * n + (s + R)] = lr;
-        Ms[r * n + (s + R)] = -li;
-        Ms[(r + R) * n + s] = li;
+        A[r * S + s] = l;
     }
-    __syncthreads();
-    jacobi_values_lds(Ms, n, 60, cs, sn, pa, pb, red);
-    if (t == 0) {
-        double neg = 0.0;
-        for (int r = 0; r < n; ++r) {
-            const double w = Ms[r * n + r];
-            if (w < 0.0) neg += w;
+    wave_lds_sync();
+    // Householder: column c's part below the subdiagonal is reflected away,
+    // leaving the subdiagonal's modulus in ee[c]
+    for (int c = 0; c < R - 1; ++c) {
+        const bool on = t > c && t < R;
+        c64 x = {0.0, 0.0};
+        if (on) xs[t] = x = A[t * S + c];
+        wave_lds_sync();
+        const c64 x0 = xs[c + 1];
+        double tail = 0.0;
+#pragma unroll 4
+        for (int s = c + 2; s < R; ++s) tail += xs[s].re * xs[s].re + xs[s].im * xs[s].im;
+        const double h0 = x0.re * x0.re + x0.im * x0.im;
+        const double a0 = sqrt(h0), nrm = sqrt(h0 + tail);
+        if (t == 0) ee[c] = nrm;
+        if (!(tail > 0.0)) {   // nothing to reflect
+            wave_lds_sync();
+            continue;
         }
-        per_k[k] = 0.5 * neg;
+        const double beta = 1.0 / (nrm * (nrm + a0));   // H = 1 - beta u u^H
+        const double f = a0 > 0.0 ? 1.0 + nrm / a0 : 0.0;
+        c64 u = x;
+        if (t == c + 1) {
+            u.re = a0 > 0.0 ? x0.re * f : nrm;
+            u.im = a0 > 0.0 ? x0.im * f : 0.0;
+            xs[t] = u;
+        }
+        wave_lds_sync();
+        // p = beta A u, w = p - (beta/2) (u^H p) u
+        c64 p = {0.0, 0.0};
+        const c64 *Ar = A + (on ? t : c + 1) * S;
+#pragma unroll 4
+        for (int s = c + 1; s < R; ++s) {
+            const c64 a = Ar[s], us = xs[s];
+            p.re = fma(a.re, us.re, fma(-a.im, us.im, p.re));
+            p.im = fma(a.re, us.im, fma(a.im, us.re, p.im));
+        }
+        p.re *= beta;
+        p.im *= beta;
+        if (on) ws[t] = p;
+        wave_lds_sync();
+        double up = 0.0;   // u^H p is real
+#pragma unroll 4
+        for (int s = c + 1; s < R; ++s) up += xs[s].re * ws[s].re + xs[s].im * ws[s].im;
+        const double K = 0.5 * beta * up;
+        const c64 w = {p.re - K * u.re, p.im - K * u.im};
+        wave_lds_sync();
+        if (on) ws[t] = w;
+        wave_lds_sync();
+        // A -= u w^H + w u^H
+        if (on) {
+            c64 *Aw = A + t * S;
+#pragma unroll 4
+            for (int s = c + 1; s < R; ++s) {
+                const c64 us = xs[s], w2 = ws[s];
+                c64 a = Aw[s];
+                a.re -= u.re * w2.re + u.im * w2.im + w.re * us.re + w.im * us.im;
+                a.im -= u.im * w2.re - u.re * w2.im + w.im * us.re - w.re * us.im;
+                Aw[s] = a;
+            }
+        }
+        wave_lds_sync();
+    }
+    // the real tridiagonal matrix: dd, and the squared moduli for the counts
+    const double d = t < R ? A[t * S + t].re : 0.0;
+    const double el = t > 0 && t < R ? ee[t - 1] : 0.0, er = t < R - 1 ? ee[t] : 0.0;
+    wave_lds_sync();
+    if (t < R) {
+        dd[t] = d;
+        ee[t] = er * er;
+    }
+    // Gershgorin bounds
+    double lo = t < R ? d - el - er : 0.0, hi = t < R ? d + el + er : 0.0;
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, o));
+        hi = fmax(hi, __shfl_xor(hi, o));
+    }
+    wave_lds_sync();
+    const double scale = fmax(fabs(lo), fabs(hi));
+    lo -= 1e-15 * scale;
+    const int nneg = sturm_below(R, dd, ee, 0.0);
+    double v = 0.0;
+    if (nneg > 0) {
+        // lane e g + j tests point j of g in the bracket of eigenvalue e
+        const int g = 64 / nneg, e = t / g, j = t - e * g;
+        double bl = lo, bh = 0.0;
+        for (int it = 0; it < 64; ++it) {
+            const bool wide = e < nneg && bh - bl > 2e-17 * scale && bl < bl + 0.5 * (bh - bl);
+            if (!__any(wide)) break;
+            auto point = [&](int i) { return bl + (bh - bl) * (double)(i + 1) / (double)(g + 1); };
+            const unsigned long long m = __ballot(e < nneg && sturm_below(R, dd, ee, point(j)) > e);
+            const unsigned long long mine =
+                e < nneg ? (m >> (e * g)) & (g < 64 ? (1ull << g) - 1ull : ~0ull) : 0ull;
+            const int first = mine ? __ffsll(mine) - 1 : g;
+            const double nl = first == 0 ? bl : point(first - 1);
+            bh = first == g ? bh : point(first);
+            bl = nl;
+        }
+        if (j == 0 && e < nneg) v = 0.5 * (bl + bh);
+        wave_lds_sync();
+        bc[t] = v;
+        wave_lds_sync();
+        if (t == 0) {
+            double neg = 0.0;
+            for (int i = 0; i < nneg; ++i) neg += bc[i * g];
+            per_k[k] = neg;
+        }
+    } else if (t == 0) {
+        per_k[k] = 0.0;
     }
 }
 
@@ -480,8 +535,8 @@ extern "C" int qcm_vca_omega(int32_t L, int32_t R, const double *h_poles, const 
     if (n_bonds > 0)
         QCM_HIP(hipMemcpyAsync(bd, hb.data(), sizeof(VBond) * n_bonds, hipMemcpyHostToDevice, s));
     QCM_HIP(hipMemcpyAsync(kd, h_k, sizeof(double) * 3 * n_k, hipMemcpyHostToDevice, s));
-    const size_t lds = sizeof(double) * 4 * (size_t)R * R;
-    k_vca_k<<<n_k, 256, lds, s>>>(L, R, po, Qd, dtd, bd, n_bonds, kd, pk);
+    const size_t lds = sizeof(c64) * (size_t)R * (R + 1);
+    k_vca_k<<<n_k, 64, lds, s>>>(L, R, po, Qd, dtd, bd, n_bonds, kd, pk);
     QCM_LAUNCH_CHECK();
     k_vca_sum<<<1, 256, 0, s>>>(pk, n_k, po, R, e0, od);
     QCM_LAUNCH_CHECK();
