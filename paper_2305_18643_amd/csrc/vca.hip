@@ -75,8 +75,10 @@ struct VBond {
 // lane from LDS (broadcast reads that can be in flight together) instead of
 // by six dependent shuffles, and the eigenvalues, wanted only where negative,
 // share the lanes: with n of them, 64 / n points of each bracket per Sturm
-// count.  R = 24, 1,024 wave-vectors: 2.7 ms as a parallel Jacobi method on
-// the real 48 x 48 form in one workgroup each.
+// count.  R = 24, 1,024 wave-vectors: 0.13 ms, against 2.7 ms as a parallel
+// Jacobi method on the real 48 x 48 form in one workgroup each.  Error of the
+// sum relative to |L|, rms: 7e-16 (R = 24) and 1.2e-15 (R = 64), Jacobi 1.4e-14
+// and 7.4e-14.
 struct alignas(16) c64 {
     double re, im;
 };
