@@ -545,7 +545,9 @@ extern "C" int qcm_green_cf(const qcm_model *m, const qcm_basis *gs, const doubl
         QCM_TRY(engine_normalize_from_partials(e, s));
         e.lazy = 1;   // only the coefficients are kept
         std::vector<int32_t> done(npairs);
-        for (int step = 0; step < maxs; ++step) {
+        int ran = 0;
+        QCM_TRY(engine_run_chains(e, maxs, &ran, s));
+        for (int step = 0; step < maxs && !ran; ++step) {
             QCM_TRY(engine_step(e, step, s));
             if ((step + 1) % 32 == 0 && step + 1 < maxs) {
                 QCM_HIP(hipMemcpyAsync(done.data(), e.cs.done, sizeof(int32_t) * npairs,

@@ -454,6 +454,28 @@ int engine_step(Engine &e, int n, hipStream_t s) {
     return step_t<float>(e, n, s);
 }
 
+// Coefficients of n steps from normalised start vectors, in one launch where
+// the sector fits (*ran), by LDS and by the sums' layout: one norm chunk, at
+// most 64 product blocks.  The vectors are left as they were.
+int engine_run_chains(Engine &e, int n, int *ran, hipStream_t s) {
+    *ran = 0;
+    const HvOp &op = e.op;
+    if (!e.fused || !op.hu.pk || e.nchunks != 1 || e.nblk > 64 || hv_one(op.up.d, e.rows)) return QCM_OK;
+    const OneSrc src{engine_group(e, 0)};
+    const int nlut = op.md.u_uniform >= 0.0 ? 0 : op.md.nbytes * 256;
+    const size_t lds = chain_lds(op.up.d, op.dn.d, src.g.wu, (src.g.wd + 3) & ~3, src.g.nctab, nlut,
+                                 e.reorth ? 5 : 3, e.nblk, e.prec == QCM_FP64 ? 8 : 4)
+                           .bytes;
+    if (lds > 158 * 1024) return QCM_OK;   // 160 KB less the kernel's own few words
+    if (e.prec == QCM_FP64)
+        ks_chain<double><<<e.nvec, kChainThreads, lds, s>>>(src, n);
+    else
+        ks_chain<float><<<e.nvec, kChainThreads, lds, s>>>(src, n);
+    QCM_LAUNCH_CHECK();
+    *ran = 1;
+    return QCM_OK;
+}
+
 // The deferred update as its own pass (the update pass of the step before the
 // rotation: w was its w, v its v, vp its vp).
 template <typename T>

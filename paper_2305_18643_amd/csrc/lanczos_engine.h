@@ -63,6 +63,7 @@ int engine_seed(Engine &e, uint64_t seed, const void *v0, hipStream_t s);
 int engine_normalize(Engine &e, hipStream_t s);
 int engine_step(Engine &e, int n, hipStream_t s);
 int engine_settle(Engine &e, hipStream_t s);
+int engine_run_chains(Engine &e, int n, int *ran, hipStream_t s);
 int engine_accum(Engine &e, double *psi, const double *coef, int n, hipStream_t s);
 int engine_normalize_from_partials(Engine &e, hipStream_t s);
 int psi_finalize(Engine &e, double *psi, hipStream_t s);

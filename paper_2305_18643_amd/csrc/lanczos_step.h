@@ -996,6 +996,279 @@ __global__ void __launch_bounds__(256) ks_update(Src src) {
     }
 }
 
+// Whole chains of a small sector in one launch: a workgroup runs the steps of
+// one chain from LDS.
+//
+// A step of a sector of a few thousand states is otherwise three launches of
+// 3 to 12 us each, all latency: 10 chains of 3,920 states (the Green function
+// of an 8-orbital impurity) took 25 us a step.  Here the three vectors, the hop
+// lists and the diagonal's tables stay in LDS and nothing is read from memory
+// between the first and the last step.  Every sum is the one of the separate
+// kernels (the element's terms in list order; the dots per product block over
+// 256 threads and a tree; the direct norm over a chunk), so the coefficients
+// are the same bit for bit: 7.6 us a step for the same chains, of which about 5
+// are LDS reads (hop entry, neighbour, coefficient).  More workgroups per chain
+// would have to exchange the vector through memory.  Rows lie du + 1 apart with a zero after each and a
+// zero row at the end: hop lists are read four at a time, and entries past a
+// string's own read a zero.
+constexpr int kChainThreads = 1024;
+
+struct ChainLds {
+    size_t v, sh, part, ct, lut, su, eu, sd, ed, nu, nd, pk, cl, cf, bytes;
+};
+__host__ __device__ inline ChainLds chain_lds(int64_t du, int64_t dn, int wu, int wd, int nctab,
+                                              int nlut, int na, int nblk, size_t s) {
+    ChainLds l;
+    size_t o = 0;
+    auto take = [&](size_t n) {
+        const size_t at = o;
+        o = (o + n + 15) & ~(size_t)15;
+        return at;
+    };
+    l.v = take(3 * s * (size_t)(dn + 1) * (size_t)(du + 1));
+    l.sh = take(sizeof(double) * na * kChainThreads);
+    l.part = take(sizeof(double) * na * nblk);
+    l.ct = take(sizeof(double) * nctab);
+    l.lut = take(sizeof(double) * nlut);
+    l.eu = take(sizeof(double) * du);
+    l.ed = take(sizeof(double) * dn);
+    l.cf = take(sizeof(double) * wd * dn);
+    l.cl = take(sizeof(int32_t) * wd * dn);
+    l.pk = take(sizeof(uint32_t) * wu * du);
+    l.su = take(sizeof(uint32_t) * du);
+    l.sd = take(sizeof(uint32_t) * dn);
+    l.nu = take(sizeof(int32_t) * du);
+    l.nd = take(sizeof(int32_t) * dn);
+    l.bytes = o;
+    return l;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kChainThreads) ks_chain(const OneSrc src, const int n1) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ double tot[5], sc[5];   // sums of the dots; a, c1, c2, inv, beta
+    __shared__ int flag[2];            // direct norm wanted; chain stopped
+    const BGroup &q = src.g;
+    const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int NT = kChainThreads;
+    const int du = (int)q.d_up, dn = (int)q.d_dn, d = (int)q.dim, wd = (q.wd + 3) & ~3, wu = q.wu;
+    const int nlut = q.u_uniform >= 0.0 ? 0 : q.nbytes * 256, na = q.reorth ? 5 : 3;
+    const ChainLds o = chain_lds(du, dn, wu, wd, q.nctab, nlut, na, q.nblk, sizeof(T));
+    const int st = du + 1, vlen = (dn + 1) * st;
+    T *bvp = reinterpret_cast<T *>(smem_raw + o.v), *bv = bvp + vlen, *bw = bv + vlen;
+    double *sh = (double *)(smem_raw + o.sh), *part = (double *)(smem_raw + o.part);
+    double *ct = (double *)(smem_raw + o.ct), *lut = (double *)(smem_raw + o.lut);
+    double *eu = (double *)(smem_raw + o.eu), *ed = (double *)(smem_raw + o.ed);
+    double *cf = (double *)(smem_raw + o.cf);
+    int32_t *cl = (int32_t *)(smem_raw + o.cl), *nu = (int32_t *)(smem_raw + o.nu);
+    int32_t *nd = (int32_t *)(smem_raw + o.nd);
+    uint32_t *pk = (uint32_t *)(smem_raw + o.pk), *su = (uint32_t *)(smem_raw + o.su);
+    uint32_t *sd = (uint32_t *)(smem_raw + o.sd);
+    for (int k = tid; k < q.nctab; k += NT) ct[k] = q.ctab[k];
+    for (int k = tid; k < nlut; k += NT) lut[k] = q.ulut[k];
+    for (int k = tid; k < wu * du; k += NT) pk[k] = q.pku[k];
+    for (int k = tid; k < du; k += NT) {
+        su[k] = q.su[k];
+        eu[k] = q.eu[k];
+        nu[k] = q.nhu[k] & 0xffff;
+    }
+    for (int i = tid; i < dn; i += NT) {
+        sd[i] = q.sd[i];
+        ed[i] = q.ed[i];
+        const int n = q.nhd[i];
+        nd[i] = n;
+        for (int s = 0; s < wd; ++s) {
+            cl[i * wd + s] = s < n ? q.cold[i * q.wd + s] * st : dn * st;
+            cf[i * wd + s] = s < n ? q.cfd[i * q.wd + s] : 0.0;
+        }
+    }
+    for (int k = tid; k < 3 * vlen; k += NT) bvp[k] = T(0);
+    __syncthreads();
+    // e / du for e < 2^16: M = ceil(2^32 / du), and du = 1 apart
+    const uint32_t M = 0xffffffffu / (uint32_t)du + 1u;
+    auto row_of = [&](int e) { return du == 1 ? e : (int)__umulhi((uint32_t)e, M); };
+    const T *gv = (const T *)q.v + (int64_t)c * d;
+    for (int e = tid; e < d; e += NT) bv[e + row_of(e)] = gv[e];
+    const ChainState &cs = q.cs;
+    double amax = 0.0;
+    int done = 0, len = 0;
+    if (tid == 0) {
+        amax = cs.amax[c];
+        done = cs.done[c];
+        len = cs.len[c];
+        flag[1] = done;
+        sc[4] = 0.0;
+    }
+    const double uu = q.u_uniform;
+    double *const al = cs.alpha + (int64_t)c * cs.maxs, *const be = cs.beta + (int64_t)c * cs.maxs;
+    __syncthreads();
+    for (int n = 0; n < n1; ++n) {
+        if (flag[1]) break;   // nothing after a stopped chain's last step is read
+        // w = H v - beta' vp
+        const double b = sc[4];
+        for (int e = tid; e < d; e += NT) {
+            const int idn = row_of(e), iu = e - idn * du, at = e + idn;
+            const T *row = bv + idn * st;
+            const uint32_t dbl = su[iu] & sd[idn];
+            double diag = eu[iu] + ed[idn];
+            if (uu >= 0.0) {
+                diag += uu * (double)__popc(dbl);
+            } else {
+                for (int byte = 0; byte < q.nbytes; ++byte)
+                    diag += lut[byte * 256 + ((dbl >> (8 * byte)) & 255u)];
+            }
+            double acc = diag * (double)bv[at];
+            const uint32_t *pe = pk + iu;
+            const int nh = nu[iu];
+            for (int s = 0; s < nh; s += 4) {
+                uint32_t p[4];
+                double x[4], cc[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) p[u] = pe[(s + u) * du];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[u] = (double)row[p[u] & 0xffffu];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) cc[u] = ct[(p[u] >> 16) & 0x3ffu];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) acc = fma(cc[u], x[u], acc);
+            }
+            const T *col = bv + iu;
+            const int nhd = nd[idn], l0 = idn * wd;
+            for (int s = 0; s < nhd; s += 4) {
+                double x[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[u] = (double)col[cl[l0 + s + u]];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) acc = fma(cf[l0 + s + u], x[u], acc);
+            }
+            if (n > 0) acc = fma(-b, (double)bvp[at], acc);
+            bw[at] = (T)acc;
+        }
+        __syncthreads();
+        // the dots per product block
+        for (int b0 = 0; b0 < q.nblk; b0 += NT / 256) {
+            const int blk = b0 + (tid >> 8), t = tid & 255;
+            double s5[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+            if (blk < q.nblk) {
+                const int e0 = blk * q.rows * du, e1 = min(e0 + q.rows * du, d);
+                for (int e = e0 + t; e < e1; e += 256) {
+                    const int at = e + row_of(e);
+                    const double wdv = (double)bw[at], vi = (double)bv[at];
+                    s5[0] = fma(vi, wdv, s5[0]);
+                    s5[1] = fma(wdv, wdv, s5[1]);
+                    s5[2] = fma(vi, vi, s5[2]);
+                    if (q.reorth) {
+                        const double pv = n > 0 ? (double)bvp[at] : 0.0;
+                        s5[3] = fma(pv, wdv, s5[3]);
+                        s5[4] = fma(pv, vi, s5[4]);
+                    }
+                }
+            }
+            if (b0 > 0) __syncthreads();
+            for (int a = 0; a < na; ++a) sh[a * NT + tid] = s5[a];
+            __syncthreads();
+            for (int k = wave; k < na * (NT / 256); k += NT / 64) {
+                const int g = k / na, a = k - g * na;
+                const double *x = sh + a * NT + g * 256;
+                double t2 = (x[lane] + x[lane + 128]) + (x[lane + 64] + x[lane + 192]);
+                for (int r = 32; r > 0; r >>= 1) t2 += __shfl_down(t2, r);
+                if (lane == 0 && b0 + g < q.nblk) part[a * q.nblk + b0 + g] = t2;
+            }
+        }
+        __syncthreads();
+        if (wave < na) {   // nblk <= 64: the other leaves of the tree are zero
+            double t2 = lane < q.nblk ? part[wave * q.nblk + lane] : 0.0;
+            for (int r = 32; r > 0; r >>= 1) t2 += __shfl_down(t2, r);
+            if (lane == 0) tot[wave] = t2;
+        }
+        __syncthreads();
+        double a = 0.0, s0 = 0.0, s1 = 0.0, s2 = 0.0;
+        // beta_n and the bookkeeping (finish_beta)
+        auto beta_of = [&]() {
+            if (q.reorth) al[n] = a + s1;
+            const double bb = s0 - s1 * s1 - s2 * s2;
+            const double bn = sqrt(bb > 0.0 ? bb : 0.0);
+            be[n] = bn;
+            const double am = amax > 0.0 ? amax : 1.0;
+            if (!(bn >= cs.btol * am)) done = 1;
+            len = n + 1;
+            sc[0] = a;
+            sc[1] = s1;
+            sc[2] = s2;
+            sc[3] = done ? 0.0 : 1.0 / bn;
+            sc[4] = bn;
+            flag[1] = done;
+        };
+        if (tid == 0) {
+            const double ww = tot[1], vv = tot[2];
+            a = tot[0];
+            al[n] = a;
+            if (fabs(a) > amax) amax = fabs(a);
+            s0 = fma(a * a, vv, fma(-2.0 * a, a, ww));
+            s1 = q.reorth ? fma(-a, vv, a) : 0.0;
+            s2 = q.reorth ? fma(-a, tot[4], tot[3]) : 0.0;
+            flag[0] = !(s0 > kDotRel * ww);
+            sc[0] = a;
+            if (!flag[0]) beta_of();
+        }
+        __syncthreads();
+        if (flag[0]) {
+            // the direct norm (one chunk: d <= kChunk)
+            double r[3] = {0.0, 0.0, 0.0};
+            if (tid < 256) {
+                const double an = sc[0];
+                for (int e = tid; e < d; e += 256) {
+                    const int at = e + row_of(e);
+                    const double vi = (double)bv[at], x = fma(-an, vi, (double)bw[at]);
+                    r[0] = fma(x, x, r[0]);
+                    if (q.reorth) {
+                        r[1] = fma(vi, x, r[1]);
+                        r[2] = fma((double)bvp[at], x, r[2]);
+                    }
+                }
+                for (int k = 0; k < 3; ++k) sh[k * NT + tid] = r[k];
+            }
+            __syncthreads();
+            if (wave < 3) {
+                const double *x = sh + wave * NT;
+                double t2 = (x[lane] + x[lane + 128]) + (x[lane + 64] + x[lane + 192]);
+                for (int k = 32; k > 0; k >>= 1) t2 += __shfl_down(t2, k);
+                if (lane == 0) tot[wave] = t2;
+            }
+            __syncthreads();
+            if (tid == 0) {
+                s0 = tot[0];
+                s1 = q.reorth ? tot[1] : 0.0;
+                s2 = q.reorth ? tot[2] : 0.0;
+                beta_of();
+            }
+            __syncthreads();
+        }
+        // v_{n+1} in the place of w
+        const double an = sc[0], c1 = sc[1], c2 = sc[2], inv = sc[3];
+        for (int e = tid; e < d; e += NT) {
+            const int at = e + row_of(e);
+            const double vi = (double)bv[at];
+            double x = fma(-an, vi, (double)bw[at]);
+            if (q.reorth) {
+                x = fma(-c1, vi, x);
+                x = fma(-c2, (double)bvp[at], x);
+            }
+            bw[at] = (T)(x * inv);
+        }
+        T *const t3 = bvp;
+        bvp = bv;
+        bv = bw;
+        bw = t3;
+        __syncthreads();
+    }
+    if (tid == 0) {
+        cs.amax[c] = amax;
+        cs.done[c] = done;
+        cs.len[c] = len;
+    }
+}
+
 // psi += svec[n] v_n alone (the last replay step)
 template <typename T, class Src>
 __global__ void __launch_bounds__(256) ks_accum(Src src) {
