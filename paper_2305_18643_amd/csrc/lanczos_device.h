@@ -11,6 +11,18 @@
 
 namespace qcm {
 
+// LDS written by a wave's lanes is read by its others
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// x of lane l (wave-uniform)
+__device__ __forceinline__ int64_t wave_read(int64_t x, int l) {
+    return (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)x, l) |
+           ((int64_t)__builtin_amdgcn_readlane((int)(x >> 32), l) << 32);
+}
+
 template <typename T>
 __device__ __forceinline__ double ldd(const T *p) {
     return (double)*p;

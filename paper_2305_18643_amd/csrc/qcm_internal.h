@@ -140,7 +140,7 @@ int build_hop_tables(const ModelDev &md, const SpinTables &st, Carver &cv, HopTa
 // ---------------------------------------------------------------- H.v
 // The stored matrix of a symmetry-adapted sector (sym.hip): rows of H in CSR.
 struct SymCsrDev {
-    int64_t dim = 0;
+    int64_t dim = 0, nnz = 0;
     const int64_t *rowptr = nullptr;
     const uint32_t *col = nullptr;
     const double *val = nullptr;

@@ -19,12 +19,14 @@
 //    by column.  A first launch counts them per row, a second writes them.
 //  * k_sym_spmv: w = H v over the stored rows, eight lanes per row, each
 //    lane striding the row and the eight partial sums added by a fixed
-//    butterfly.
+//    butterfly.  k_sym_spmv_pk: the same from the packed elements, one row per
+//    lane, the elements of a wave's rows staged in LDS.
 #include <math.h>
 #include <string.h>
 
 #include <vector>
 
+#include "lanczos_device.h"
 #include "lanczos_engine.h"
 #include "qcm_internal.h"
 
@@ -36,7 +38,11 @@ constexpr int kSymE = 2 * kSymBonds + 1;   // entries of one column before mergi
 constexpr int kCsrWaves = 4;               // columns per 256-thread workgroup
 constexpr int kScanB = 1024;               // elements per prefix-sum block
 constexpr int kSpmvLanes = 8;              // lanes per stored row (explicit elements)
-constexpr int kPkLanes = 4;                // lanes per stored row (packed elements)
+constexpr int kSpmvAhead = 4;              // elements of a lane read together
+constexpr int kPkWaves = 4;                // waves of 64 rows per workgroup (packed elements)
+constexpr int kPkAhead = 8;                // gathers of a row in flight
+constexpr int kPkCopies = 4;               // 16-byte copies of a lane in flight
+constexpr int kSymRun = 64;                // consecutive workgroups of one XCD
 constexpr int kMaxVals = QCM_SYM_MAX_VALUES;
 constexpr int kColBits = 26;               // packed element: column in the low 26 bits
 constexpr uint32_t kColMask = (1u << kColBits) - 1u;
@@ -337,6 +343,19 @@ __global__ void __launch_bounds__(256)
     }
 }
 
+// This workgroup's place among the rows: each XCD (workgroup mod 8) takes runs
+// of kSymRun.  The last, incomplete set of runs stays in order.
+__device__ __forceinline__ int64_t sym_block() {
+    const uint32_t set = blockIdx.x / (8 * kSymRun), in = blockIdx.x % (8 * kSymRun);
+    if ((int64_t)(set + 1) * (8 * kSymRun) > gridDim.x) return blockIdx.x;
+    return (int64_t)set * (8 * kSymRun) + (in & 7) * kSymRun + (in >> 3);
+}
+
+// w = H v from the explicit elements, kSpmvLanes lanes per row.  The loads of
+// kSpmvAhead elements of a lane are in flight together (a row of up to 32 in
+// one go): one at a time, the chain row pointer - column - neighbour was waited
+// for at every element.  41.4 M rows of 28 elements: 4.73 -> 3.80 ms, of which
+// the 14 GB of elements take 2.9.
 __global__ void __launch_bounds__(256)
     k_sym_spmv(const int64_t *__restrict__ rowptr, const uint32_t *__restrict__ col,
                const double *__restrict__ val, int64_t dim, const double *__restrict__ v,
@@ -347,35 +366,120 @@ __global__ void __launch_bounds__(256)
     double acc = 0.0;
     if (r < dim) {
         const int64_t e = rowptr[r + 1];
-        for (int64_t k = rowptr[r] + sub; k < e; k += kSpmvLanes)
-            acc = fma(val[k], v[off + col[k]], acc);
+        for (int64_t k = rowptr[r] + sub; k < e; k += kSpmvLanes * kSpmvAhead) {
+            uint32_t x[kSpmvAhead];
+            double a[kSpmvAhead], y[kSpmvAhead];
+#pragma unroll
+            for (int u = 0; u < kSpmvAhead; ++u) {
+                const int64_t at = min(k + u * kSpmvLanes, e - 1);
+                x[u] = col[at];
+                a[u] = val[at];
+            }
+#pragma unroll
+            for (int u = 0; u < kSpmvAhead; ++u) y[u] = v[off + x[u]];
+#pragma unroll
+            for (int u = 0; u < kSpmvAhead; ++u) {
+                const double t = fma(a[u], y[u], acc);
+                acc = k + u * kSpmvLanes < e ? t : acc;
+            }
+        }
     }
     for (int m = kSpmvLanes / 2; m > 0; m >>= 1) acc += __shfl_xor(acc, m);
     if (sub == 0 && r < dim) w[off + r] = acc;
 }
 
-// w = H v from the packed elements (kPkLanes lanes per row: with 4-byte
-// elements, more rows per wave in flight pay more than longer row segments)
-__global__ void __launch_bounds__(256)
+// w = H v from the packed elements, one row per lane.
+//
+// The product is bound by its gathers: an instruction whose 64 lanes read 64
+// lines takes the address unit that many cycles.  Lanes on consecutive rows
+// share lines (one hop moves consecutive strings to consecutive strings), half
+// of them in the 4 x 4 cluster (721 M line reads for 1.16 G elements; four
+// lanes on each row shared none).  Read by its own lane, a row's elements would
+// be 64 separate streams, so a wave copies those of its rows to LDS, 16 bytes a
+// lane, and each lane reads its own from there: as many rows at a time as fit
+// the window.  Eight gathers of a lane are in flight together.  Each XCD takes
+// runs of kSymRun workgroups, so that the neighbours of its rows stay in its
+// own L2 (9.1 GB fetched in place of 15.3; longer runs save no more).
+// 41.4 M rows of 28 elements: 3.29 ms as four lanes per row with one gather at a time; 2.29 with eight;
+// 2.02 one row per lane; 1.95 with 16-byte copies: 4.9 TB/s, the card's rate.
+//
+// A row's sum is four partial sums, of the elements at 0..3 mod 4, added in
+// pairs.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));   // rows start anywhere
+
+__global__ void __launch_bounds__(kPkWaves * 64)
     k_sym_spmv_pk(const int64_t *__restrict__ rowptr, const uint32_t *__restrict__ pk,
-                  const double *__restrict__ table, int64_t dim, const double *__restrict__ v,
-                  double *__restrict__ w) {
+                  const double *__restrict__ table, int64_t dim, int window,
+                  const double *__restrict__ v, double *__restrict__ w) {
+    extern __shared__ __align__(16) uint32_t xs[];   // [kPkWaves][window]
     __shared__ double tab[kMaxVals];
+    static_assert(kMaxVals <= kPkWaves * 64, "one table entry per thread");
     if (threadIdx.x < kMaxVals) tab[threadIdx.x] = table[threadIdx.x];
     __syncthreads();
-    const int64_t r = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kPkLanes;
-    const int sub = threadIdx.x & (kPkLanes - 1);
-    const int64_t off = (int64_t)blockIdx.y * dim;
-    double acc = 0.0;
-    if (r < dim) {
-        const int64_t e = rowptr[r + 1];
-        for (int64_t k = rowptr[r] + sub; k < e; k += kPkLanes) {
-            const uint32_t x = pk[k];
-            acc = fma(tab[x >> kColBits], v[off + (x & kColMask)], acc);
+    const int64_t bx = sym_block();
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t r0 = (bx * kPkWaves + wave) * 64, r = r0 + lane;
+    if (r0 >= dim) return;
+    const int64_t kl0 = rowptr[min(r, dim)], kl1 = rowptr[min(r + 1, dim)];
+    const char *vb = (const char *)(v + (int64_t)blockIdx.y * dim);
+    uint32_t *xw = xs + (size_t)wave * window;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    auto value = [&](uint32_t x) { return *(const double *)(vb + ((x & kColMask) << 3)); };
+    auto row = [&](const uint32_t *q, int n) {
+        int j = 0;
+        for (; j + kPkAhead <= n; j += kPkAhead) {
+            uint32_t x[kPkAhead];
+            double y[kPkAhead];
+#pragma unroll
+            for (int u = 0; u < kPkAhead; ++u) x[u] = q[j + u];
+#pragma unroll
+            for (int u = 0; u < kPkAhead; ++u) y[u] = value(x[u]);
+#pragma unroll
+            for (int u = 0; u < kPkAhead; ++u)
+                acc[u & 3] = fma(tab[x[u] >> kColBits], y[u], acc[u & 3]);
         }
+        for (; j < n; j += 4) {
+            uint32_t x[4];
+            double y[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = q[min(j + u, n - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) y[u] = value(x[u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const double t = fma(tab[x[u] >> kColBits], y[u], acc[u]);
+                acc[u] = j + u < n ? t : acc[u];
+            }
+        }
+    };
+    for (int i0 = 0; i0 < 64;) {
+        const int64_t kb = wave_read(kl0, i0);
+        const int i1 = __popcll(__ballot(kl1 - kb <= window));   // row ends ascend
+        if (i1 <= i0) {   // a row longer than the window
+            if (lane == i0) row(pk + kl0, (int)(kl1 - kl0));
+            ++i0;
+            continue;
+        }
+        const int cnt = (int)(wave_read(kl1, i1 - 1) - kb), nv = cnt & ~3;
+        const uint32_t *p = pk + kb;
+        if (nv)
+            for (int j = 4 * lane; j - 4 * lane < nv; j += 256 * kPkCopies) {
+                u32x4 x[kPkCopies];
+#pragma unroll
+                for (int u = 0; u < kPkCopies; ++u)
+                    x[u] = *(const u32x4u *)(p + min(j + 256 * u, nv - 4));
+#pragma unroll
+                for (int u = 0; u < kPkCopies; ++u)
+                    if (j + 256 * u < nv) *(u32x4 *)(xw + j + 256 * u) = x[u];
+            }
+        if (lane < (cnt & 3)) xw[nv + lane] = p[nv + lane];
+        wave_lds_sync();
+        if (lane >= i0 && lane < i1) row(xw + (int)(kl0 - kb), (int)(kl1 - kl0));
+        wave_lds_sync();
+        i0 = i1;
     }
-    for (int m = kPkLanes / 2; m > 0; m >>= 1) acc += __shfl_xor(acc, m);
-    if (sub == 0 && r < dim) w[off + r] = acc;
+    if (r < dim) w[(int64_t)blockIdx.y * dim + r] = (acc[0] + acc[2]) + (acc[1] + acc[3]);
 }
 
 __device__ __forceinline__ uint32_t mix64(unsigned long long x) {
@@ -610,8 +714,14 @@ static int model_args(const qcm_model *m, const qcm_sym_sector *s, SymModelDev *
 int sym_hv_launch(const SymCsrDev &h, const double *v, double *w, int nvec, hipStream_t s) {
     if (h.dim == 0 || nvec == 0) return QCM_OK;
     if (h.pk) {
-        const dim3 grid((unsigned)ceil_div((size_t)h.dim * kPkLanes, 256), (unsigned)nvec);
-        k_sym_spmv_pk<<<grid, 256, 0, s>>>(h.rowptr, h.pk, h.tab, h.dim, v, w);
+        // a window of a wave's 64 rows and a third (1.94 ms, against 1.97 with a
+        // twentieth: fewer second windows), and at most 4,096 elements, which
+        // leave a CU eight waves
+        const double rows = 64.0 * (double)h.nnz / (double)h.dim;
+        const int window = (int)fmin(fmax(ceil(rows * (4.0 / 3.0) / 64.0) * 64.0, 256.0), 4096.0);
+        const dim3 grid((unsigned)ceil_div((size_t)h.dim, kPkWaves * 64), (unsigned)nvec);
+        k_sym_spmv_pk<<<grid, kPkWaves * 64, sizeof(uint32_t) * kPkWaves * window, s>>>(
+            h.rowptr, h.pk, h.tab, h.dim, window, v, w);
     } else {
         const dim3 grid((unsigned)ceil_div((size_t)h.dim * kSpmvLanes, 256), (unsigned)nvec);
         k_sym_spmv<<<grid, 256, 0, s>>>(h.rowptr, h.col, h.val, h.dim, v, w);
@@ -756,6 +866,7 @@ static int check_csr(const qcm_sym_csr *h, const char *fn) {
 static SymCsrDev csr_dev(const qcm_sym_csr *h) {
     SymCsrDev d;
     d.dim = h->dim;
+    d.nnz = h->nnz;
     d.rowptr = h->rowptr;
     d.col = h->col;
     d.val = h->val;

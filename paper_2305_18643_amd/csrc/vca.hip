@@ -82,10 +82,6 @@ struct VBond {
 struct alignas(16) c64 {
     double re, im;
 };
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
 
 __global__ void __launch_bounds__(64) k_vca_k(int L, int R, const double *__restrict__ poles,
                                               const double *__restrict__ Q,
