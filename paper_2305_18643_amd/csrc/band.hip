@@ -66,12 +66,14 @@ __global__ void __launch_bounds__(256) kbl_dots(const T *__restrict__ base, int6
     if (threadIdx.x == 0) partial[(int64_t)q * nchunks + blockIdx.x] = s;
 }
 
-// res[q] = sum of the partials of sum q (fixed order), stored as `put` says
+// res[q] = sum of the partials of sum q (fixed order), stored as `put` says;
+// host (pinned, or null) takes the first sum and the scale
 __global__ void __launch_bounds__(256) kbl_finish(const double *__restrict__ partial, int nchunks,
                                                   Put put, double *__restrict__ res,
                                                   double *__restrict__ Tm, int ldt,
                                                   double *__restrict__ rho, int p,
-                                                  double *__restrict__ scal) {
+                                                  double *__restrict__ scal,
+                                                  double *__restrict__ host) {
     __shared__ double sh[256];
     const int q = blockIdx.x;
     double acc = 0.0;
@@ -79,6 +81,10 @@ __global__ void __launch_bounds__(256) kbl_finish(const double *__restrict__ par
     const double s = block_sum(acc, sh);
     if (threadIdx.x != 0) return;
     res[q] = s;
+    if (host && q == 0) {
+        host[0] = s;
+        host[1] = scal[1];
+    }
     const int i = put.i[q], k = put.k[q];
     switch (put.mode[q]) {
         case 0:
@@ -128,6 +134,70 @@ __global__ void __launch_bounds__(256) kbl_sub_band(T *__restrict__ base, int64_
             x = fma(-c, ldd(base + vs.off[q] + e), x);
         }
         w[e] = (T)x;
+    }
+}
+
+// A step's part after w = H v_j, for vectors of one chunk: kbl_sub_band, then
+// kbl_dots, kbl_finish and kbl_axpys for v_j and each look-back vector (ks, in
+// order; kput: where its sum goes), kbl_dots of the next candidate (at xo) with
+// w, and kbl_finish of the next step's pc sums, whose first goes to the host with
+// the scale.  One workgroup with w in LDS; the sums and their order are those of
+// the separate kernels.  Six launches of 2 to 4 us and as many gaps became one:
+// a band of 24 vectors in a sector of 24 states is all launches (functional
+// value 4.2 -> 2.6 ms, with the host reading pinned memory instead of two
+// copies).
+template <typename T>
+__global__ void __launch_bounds__(256) kbl_tail(T *__restrict__ base, int64_t wo, VecList vs,
+                                                Put idx, VecList ks, Put kput, int64_t xo, int pc,
+                                                int64_t dim, double *__restrict__ Tm, int ldt,
+                                                double *__restrict__ scal,
+                                                double *__restrict__ ahead,
+                                                double *__restrict__ res,
+                                                double *__restrict__ host) {
+    extern __shared__ __align__(16) unsigned char tail_raw[];
+    __shared__ double sh[256];
+    T *w = reinterpret_cast<T *>(tail_raw);   // each thread its own elements
+    const int t = threadIdx.x, n = (int)dim;
+    for (int e = t; e < n; e += 256) {
+        double x = ldd(base + wo + e);
+        for (int q = 0; q < vs.n; ++q) {
+            const double c = Tm[(int64_t)idx.i[q] * ldt + idx.k[q]];
+            x = fma(-c, ldd(base + vs.off[q] + e), x);
+        }
+        w[e] = (T)x;
+    }
+    double scale = t == 0 ? scal[1] : 0.0;
+    for (int q = 0; q < ks.n; ++q) {
+        const T *x = base + ks.off[q];
+        double acc = 0.0;
+        for (int e = t; e < n; e += 256) acc = fma(ldd(x + e), (double)w[e], acc);
+        const double c = block_sum(acc, sh);
+        if (t == 0) {
+            const int i = kput.i[q], k = kput.k[q];
+            if (kput.mode[q] == 3) {
+                Tm[(int64_t)i * ldt + i] = c;
+                if (fabs(c) > scale) scale = fabs(c);
+            } else {
+                Tm[(int64_t)i * ldt + k] = c;
+                Tm[(int64_t)k * ldt + i] = c;
+            }
+        }
+        for (int e = t; e < n; e += 256) w[e] = (T)fma(-c, ldd(x + e), (double)w[e]);
+    }
+    double acc = 0.0;
+    for (int e = t; e < n; e += 256) {
+        base[wo + e] = w[e];
+        const double wi = (double)w[e];
+        acc = fma(xo == wo ? wi : ldd(base + xo + e), wi, acc);
+    }
+    const double c = block_sum(acc, sh);
+    if (t < pc - 1) res[t] = ahead[t];
+    if (t == 0) {
+        ahead[pc - 1] = c;
+        res[pc - 1] = c;
+        scal[1] = scale;
+        host[0] = pc > 1 ? ahead[0] : c;
+        host[1] = scale;
     }
 }
 
@@ -617,8 +687,8 @@ static int band_run(const qcm_band_opts *o, BandPart &P, const double *d_gs, int
     int pc = p;
     double scale = 1.0;
     int j = 0;
-    double host[2];
-    bool ahead = false;
+    bool ahead = false;   // the next step's dots are in P.ahead
+    bool sent = false;    // and their sums in P.res, the first in host memory
     bool have_prev = false;
     double theta_prev = 0.0;
     // The paper's stopping rule, once per block: the lowest eigenvalue of T_j
@@ -632,7 +702,8 @@ static int band_run(const qcm_band_opts *o, BandPart &P, const double *d_gs, int
     int stop_at = 0;  // basis size a finished test stopped the part at
     bool near = false;
     double prev_d = 0.0;  // the change of the lowest eigenvalue at the last test
-    if (o->etol > 0.0) QCM_TRY(side.lease());
+    QCM_TRY(side.lease());
+    double *const host = (double *)side.pinned + 8;   // past the tests' word
     // take the result of the test in flight, waiting for it or only if done
     auto settle = [&](bool wait) -> int {
         if (!pend_j) return QCM_OK;
@@ -678,13 +749,15 @@ static int band_run(const qcm_band_opts *o, BandPart &P, const double *d_gs, int
                 kbl_dots<T><<<dim3(nch, pc), 256, 0, s>>>(base, off(cand[j]), ys, dim, nch,
                                                           P.ahead);
             }
-            Put raw{};
-            raw.n = pc;
-            for (int q = 0; q < pc; ++q) raw.mode[q] = 2;
-            kbl_finish<<<pc, 256, 0, s>>>(P.ahead, nch, raw, P.res, P.Tm, ldt, P.rho, p, P.scal);
-            QCM_LAUNCH_CHECK();
-            QCM_HIP(hipMemcpyAsync(host, P.res, sizeof(double), hipMemcpyDeviceToHost, s));
-            QCM_HIP(hipMemcpyAsync(host + 1, P.scal + 1, sizeof(double), hipMemcpyDeviceToHost, s));
+            if (!sent) {
+                Put raw{};
+                raw.n = pc;
+                for (int q = 0; q < pc; ++q) raw.mode[q] = 2;
+                kbl_finish<<<pc, 256, 0, s>>>(P.ahead, nch, raw, P.res, P.Tm, ldt, P.rho, p,
+                                              P.scal, host);
+                QCM_LAUNCH_CHECK();
+            }
+            sent = false;
             QCM_HIP(hipStreamSynchronize(s));
             scale = std::max(1.0, host[1]);
             nrm = sqrt(host[0] > 0.0 ? host[0] : 0.0);
@@ -740,50 +813,63 @@ static int band_run(const qcm_band_opts *o, BandPart &P, const double *d_gs, int
         QCM_TRY(hv_launch(P.op, sizeof(T) == 8 ? QCM_FP64 : QCM_FP32V, base + off(sj),
                           base + off(sw), 1, s));
         // (5) the band of previous basis vectors, coefficients T[k][j] = T[j][k]
-        {
-            VecList vs{};
-            Put idx{};
-            for (int k = std::max(1, j - pc); k < j; ++k) {
-                vs.off[vs.n] = off(vslot[k]);
-                idx.i[vs.n] = k - 1;
-                idx.k[vs.n] = j - 1;
-                ++vs.n;
+        VecList vs{};
+        Put idx{};
+        for (int k = std::max(1, j - pc); k < j; ++k) {
+            vs.off[vs.n] = off(vslot[k]);
+            idx.i[vs.n] = k - 1;
+            idx.k[vs.n] = j - 1;
+            ++vs.n;
+        }
+        idx.n = vs.n;
+        // (6) v_j and the look-back set, coefficients computed (in index order)
+        std::set<int> K = I;
+        K.insert(j);
+        cand[j + pc] = sw;
+        // (7) the next candidate's dot with w (row pc - 1 of P.ahead), or its
+        // norm when w is the next candidate itself
+        const int x_next = pc > 1 ? cand[j + 1] : sw;
+        ahead = true;
+        if (nch == 1 && K.size() <= kBandMaxP + 1) {
+            VecList ks{};
+            Put kput{};
+            for (int k : K) {
+                ks.off[ks.n] = off(vslot[k]);
+                kput.mode[ks.n] = k == j ? 3 : 0;
+                kput.i[ks.n] = k - 1;
+                kput.k[ks.n] = j - 1;
+                ++ks.n;
             }
-            idx.n = vs.n;
+            kput.n = ks.n;
+            kbl_tail<T><<<1, 256, sizeof(T) * (size_t)dim, s>>>(base, off(sw), vs, idx, ks, kput,
+                                                               off(x_next), pc, dim, P.Tm, ldt,
+                                                               P.scal, P.ahead, P.res, host);
+            QCM_LAUNCH_CHECK();
+            sent = true;
+        } else {
             if (vs.n > 0) {
                 kbl_sub_band<T><<<g1, 256, 0, s>>>(base, off(sw), vs, idx, dim, P.Tm, ldt);
                 QCM_LAUNCH_CHECK();
             }
-        }
-        // (6) v_j and the look-back set, coefficients computed (in index order)
-        std::set<int> K = I;
-        K.insert(j);
-        for (int k : K) {
             VecList one{};
             one.n = 1;
             one.off[0] = off(sw);
-            Put put{};
-            put.n = 1;
-            put.mode[0] = k == j ? 3 : 0;
-            put.i[0] = k - 1;
-            put.k[0] = j - 1;
-            kbl_dots<T><<<dim3(nch, 1), 256, 0, s>>>(base, off(vslot[k]), one, dim, nch, P.partial);
-            kbl_finish<<<1, 256, 0, s>>>(P.partial, nch, put, P.res, P.Tm, ldt, P.rho, p, P.scal);
-            kbl_axpys<T><<<dim3(nch, 1), 256, 0, s>>>(base, off(vslot[k]), one, dim, P.res);
-            QCM_LAUNCH_CHECK();
-        }
-        cand[j + pc] = sw;
-        // the next candidate's dot with w (row pc - 1), or its norm when w is
-        // the next candidate itself
-        {
-            VecList one{};
-            one.n = 1;
-            one.off[0] = off(sw);
-            const int x_next = pc > 1 ? cand[j + 1] : sw;
+            for (int k : K) {
+                Put put{};
+                put.n = 1;
+                put.mode[0] = k == j ? 3 : 0;
+                put.i[0] = k - 1;
+                put.k[0] = j - 1;
+                kbl_dots<T><<<dim3(nch, 1), 256, 0, s>>>(base, off(vslot[k]), one, dim, nch,
+                                                         P.partial);
+                kbl_finish<<<1, 256, 0, s>>>(P.partial, nch, put, P.res, P.Tm, ldt, P.rho, p,
+                                             P.scal, nullptr);
+                kbl_axpys<T><<<dim3(nch, 1), 256, 0, s>>>(base, off(vslot[k]), one, dim, P.res);
+                QCM_LAUNCH_CHECK();
+            }
             kbl_dots<T><<<dim3(nch, 1), 256, 0, s>>>(base, off(x_next), one, dim, nch,
                                                      P.ahead + (size_t)(pc - 1) * nch);
             QCM_LAUNCH_CHECK();
-            ahead = true;
         }
         // basis vectors older than the band and outside the look-back set are done
         for (auto it = vslot.begin(); it != vslot.end();) {
