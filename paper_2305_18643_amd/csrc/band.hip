@@ -697,13 +697,22 @@ static int band_run(const qcm_band_opts *o, BandPart &P, const double *d_gs, int
     // convergence the part ends at R = j_t, exactly as if it had stopped
     // there: later steps only add rows and columns to T and rho, so their
     // leading j_t block is final once step j_t is done.
-    SideLease side;   // the stopping tests run beside the recurrence
+    SideLease side;   // for the tests' stream, and the norms' pinned memory
     int pend_j = 0;   // basis size of the test in flight (0: none)
     int stop_at = 0;  // basis size a finished test stopped the part at
     bool near = false;
     double prev_d = 0.0;  // the change of the lowest eigenvalue at the last test
     QCM_TRY(side.lease());
     double *const host = (double *)side.pinned + 8;   // past the tests' word
+    // the last step's sums may still be on their way to the pinned memory, which
+    // another call may lease next
+    struct Drain {
+        hipStream_t s;
+        const bool &sent;
+        ~Drain() {
+            if (sent) (void)hipStreamSynchronize(s);
+        }
+    } drain{s, sent};
     // take the result of the test in flight, waiting for it or only if done
     auto settle = [&](bool wait) -> int {
         if (!pend_j) return QCM_OK;
