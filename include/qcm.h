@@ -137,11 +137,12 @@ int qcm_hv(const qcm_model *m, const qcm_basis *b, int32_t prec, const void *d_v
  * stream capture: the model is copied from host memory on every call, and on
  * sectors with long rows the set-up waits for the stream once.  The hopping
  * tables go to a fixed device-resident array of
- * 32 MiB per GPU that the library holds until the process ends (the first
+ * 32.75 MiB per GPU that the library holds until the process ends (the first
  * call on a device looks up its address there); the call allocates nothing.
- * Sectors whose tables need more (qcm_hv's size query above 32 MiB; the
- * 16-orbital (8, 8) sector needs about 18 MB) are rejected with
- * QCM_EWORKSPACE before anything is enqueued.
+ * Sectors whose tables need more than 32 MiB, counted with unrounded packed
+ * hops for both spins and, for long rows, two lists of the down hops (the
+ * 16-orbital (8, 8) sector: about 18 MB), are rejected with QCM_EWORKSPACE
+ * before anything is enqueued.
  *   m, b, prec, d_v, d_w, stream: as in qcm_hv.
  * Every call on one GPU rewrites that GPU's array: calls that overlap on one
  * GPU (other streams, other host threads) race and give undefined results;

@@ -442,8 +442,28 @@ namespace qcm {
 // copy per GPU the library runs on, held until the process ends.  Host code
 // never passes the array's name to a kernel or a copy: it uses the address
 // hipGetSymbolAddress returns for the current device.
+// A sector is taken when its tables, as limit_bytes counts them, fit 32 MiB; the
+// array also holds what the packed up list's width rounded up to four may add
+// (three entries for each of fewer than 65,536 strings).
 constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+constexpr size_t kPackedSlack = (size_t)3 * sizeof(uint32_t) * 65536;
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kPackedSlack];
+
+// The size by which qcm_hv_noalloc takes or refuses a sector whose tables need
+// `need` bytes: with the packed up list unrounded, a packed list for the down
+// strings too, and for the two-pass product a second list of the down hops.
+// This layout was the first one; the limit keeps to it, so that which sectors
+// are taken does not change with the layout.
+static size_t limit_bytes(const qcm_model *m, const qcm_basis *b, size_t need) {
+    auto take = [](size_t n) { return (n + 255) / 256 * 256; };
+    const int nb = count_bonds(m), W = nb < 1 ? 1 : nb;
+    const size_t du = (size_t)b->d_up, dd = (size_t)b->d_dn;
+    if (du < 65536) need -= take(4 * (size_t)pk_width(W) * du) - take(4 * (size_t)W * du);
+    if (dd < 65536) need += take(4 * (size_t)W * dd);
+    if (split_applies(m, b->n_up, b->d_up, b->d_dn))
+        need += take(4 * dd) + take(4 * (size_t)W * dd) + take(8 * (size_t)W * dd) + take(8 * dd);
+    return need;
+}
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -479,11 +499,12 @@ extern "C" int qcm_hv_noalloc(const qcm_model *m, const qcm_basis *b, int32_t pr
         return fail(QCM_EARG, "qcm_hv_noalloc: bad prec %d", prec);
     size_t need = 0;
     QCM_TRY(hv_setup_bytes(m, b, &need));
-    if (need > kStaticScratchBytes)
+    const size_t counted = limit_bytes(m, b, need);
+    if (counted > kStaticScratchBytes || need > sizeof scratch)
         return fail(QCM_EWORKSPACE,
                     "qcm_hv_noalloc: the sector's tables need %zu bytes, more than the %zu-byte "
                     "static scratch (use qcm_hv with a workspace)",
-                    need, kStaticScratchBytes);
+                    counted, kStaticScratchBytes);
     if (!d_v || !d_w) return fail(QCM_EARG, "qcm_hv_noalloc: NULL vector");
     size_t vb = (prec == QCM_FP64 ? 8 : 4) * (size_t)b->dim;
     const char *pv = (const char *)d_v, *pw = (const char *)d_w;
