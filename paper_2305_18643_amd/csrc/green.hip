@@ -5,7 +5,8 @@
 // For every pair (i <= j) of the requested orbitals two chains are run:
 // electron, from (c_i + c_j)+ |Omega> in sector (N_up + 1, N_dn), and hole,
 // from (c_i + c_j) |Omega> in (N_up - 1, N_dn).  All chains of one part live
-// in the same sector, so they run together through the multi-chain engine.
+// in the same sector, so they run together: in one launch where the sector fits
+// LDS, else step by step through the multi-chain engine.
 // Start vectors are built by a gather over the target sector: only the up
 // string changes, the sign is (-1)^(up electrons on orbitals below the
 // operator's orbital), and the down label is untouched.

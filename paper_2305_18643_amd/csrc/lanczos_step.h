@@ -18,6 +18,10 @@
 //           unit v, vp orthogonal to each other, up to terms of order c^2 eps);
 //   pass 3  v_{n+1} = (x - c1 v - c2 vp) / beta_n, rounded once to the storage
 //           type (optionally also psi += s_n v_n for the ground-state replay).
+// After the fused product one launch finishes a step: ks_finish_fused, which also
+// takes the direct norm of pass 2 for short vectors where the dots cancel (longer
+// ones: ks_norm and ks_finish).  The continued-fraction chains of a sector that
+// fits LDS run all their steps in one launch (ks_chain), with the same sums.
 // After the two-pass product the two finishes are ks_dots_stage and
 // ks_finish_dots, and pass 3 may be deferred into the next step's in-row
 // pass, which forms v_{n+1} element by element with the same operations when
