@@ -434,9 +434,8 @@ static void rotate(Engine &e) {
 }
 
 template <typename T>
-static int launch_round(qcm_engine *E, int ng, int n1, int na, int nc, const size_t (&lds)[2], bool big,
-                        bool norms,
-                        const TabLayout &tl,
+static int launch_round(qcm_engine *E, int ng, const int (&n1)[4], int na, int nc, const size_t (&lds)[3],
+                        bool big, bool norms, const TabLayout &tl,
                         const int64_t *hvb, const int64_t *chb, const int64_t *cnb,
                         const int64_t *acb) {
     hipStream_t s = E->s;
@@ -449,18 +448,13 @@ static int launch_round(qcm_engine *E, int ng, int n1, int na, int nc, const siz
     const BCtl *C = (const BCtl *)(E->d_tab + tl.ctl);
     if (na > 0 && acb[na] > 0) ks_accum<T, TabSrc><<<(unsigned)acb[na], 256, 0, s>>>(ac);
     if (ng > 0) {
-        const unsigned nh = (unsigned)hvb[ng], nk = (unsigned)chb[ng], nn = (unsigned)cnb[ng];
-        // groups of blocks with several rows, then (from group n1) of single rows
-        const TabSrc h0{G, hv.begin, n1}, h1{G + n1, hv.begin + n1, ng - n1, hvb[n1]};
-        const unsigned w0 = (unsigned)hvb[n1], w1 = nh - w0;
-        if (w0 && big)
-            ks_hv<T, TabSrc, false, true><<<w0, kHvThreads, lds[0], s>>>(h0);
-        else if (w0)
-            ks_hv<T, TabSrc, false, false><<<w0, kHvThreads, lds[0], s>>>(h0);
-        if (w1 && big)
-            ks_hv<T, TabSrc, true, true><<<w1, kHvThreads, lds[1], s>>>(h1);
-        else if (w1)
-            ks_hv<T, TabSrc, true, false><<<w1, kHvThreads, lds[1], s>>>(h1);
+        const unsigned nk = (unsigned)chb[ng], nn = (unsigned)cnb[ng];
+        // the groups of each form of the product
+        for (int k = 0; k < 3; ++k) {
+            const int64_t b0 = hvb[n1[k]], n = hvb[n1[k + 1]] - b0;
+            const TabSrc src{G + n1[k], hv.begin + n1[k], n1[k + 1] - n1[k], b0};
+            if (n > 0) hv_form_launch<T>(src, k, big, (unsigned)n, kHvThreads, lds[k], s);
+        }
         // alpha and beta from the product's dots; the direct norm pass only
         // for chains whose beta the dots cannot resolve
         ks_finish_fused<T, TabSrc><<<nn, 256, 0, s>>>(cn);
@@ -507,19 +501,20 @@ static int run_round(qcm_engine *E) {
     BCtl *C = (BCtl *)(E->h_tab + tl.ctl);
     const int lim = gs_limit(o);
     int ng = 0, na = 0, nc = 0;
-    size_t lds[2] = {0, 0};
+    size_t lds[3] = {0, 0, 0};
     bool big = false;   // a vector of 2 GB or more in the round
     bool norms = false; // a vector too long for the finishing kernel's norm
     hvb[0] = chb[0] = cnb[0] = acb[0] = 0;
-    // the round's groups: those whose product blocks hold several rows first
+    // the round's groups, by the form of their product
     struct Item {
         const Job *j;
         const Part *p;
         bool replay;
     };
-    std::vector<Item> items[2];
+    std::vector<Item> items[3];
+    int n1[4] = {0, 0, 0, 0};
     auto add_group = [&](const Job &j, const Part &p, bool replay) {
-        items[hv_one(p.up.d, p.e.rows) ? 1 : 0].push_back({&j, &p, replay});
+        items[hv_form(p.up.d, p.e.rows)].push_back({&j, &p, replay});
     };
     for (Job *jp : E->active) {
         Job &j = *jp;
@@ -562,7 +557,7 @@ static int run_round(qcm_engine *E) {
             }
         }
     }
-    for (int k = 0; k < 2; ++k)
+    for (int k = 0; k < 3; ++k) {
         for (const Item &it : items[k]) {
             const Job &j = *it.j;
             const Engine &e = it.p->e;
@@ -580,7 +575,8 @@ static int run_round(qcm_engine *E) {
             cnb[ng + 1] = cnb[ng] + e.nvec;
             ++ng;
         }
-    const int n1 = (int)items[0].size();
+        n1[k + 1] = ng;
+    }
     QCM_HIP(hipMemcpyAsync(E->d_tab, E->h_tab, tl.bytes, hipMemcpyHostToDevice, E->s));
     if (o.prec == QCM_FP64)
         QCM_TRY(launch_round<double>(E, ng, n1, na, nc, lds, big, norms, tl, hvb, chb, cnb, acb));

@@ -149,6 +149,20 @@ inline int32_t side_rows(int64_t d_up, int32_t rows, int prec) {
     return kSide * row <= 64 * 1024 ? kSide : 1;
 }
 
+// How a product workgroup deals out its elements: tiles of 64 lanes along the
+// rows, of a block of several rows or of one row per block, or, for rows too
+// short for that, pairs of elements (one column of two rows) one after another.
+// The line between the two for blocks of several rows: along rows of 45 the
+// tiles leave more than half their lanes idle and the pairs are 1.02 to 1.4
+// times as fast (10 orbitals (2,5), FP64 all-to-all hopping to FP32 chain); at
+// 55 they are 0.88 to 1.2 times as fast, since each lane then loads its own
+// down-hop lists.
+enum { kHvRows = 0, kHvOne = 1, kHvShort = 2 };
+constexpr int kShortRow = 48;
+inline int hv_form(int64_t d_up, int32_t rows) {
+    return hv_one(d_up, rows) ? kHvOne : d_up <= kShortRow ? kHvShort : kHvRows;
+}
+
 // LDS of a product workgroup: lookup tables, the rows (interleaved in sets of
 // rg, or kSide for blocks of several rows, each set with a zero slot), and for
 // blocks of several rows the products awaiting the dots.
@@ -254,8 +268,8 @@ typedef double f64x4_t __attribute__((ext_vector_type(4), aligned(8)));
 // <w, w>, <v, v> (<vp, w>, <vp, v>) per block of q.rows rows, summed as 256
 // threads taking the block's elements in turn, so that they do not depend on
 // how the tiles are dealt out.
-// ONE: sectors of one row per block, q.rg blocks per workgroup (their products
-// are read back for the dots); otherwise one block of several rows per
+// FORM kHvOne: sectors of one row per block, q.rg blocks per workgroup (their
+// products are read back for the dots); otherwise one block of several rows per
 // workgroup, in sets of kSide (products kept in LDS for the dots).
 constexpr int kHvThreads = 512;
 
@@ -265,19 +279,22 @@ constexpr int kHvThreads = 512;
 // 11.7 us, 10 chains of 8 orbitals 11.4 -> 9.6 us); a batched round mixes
 // short and long rows and is faster with one column and as many waves as fit
 // (24 solves of 6 to 12 orbitals: 101 ms against 115).
-template <typename T, class S, bool ONE>
+template <typename T, class S, int FORM>
 constexpr int hv_waves() {
-    return ONE ? (sizeof(T) == 8 ? 4 : 5) : (std::is_same<S, OneSrc>::value ? 4 : 8);
+    return FORM == kHvOne     ? (sizeof(T) == 8 ? 4 : 5)
+           : FORM == kHvShort ? 6
+                              : (std::is_same<S, OneSrc>::value ? 4 : 8);
 }
 
-template <typename T, class Src, bool ONE, bool BIG>
-__global__ void __launch_bounds__(kHvThreads, (hv_waves<T, Src, ONE>())) ks_hv(Src src) {
+template <typename T, class Src, int FORM, bool BIG>
+__global__ void __launch_bounds__(kHvThreads, (hv_waves<T, Src, FORM>())) ks_hv(Src src) {
+    constexpr bool ONE = FORM == kHvOne;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     int64_t local;
     const BGroup &q = src.at(blockIdx.x, &local);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    constexpr int NT = kHvThreads, NW = NT / 64;
+    const int NT = FORM == kHvShort ? (int)blockDim.x : kHvThreads, NW = NT / 64;
     const int du = (int)q.d_up;
     const int64_t d_up = q.d_up, d_dn = q.d_dn;
     int64_t vec, wg;
@@ -325,21 +342,13 @@ __global__ void __launch_bounds__(kHvThreads, (hv_waves<T, Src, ONE>())) ks_hv(S
     const int W = q.wd;
     const double uu = q.u_uniform;
     const int tun = q.t_uniform, upc = __builtin_amdgcn_readfirstlane(uu >= 0.0);
-    // the products of 64 CW up strings (tile tt; CW adjacent columns per lane)
-    // in RG rows, held interleaved at rs; out(r, iu, w) takes element iu of row r
-    auto tile_rows = [&](auto rg_, auto cw_, int tt, const auto &ri, const T *rs, auto &&out) {
+    // the diagonal and the in-row hops of CW adjacent columns (from ic) of RG rows,
+    // held interleaved at rs: nh hops, or as many more as fill a group of four
+    auto in_row = [&](auto rg_, auto cw_, int ic, int nh, const T *rs, const auto &bd, const auto &ed,
+                      auto &acc) {
         constexpr int RG = decltype(rg_)::value, CW = decltype(cw_)::value;
         typedef RowSet<T, RG> Set;
-        typedef Cols<T, CW> C;
         const Set *row = reinterpret_cast<const Set *>(rs);
-        // a lane past the row's end redoes the row's last columns
-        const int iu = tt * (64 * CW) + lane * CW;
-        const bool in = iu < du;
-        const int ic = min(iu, du - CW);
-        const int vo = ic * (int)sizeof(T);
-        // the largest hop count of the tile's strings
-        int nh = nhu[tt * (64 * CW)] >> 16;
-        if constexpr (CW == 2) nh = max(nh, nhu[min(tt * 128 + 64, du - 1)] >> 16);
         const int du4 = afresh(du * 4);
         constexpr int kAhead = 8;   // entries loaded together
         Cols<uint32_t, CW> pe[kAhead];
@@ -354,14 +363,13 @@ __global__ void __launch_bounds__(kHvThreads, (hv_waves<T, Src, ONE>())) ks_hv(S
         entries(0, nh);
         const auto bu = ld_cols<Cols<uint32_t, CW>>(su + (uint32_t)ic);
         const auto eui = ld_cols<Cols<double, CW>>(eu + (uint32_t)ic);
-        double acc[RG][CW];
 #pragma unroll
         for (int c = 0; c < CW; ++c) {
             const Set own = row[ic + c];
 #pragma unroll
             for (int r = 0; r < RG; ++r) {
-                const uint32_t dbl = bu.x[c] & ri.bd[r];
-                double diag = eui.x[c] + ri.ed[r];
+                const uint32_t dbl = bu.x[c] & bd[r];
+                double diag = eui.x[c] + ed[r];
                 if (afresh(upc)) {
                     diag += uu * (double)__popc(dbl);
                 } else {
@@ -408,6 +416,22 @@ __global__ void __launch_bounds__(kHvThreads, (hv_waves<T, Src, ONE>())) ks_hv(S
             hops(std::true_type{});
         else
             hops(std::false_type{});
+    };
+    // the products of 64 CW up strings (tile tt; CW adjacent columns per lane)
+    // in RG rows, held interleaved at rs; out(r, iu, w) takes element iu of row r
+    auto tile_rows = [&](auto rg_, auto cw_, int tt, const auto &ri, const T *rs, auto &&out) {
+        constexpr int RG = decltype(rg_)::value, CW = decltype(cw_)::value;
+        typedef Cols<T, CW> C;
+        // a lane past the row's end redoes the row's last columns
+        const int iu = tt * (64 * CW) + lane * CW;
+        const bool in = iu < du;
+        const int ic = min(iu, du - CW);
+        const int vo = ic * (int)sizeof(T);
+        // the largest hop count of the tile's strings
+        int nh = nhu[tt * (64 * CW)] >> 16;
+        if constexpr (CW == 2) nh = max(nh, nhu[min(tt * 128 + 64, du - 1)] >> 16);
+        double acc[RG][CW];
+        in_row(rg_, cw_, ic, nh, rs, ri.bd, ri.ed, acc);
         // row-mixing neighbours: whole groups of four hops, the first kGr of
         // them and the last one to three hops loaded together for all rows
         constexpr int kGr = 2;
@@ -481,6 +505,83 @@ __global__ void __launch_bounds__(kHvThreads, (hv_waves<T, Src, ONE>())) ks_hv(S
             }
         }
     };
+    // short rows: a lane takes one column of a set of RG rows; pair p is column
+    // p mod du of set p / du (row_of).  Its rows' lists are its own, read four
+    // hops at a time.  Tiles along the row left 64 - du lanes (or 128 - du of
+    // two columns) idle: 16 orbitals (1,8), 29 vectors in FP64 230 -> 81 us;
+    // (0,8), ten vectors 117 -> 9.5 us.
+    auto short_rows = [&](auto rg_, int row0, int nr, int SR, auto &&row_of, auto &&out) {
+        constexpr int RG = decltype(rg_)::value;
+        int nh = 0;
+        for (int k = 0; k < du; k += 64) nh = max(nh, nhu[k] >> 16);
+        const int np = (nr + RG - 1) / RG * du;
+        for (int p = tid; p < np; p += NT) {
+            const int g = row_of(p), c = p - g * du;
+            int idn[RG], nhr[RG];
+            uint32_t bd[RG];
+            double ed[RG], acc[RG][1];
+            gptr<const int32_t> cl[RG];
+            gptr<const double> cf[RG];
+#pragma unroll
+            for (int r = 0; r < RG; ++r) {
+                const int i = row0 + min(g * RG + r, nr - 1);
+                idn[r] = i;
+                nhr[r] = gp(q.nhd)[i];
+                bd[r] = gp(q.sd)[i];
+                ed[r] = gp(q.ed)[i];
+                cl[r] = gp(q.cold) + (int64_t)i * W;
+                cf[r] = gp(q.cfd) + (int64_t)i * W;
+            }
+            in_row(rg_, std::integral_constant<int, 1>{}, c, nh, tile + g * SR, bd, ed, acc);
+            auto neighbour = [&](int j) -> T {
+                if constexpr (BIG)
+                    return *(gptr<const T>)((gptr<const char>)v + (uint64_t)(uint32_t)j * rstep +
+                                            (uint32_t)c * (uint32_t)sizeof(T));
+                else
+                    return buf_load<T>(rv, (j * du + c) * (int)sizeof(T), 0);
+            };
+            // whole groups of four hops, then the last one to three together
+#pragma unroll
+            for (int r = 0; r < RG; ++r) {
+                const int n = nhr[r], nt = n & ~3;
+                for (int t = 0; t < nt; t += 4) {
+                    const i32x4_t cc = *(gptr<const i32x4_t>)(cl[r] + t);
+                    const f64x4_t co = *(gptr<const f64x4_t>)(cf[r] + t);
+                    T x[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) x[u] = neighbour(cc[u]);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) acc[r][0] = fma(co[u], (double)x[u], acc[r][0]);
+                }
+                T x[3];
+                double co[3];
+                if (n & 2)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        co[u] = cf[r][nt + u];
+                        x[u] = neighbour(cl[r][nt + u]);
+                    }
+                if (n & 1) {
+                    co[2] = cf[r][n - 1];
+                    x[2] = neighbour(cl[r][n - 1]);
+                }
+                if (n & 2) {
+                    acc[r][0] = fma(co[0], (double)x[0], acc[r][0]);
+                    acc[r][0] = fma(co[1], (double)x[1], acc[r][0]);
+                }
+                if (n & 1) acc[r][0] = fma(co[2], (double)x[2], acc[r][0]);
+            }
+#pragma unroll
+            for (int r = 0; r < RG; ++r)
+                if (g * RG + r < nr) {
+                    const uint64_t at = (uint64_t)(uint32_t)idn[r] * rstep + (uint32_t)c * (uint32_t)sizeof(T);
+                    if (sub) acc[r][0] = fma(-b, (double)*(gptr<const T>)(vpb + at), acc[r][0]);
+                    const T wt = (T)acc[r][0];
+                    *(gptr<T>)(wb + at) = wt;
+                    out(g * RG + r, c, wt);
+                }
+        }
+    };
     // what the tiles need of the nr (<= RG) rows from idn0
     auto row_info = [&](auto rg_, int idn0, int nr) {
         constexpr int RG = decltype(rg_)::value;
@@ -514,19 +615,19 @@ __global__ void __launch_bounds__(kHvThreads, (hv_waves<T, Src, ONE>())) ks_hv(S
         const int nset = (nr + RG - 1) / RG;
         const int SR = RG * (du + 1);   // elements of a set
         T *wt_s = tile + (rows + RG - 1) / RG * SR;
-        for (int r = 0; r < nset * RG; ++r) {
-            T *t = tile + (r / RG) * SR + r % RG;
-            const auto vr = v + (row0 + min(r, nr - 1)) * d_up;
-            if (ONE || du >= NT) {
+        const bool by_row = FORM != kHvShort && (ONE || du >= NT);
+        if (by_row)
+            for (int r = 0; r < nset * RG; ++r) {
+                T *t = tile + (r / RG) * SR + r % RG;
+                const auto vr = v + (row0 + min(r, nr - 1)) * d_up;
                 for (int k = tid; k < du; k += NT) t[k * RG] = vr[k];
             }
-            if (tid == 0) t[du * RG] = T(0);
-        }
+        for (int r = tid; r < nset * RG; r += NT) tile[(r / RG) * SR + du * RG + r % RG] = T(0);
         // e / du for e < 2^16: M = ceil(2^32 / du), and du = 1 apart
         const uint32_t M = 0xffffffffu / (uint32_t)du + 1u;
         auto row_of = [&](int e) { return du == 1 ? e : (int)__umulhi((uint32_t)e, M); };
         const int nel = nr * du;
-        if (!(ONE || du >= NT))
+        if (!by_row)
             for (int e = tid; e < nel; e += NT) {
                 const int r = row_of(e), iu = e - r * du;
                 tile[(r / RG) * SR + iu * RG + (r % RG)] = (v + row0 * d_up)[e];
@@ -537,6 +638,10 @@ __global__ void __launch_bounds__(kHvThreads, (hv_waves<T, Src, ONE>())) ks_hv(S
             const int nt = (du + 127) >> 7;
             for (int tt = wave; tt < nt; tt += NW)
                 tile_rows(rg_, std::integral_constant<int, 2>{}, tt, ri, tile, [](int, int, auto) {});
+        } else if constexpr (FORM == kHvShort) {
+            short_rows(rg_, (int)row0, nr, SR, row_of, [&](int r, int iu, T wt) {
+                if (dots) wt_s[r * du + iu] = wt;
+            });
         } else {
             auto tiles = [&](auto cw_) {
                 constexpr int CW = decltype(cw_)::value;
@@ -619,18 +724,42 @@ __global__ void __launch_bounds__(kHvThreads, (hv_waves<T, Src, ONE>())) ks_hv(S
 // Vectors whose byte offsets leave the 31 bits of a buffer load's offset.
 inline bool hv_big(int64_t dim, size_t s) { return dim * (int64_t)s >= ((int64_t)1 << 31); }
 
-// The fused product of one group.
+// Threads of a product workgroup.  One of short rows takes no more waves than its
+// pairs of elements fill, or four where they would fill five to seven, whose last
+// waves run half empty (8 orbitals (1,4), 10,714 vectors: 79 us with five, 62);
+// but at least the 256 of the dots, if there are any.  A tiny sector in many
+// vectors is one workgroup per vector and bound by the waves it starts: 4
+// orbitals (2,2), 166,666 vectors, 1082 us with eight waves each, 170 with one.
+// Two waves where sums of U are staged (256 entries per eight orbitals).
+inline unsigned hv_threads(int64_t d_up, int32_t rows, bool lut, bool dots) {
+    if (hv_form(d_up, rows) != kHvShort) return kHvThreads;
+    const int64_t n = ((rows + kSide - 1) / kSide * d_up + 63) / 64 * 64;
+    if (n >= kHvThreads) return kHvThreads;
+    return (unsigned)std::max<int64_t>(std::min<int64_t>(n, 256), dots ? 256 : lut ? 128 : 64);
+}
+
+// The fused product of one source of work, all of one form.
+template <typename T, class Src>
+inline void hv_form_launch(const Src &src, int form, bool big, unsigned wgs, unsigned threads,
+                           size_t lds, hipStream_t s) {
+    if (form == kHvOne && !big)
+        ks_hv<T, Src, kHvOne, false><<<wgs, threads, lds, s>>>(src);
+    else if (form == kHvOne)
+        ks_hv<T, Src, kHvOne, true><<<wgs, threads, lds, s>>>(src);
+    else if (form == kHvShort && !big)
+        ks_hv<T, Src, kHvShort, false><<<wgs, threads, lds, s>>>(src);
+    else if (form == kHvShort)
+        ks_hv<T, Src, kHvShort, true><<<wgs, threads, lds, s>>>(src);
+    else if (!big)
+        ks_hv<T, Src, kHvRows, false><<<wgs, threads, lds, s>>>(src);
+    else
+        ks_hv<T, Src, kHvRows, true><<<wgs, threads, lds, s>>>(src);
+}
 template <typename T>
 inline void hv_step_launch(const OneSrc &src, unsigned wgs, size_t lds, hipStream_t s) {
-    const bool big = hv_big(src.g.dim, sizeof(T)), one = hv_one(src.g.d_up, src.g.rows);
-    if (one && !big)
-        ks_hv<T, OneSrc, true, false><<<wgs, kHvThreads, lds, s>>>(src);
-    else if (one)
-        ks_hv<T, OneSrc, true, true><<<wgs, kHvThreads, lds, s>>>(src);
-    else if (!big)
-        ks_hv<T, OneSrc, false, false><<<wgs, kHvThreads, lds, s>>>(src);
-    else
-        ks_hv<T, OneSrc, false, true><<<wgs, kHvThreads, lds, s>>>(src);
+    const BGroup &g = src.g;
+    hv_form_launch<T>(src, hv_form(g.d_up, g.rows), hv_big(g.dim, sizeof(T)), wgs,
+                      hv_threads(g.d_up, g.rows, g.u_uniform < 0.0, g.pa != nullptr), lds, s);
 }
 
 // chunk of a chunked pass
