@@ -307,6 +307,8 @@ int engine_init(Engine &e, const HvOp &op, int prec, int nvec, int maxs, double 
     e.cs.done = ic + nvec;
     e.cs.renorm = ic + 2 * nvec;
     e.cs.dlog = cv.take<int32_t>(maxs);
+    e.cs.prog = nullptr;
+    e.cs.progn = 1;
     e.ivp = 0;
     e.iv = 1;
     e.iw = 2;
@@ -666,7 +668,38 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
     // are not read).  Test t has status record t mod kTests; launch t takes
     // its theta_0 and test t - 1's estimate.
     SideLease side;
-    if (o->fixed_steps <= 0) QCM_TRY(side.lease());
+    QCM_TRY(side.lease());
+    // With fixed steps there are no tests, but a chain that stops early (its
+    // later steps are zero vectors, which its length leaves out) should not be
+    // carried on for long: the finishing kernels leave their progress in pinned
+    // memory, and a step is enqueued once the second one before it is known to
+    // have gone on.  One step is then always queued behind the running one, so
+    // the host's look costs nothing (a stream synchronisation each step costs 15
+    // us; one every 64 steps ran up to 63 steps past the end).  The store takes 1
+    // to 2 us, so steps of less than about 0.3 ms make it every fourth time only.
+    volatile int32_t *const prog = (int32_t *)side.pinned;
+    struct Drain {   // the steps in flight write to the leased memory
+        hipStream_t s;
+        bool on;
+        ~Drain() {
+            if (on) (void)hipStreamSynchronize(s);
+        }
+    } drain{s, o->fixed_steps > 0};
+    if (o->fixed_steps > 0) {
+        *prog = 0;
+        e.cs.prog = (int32_t *)side.pinned;
+        e.cs.progn = dim < (1 << 24) ? 4 : 1;
+    }
+    auto progress = [&](int steps) -> int {   // wait for that many steps
+        for (unsigned k = 1; *prog >= 0 && *prog < steps; ++k) {
+            if (k % 4096) continue;
+            const hipError_t q = hipStreamQuery(s);
+            if (q == hipErrorNotReady) continue;
+            QCM_HIP(q);
+            if (*prog >= 0 && *prog < steps) return fail(QCM_EHIP, "%s: a step did not finish", fn);
+        }
+        return QCM_OK;
+    };
     int ntest = 0, seen = 0, nlaunch = 0, tm[kTests] = {0};
     bool stop = false;
     auto launch_test = [&](int Mt) -> int {
@@ -711,21 +744,20 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
         if (nkeep) aim(n);
         QCM_TRY(engine_step(e, n, s));
         const bool last = n + 1 == limit, check = (n + 1) % every == 0 || last;
-        if (!check) continue;
         if (o->fixed_steps > 0) {
-            // a chain that stops early goes on with zero vectors, which its
-            // length leaves out; now and then, see whether it has
-            if (last || (n + 1) % 64 == 0) {
-                int32_t ds[2] = {0, 0};
-                QCM_HIP(hipMemcpyAsync(&ds[0], e.cs.done, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-                QCM_HIP(hipMemcpyAsync(&ds[1], e.cs.len, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+            if (last)
                 QCM_HIP(hipStreamSynchronize(s));
-                M = ds[0] ? ds[1] : n + 1;
-                if (ds[0]) brk = conv = 1;
-                stop = ds[0] != 0;
+            else
+                QCM_TRY(progress((n - 1) / e.cs.progn * e.cs.progn));
+            M = n + 1;
+            if (*prog < 0) {
+                M = -1 - *prog;
+                brk = conv = 1;
+                stop = true;
             }
             continue;
         }
+        if (!check) continue;
         QCM_TRY(launch_test(n + 1));
         if (last) {
             QCM_TRY(launch_test(0));
@@ -734,6 +766,7 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
             QCM_TRY(verdicts(ntest - 3));
         }
     }
+    e.cs.prog = nullptr;
     // the record of the test that ended the recurrence (its theta_0 is the hint)
     GsStatus *const fin = status + (seen > 0 ? (seen - 1) % kTests : 0);
     if (nlaunch > 0) QCM_HIP(hipStreamWaitEvent(s, side.done[(nlaunch - 1) % kTests], 0));

@@ -1,0 +1,78 @@
+"""Ground-state calls whose recurrence ends before its last allowed step: a
+fixed number of steps from a vector in a small invariant subspace."""
+import time
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def q():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2305_18643_amd as q
+    q.load_library()
+    return q
+
+
+@pytest.mark.parametrize("L,nup,ndn", [(6, 3, 3), (14, 7, 7), (16, 8, 1)])   # fused, long rows, two-pass
+@pytest.mark.parametrize("steps", [1, 2, 3, 200])
+def test_fixed_steps_from_an_eigenvector(q, L, nup, ndn, steps):
+    """H without hopping: any basis state is an eigenvector, so the chain stops
+    after its first step whatever the number asked for."""
+    import torch
+    m = synth.chain(L, t=0.0, U=4.0, mu=1.0)
+    b = q.sector_basis(L, nup, ndn)
+    v0 = torch.zeros(b.dim, dtype=torch.float64, device="cuda")
+    v0[b.dim // 3] = 1.0
+    r = q.lanczos_gs(m, b, fixed_steps=steps, v0=v0)
+    e = oracle.hv_rows(m.t, m.U, nup, ndn, v0.cpu().numpy(), np.array([b.dim // 3]))[0]
+    assert r["n_iter"] == 1 and r["breakdown"] and r["converged"]
+    assert r["alpha"].shape == (1,) and abs(r["e0"] - e) <= 1e-12 * max(1.0, abs(e))
+    assert torch.equal(r["psi"].abs(), v0)
+
+
+@pytest.mark.parametrize("m,want", [(synth.two_site(U=4.0), None), (synth.random_model(921, 6, 1, 0), 6)],
+                         ids=["two_site", "one_electron"])
+@pytest.mark.parametrize("check_every", [1, 7])
+def test_fixed_steps_small_krylov_space(q, m, want, check_every):
+    """More steps than the sector has states: stopped at the same length as the
+    chain that may stop by itself, with the same coefficients."""
+    b = q.sector_basis(m.L, m.nup, m.ndn)
+    r = q.lanczos_gs(m, b, fixed_steps=90, check_every=check_every)
+    s = q.lanczos_gs(m, b, max_iter=90, tol=0.0)
+    assert r["breakdown"] and r["n_iter"] == s["n_iter"] <= b.dim + 1
+    if want:
+        assert abs(r["n_iter"] - want) <= 1
+    assert np.array_equal(r["alpha"], s["alpha"]) and np.array_equal(r["beta"], s["beta"])
+    assert r["e0"] == s["e0"]
+
+
+def test_time_of_a_chain_that_stops_at_once(q):
+    """64 fixed steps cost no more than a few where the chain stops at the first
+    (carried on to the end they cost five times as much as these four)."""
+    import torch
+    m = synth.chain(14, t=0.0, U=4.0, mu=1.0)
+    b = q.sector_basis(14, 7, 7)
+    v0 = torch.zeros(b.dim, dtype=torch.float64, device="cuda")
+    v0[12345] = 1.0
+    best = {}
+    for steps in (4, 64):
+        def call():
+            q.lanczos_gs(m, b, fixed_steps=steps, want_vector=False, v0=v0)
+        call()
+        ts = []
+        for _ in range(5):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            call()
+            ts.append(time.perf_counter() - t0)
+        best[steps] = min(ts)
+    print(f"stops at once: {best[4] * 1e3:.2f} ms for 4 steps, {best[64] * 1e3:.2f} ms for 64", flush=True)
+    assert best[64] <= 2.0 * best[4]
