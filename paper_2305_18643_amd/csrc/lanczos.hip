@@ -176,6 +176,24 @@ __global__ void __launch_bounds__(256) k_tridiag_test(const double *__restrict__
     }
 }
 
+// A whole test in one workgroup (theta_0 of *prev as the hint), for tests several
+// steps apart: its verdict does not wait for the next test's launch.
+__global__ void __launch_bounds__(256) k_tridiag_whole(const double *__restrict__ alpha,
+                                                       const double *__restrict__ beta, int M,
+                                                       double tol, double *work, double *svec,
+                                                       const GsStatus *prev, GsStatus *status,
+                                                       const int32_t *dlog, const int32_t *len,
+                                                       GsTest *host) {
+    if (threadIdx.x == 0) *status = *prev;
+    __syncthreads();
+    tridiag_status_block(alpha, beta, M, tol, work, svec, status, false);
+    if (threadIdx.x == 0) {
+        host->st = *status;
+        host->done = dlog[M - 1];
+        host->len = *len;
+    }
+}
+
 // psi_i = sum over n < M of svec[n] v_n[i] (FP64, in order of n) from kept
 // vectors, vec elements apart
 template <typename T>
@@ -662,11 +680,19 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
     e.lazy = 1;
     GsStatus hs{};
     int M = 0, conv = 0, brk = 0;
-    // The tests run on a side stream beside the steps, two of which may be
-    // enqueued past the step whose verdict is known: such a step is wasted if
-    // the verdict ends the recurrence, but changes nothing (its coefficients
-    // are not read).  Test t has status record t mod kTests; launch t takes
-    // its theta_0 and test t - 1's estimate.
+    // The tests run on a side stream beside the steps, some of which are
+    // enqueued past a test whose verdict is not known yet: such a step is wasted
+    // if the verdict ends the recurrence, but changes nothing (its coefficients
+    // are not read).  Test t has status record t mod kTests.  A test after every
+    // step (or every second of a short one): launch t takes its theta_0 and test
+    // t - 1's estimate, side by side, and two tests' steps run ahead.  Tests
+    // further apart: launch t is the whole test (40 to 150 us), and as many steps
+    // run ahead as take about that long, so that neither the steps wait for it
+    // nor many are wasted (with the estimate left to the next launch, 20 steps
+    // apart, up to 40 were: 14 orbitals (7,7) 59.8 -> 52.5 ms; 2 steps apart, 12
+    // orbitals, whole tests 4.65 ms, pairs 4.39).
+    const int ahead = dim >= (1 << 24) ? 1 : dim >= (1 << 21) ? 2 : 4;
+    const bool pairs = every == 1 || 2 * every <= ahead;
     SideLease side;
     QCM_TRY(side.lease());
     // With fixed steps there are no tests, but a chain that stops early (its
@@ -706,10 +732,15 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
         const int k = nlaunch % kTests, kp = (nlaunch + kTests - 1) % kTests;
         QCM_HIP(hipEventRecord(side.ready[k], s));
         QCM_HIP(hipStreamWaitEvent(side.s, side.ready[k], 0));
-        k_tridiag_test<<<nlaunch > 0 ? 2 : 1, 256, 0, side.s>>>(
-            e.cs.alpha, e.cs.beta, Mt, nlaunch > 0 ? tm[kp] : 0, o->tol, work,
-            work + 5 * (size_t)limit, svec, status + kp, status + k, e.cs.dlog, e.cs.len,
-            (GsTest *)side.pinned + kp);
+        if (pairs)
+            k_tridiag_test<<<nlaunch > 0 ? 2 : 1, 256, 0, side.s>>>(
+                e.cs.alpha, e.cs.beta, Mt, nlaunch > 0 ? tm[kp] : 0, o->tol, work,
+                work + 5 * (size_t)limit, svec, status + kp, status + k, e.cs.dlog, e.cs.len,
+                (GsTest *)side.pinned + kp);
+        else
+            k_tridiag_whole<<<1, 256, 0, side.s>>>(e.cs.alpha, e.cs.beta, Mt, o->tol, work, svec,
+                                                  status + kp, status + k, e.cs.dlog, e.cs.len,
+                                                  (GsTest *)side.pinned + k);
         QCM_LAUNCH_CHECK();
         QCM_HIP(hipEventRecord(side.done[k], side.s));
         tm[k] = Mt;
@@ -717,13 +748,16 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
         if (Mt > 0) ++ntest;
         return QCM_OK;
     };
-    // the verdicts of the tests up to t, in order, until one ends the recurrence
+    // the verdicts of the tests in order, until one ends the recurrence: those up
+    // to t are waited for, later ones (whole tests) taken if they are there
     auto verdicts = [&](int t) -> int {
-        for (; seen <= t && !stop; ++seen) {
-            const hipEvent_t ev = side.done[(seen + 1) % kTests];
+        for (; seen < ntest && !stop; ++seen) {
+            if (seen > t && pairs) break;
+            const hipEvent_t ev = side.done[(seen + (pairs ? 1 : 0)) % kTests];
             hipError_t q;
-            while ((q = hipEventQuery(ev)) == hipErrorNotReady) {
+            while ((q = hipEventQuery(ev)) == hipErrorNotReady && seen <= t) {
             }
+            if (q == hipErrorNotReady) break;
             QCM_HIP(q);
             const GsTest *g = (const GsTest *)side.pinned + seen % kTests;
             hs = g->st;
@@ -757,13 +791,16 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
             }
             continue;
         }
-        if (!check) continue;
-        QCM_TRY(launch_test(n + 1));
+        if (check) QCM_TRY(launch_test(n + 1));
         if (last) {
-            QCM_TRY(launch_test(0));
+            if (pairs) QCM_TRY(launch_test(0));
             QCM_TRY(verdicts(ntest - 1));
-        } else {
+        } else if (pairs) {
             QCM_TRY(verdicts(ntest - 3));
+        } else {
+            int t = seen;   // the first test less than `ahead` steps back
+            while (t < ntest && tm[t % kTests] <= n + 1 - ahead) ++t;
+            QCM_TRY(verdicts(t - 1));
         }
     }
     e.cs.prog = nullptr;

@@ -1,5 +1,6 @@
 """Ground-state calls whose recurrence ends before its last allowed step: a
-fixed number of steps from a vector in a small invariant subspace."""
+fixed number of steps from a vector in a small invariant subspace, and residual
+tests several steps apart."""
 import time
 
 import numpy as np
@@ -76,3 +77,51 @@ def test_time_of_a_chain_that_stops_at_once(q):
         best[steps] = min(ts)
     print(f"stops at once: {best[4] * 1e3:.2f} ms for 4 steps, {best[64] * 1e3:.2f} ms for 64", flush=True)
     assert best[64] <= 2.0 * best[4]
+
+
+@pytest.mark.parametrize("L,nup,ndn,ahead", [(8, 4, 4, 4), (14, 7, 7, 2)])
+@pytest.mark.parametrize("check_every", [2, 7, 20])
+def test_steps_past_the_test_that_ends_it(q, L, nup, ndn, ahead, check_every):
+    """The workspace holds the coefficients of every step that was enqueued: at
+    most a few lie past the last one that counts.  The result is that of a test
+    after every step, taken on to the next test."""
+    import torch
+    m = synth.chain(L, U=4.0, mu=2.0)
+    b = q.sector_basis(L, nup, ndn)
+    one = q.lanczos_gs(m, b, want_vector=False)
+    ws = torch.zeros((8 << 20) + 32 * b.dim, dtype=torch.uint8, device="cuda")
+    r = q.lanczos_gs(m, b, want_vector=False, check_every=check_every, ws=ws)
+    M = r["n_iter"]
+    assert r["converged"] and not r["breakdown"]
+    assert M == -(-one["n_iter"] // check_every) * check_every
+    assert np.array_equal(r["alpha"][:one["n_iter"]], one["alpha"])
+    x = ws[:ws.numel() // 8 * 8].view(torch.float64)
+    a = torch.from_numpy(r["alpha"]).cuda()
+    at = [int(i) for i in torch.nonzero(x == a[0]).ravel().cpu() if torch.equal(x[i:i + M], a)]
+    assert len(at) == 1
+    past = int((x[at[0] + M:at[0] + 600] != 0).long().cumprod(0).sum())
+    print(f"{L} orbitals, a test every {check_every} steps: {past} steps past step {M}", flush=True)
+    assert past <= ahead
+
+
+@pytest.mark.parametrize("m", [synth.chain(8, U=4.0, mu=2.0), synth.two_site(U=4.0), synth.random_model(922, 9, 4, 4)],
+                         ids=["chain8", "two_site", "rand9"])
+@pytest.mark.parametrize("kw", [dict(max_iter=5, check_every=2), dict(max_iter=600, check_every=3),
+                                dict(max_iter=33, check_every=50), dict(max_iter=40, check_every=40, tol=0.0)],
+                         ids=lambda k: "_".join(map(str, k.values())))
+def test_tests_apart_against_the_oracle(q, m, kw):
+    """Stopped by the limit, by a test, by a breakdown between two tests."""
+    b = q.sector_basis(m.L, m.nup, m.ndn)
+    r = q.lanczos_gs(m, b, **kw)
+    M = r["n_iter"]
+    T = np.diag(r["alpha"]) + np.diag(r["beta"][:M - 1], 1) + np.diag(r["beta"][:M - 1], -1)
+    th, sv = np.linalg.eigh(T)
+    scale = np.abs(th).max()
+    assert abs(r["e0"] - th[0]) <= 1e-13 * scale
+    if M > 1:
+        assert abs(r["theta1"] - th[1]) <= 1e-13 * scale
+    assert abs(r["residual_est"] - r["beta"][M - 1] * abs(sv[-1, 0])) <= 1e-12 * scale
+    assert M == kw["max_iter"] or r["breakdown"] or M % kw["check_every"] == 0
+    if r["converged"]:
+        o = oracle.lanczos_gs(m.t, m.U, m.nup, m.ndn)
+        assert abs(r["e0"] - o["e0"]) <= 1e-10 * max(1.0, abs(o["e0"]))
