@@ -325,8 +325,7 @@ int engine_init(Engine &e, const HvOp &op, int prec, int nvec, int maxs, double 
     e.cs.done = ic + nvec;
     e.cs.renorm = ic + 2 * nvec;
     e.cs.dlog = cv.take<int32_t>(maxs);
-    e.cs.prog = nullptr;
-    e.cs.progn = 1;
+    e.cs.stop = nullptr;
     e.ivp = 0;
     e.iv = 1;
     e.iw = 2;
@@ -697,13 +696,14 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
     QCM_TRY(side.lease());
     // With fixed steps there are no tests, but a chain that stops early (its
     // later steps are zero vectors, which its length leaves out) should not be
-    // carried on for long: the finishing kernels leave their progress in pinned
-    // memory, and a step is enqueued once the second one before it is known to
-    // have gone on.  One step is then always queued behind the running one, so
-    // the host's look costs nothing (a stream synchronisation each step costs 15
-    // us; one every 64 steps ran up to 63 steps past the end).  The store takes 1
-    // to 2 us, so steps of less than about 0.3 ms make it every fourth time only.
-    volatile int32_t *const prog = (int32_t *)side.pinned;
+    // carried on for long: the finishing kernels leave its length in pinned
+    // memory, where the host looks each time the steps up to the mark before the
+    // last one are done.  A step or more is then always queued behind the
+    // running one, so that the look costs nothing (a stream synchronisation each
+    // step costs 15 us; one every 64 steps ran up to 63 steps past the end).  A
+    // mark takes the stream 1 to 2 us, so short steps (under about 0.3 ms) have
+    // one every second time to start with, and every eighth later.
+    volatile int32_t *const stopped = (int32_t *)side.pinned;
     struct Drain {   // the steps in flight write to the leased memory
         hipStream_t s;
         bool on;
@@ -711,21 +711,11 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
             if (on) (void)hipStreamSynchronize(s);
         }
     } drain{s, o->fixed_steps > 0};
+    int nmark = 0;
     if (o->fixed_steps > 0) {
-        *prog = 0;
-        e.cs.prog = (int32_t *)side.pinned;
-        e.cs.progn = dim < (1 << 24) ? 4 : 1;
+        *stopped = 0;
+        e.cs.stop = (int32_t *)side.pinned;
     }
-    auto progress = [&](int steps) -> int {   // wait for that many steps
-        for (unsigned k = 1; *prog >= 0 && *prog < steps; ++k) {
-            if (k % 4096) continue;
-            const hipError_t q = hipStreamQuery(s);
-            if (q == hipErrorNotReady) continue;
-            QCM_HIP(q);
-            if (*prog >= 0 && *prog < steps) return fail(QCM_EHIP, "%s: a step did not finish", fn);
-        }
-        return QCM_OK;
-    };
     int ntest = 0, seen = 0, nlaunch = 0, tm[kTests] = {0};
     bool stop = false;
     auto launch_test = [&](int Mt) -> int {
@@ -754,9 +744,8 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
         for (; seen < ntest && !stop; ++seen) {
             if (seen > t && pairs) break;
             const hipEvent_t ev = side.done[(seen + (pairs ? 1 : 0)) % kTests];
-            hipError_t q;
-            while ((q = hipEventQuery(ev)) == hipErrorNotReady && seen <= t) {
-            }
+            // (a wait of the runtime's, so that it blocks or spins as the program chose)
+            const hipError_t q = seen <= t ? hipEventSynchronize(ev) : hipEventQuery(ev);
             if (q == hipErrorNotReady) break;
             QCM_HIP(q);
             const GsTest *g = (const GsTest *)side.pinned + seen % kTests;
@@ -779,13 +768,15 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
         QCM_TRY(engine_step(e, n, s));
         const bool last = n + 1 == limit, check = (n + 1) % every == 0 || last;
         if (o->fixed_steps > 0) {
-            if (last)
+            if (last) {
                 QCM_HIP(hipStreamSynchronize(s));
-            else
-                QCM_TRY(progress((n - 1) / e.cs.progn * e.cs.progn));
+            } else if ((n + 1) % (dim >= (1 << 24) ? 1 : n < 16 ? 2 : 8) == 0) {
+                QCM_HIP(hipEventRecord(side.done[nmark % 2], s));
+                if (nmark++ > 0) QCM_HIP(hipEventSynchronize(side.done[nmark % 2]));
+            }
             M = n + 1;
-            if (*prog < 0) {
-                M = -1 - *prog;
+            if (*stopped) {
+                M = *stopped - 1;
                 brk = conv = 1;
                 stop = true;
             }
@@ -803,7 +794,7 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
             QCM_TRY(verdicts(t - 1));
         }
     }
-    e.cs.prog = nullptr;
+    e.cs.stop = nullptr;
     // the record of the test that ended the recurrence (its theta_0 is the hint)
     GsStatus *const fin = status + (seen > 0 ? (seen - 1) % kTests : 0);
     if (nlaunch > 0) QCM_HIP(hipStreamWaitEvent(s, side.done[(nlaunch - 1) % kTests], 0));

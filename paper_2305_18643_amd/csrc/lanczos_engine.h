@@ -25,9 +25,7 @@ struct ChainState {
     int32_t *done;  // chain stopped (breakdown or empty start)
     int32_t *renorm;  // this step's beta needs the direct norm pass (see ks_finish)
     int32_t *dlog;    // [maxs] chain 0: whether it had stopped after each step
-    int32_t *prog;    // chain 0, in host memory, or NULL: the number of steps taken
-                      // (every progn steps), or -1 - len once the chain has stopped
-    int32_t progn;
+    int32_t *stop;    // chain 0, in host memory, or NULL: 1 + len once it has stopped
 };
 
 struct GsStatus {

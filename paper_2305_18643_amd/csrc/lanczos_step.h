@@ -901,9 +901,8 @@ __device__ __forceinline__ void finish_beta(const ChainState &cs, int c, int n, 
     cs.inv[c] = cs.done[c] ? 0.0 : 1.0 / b;
     if (c == 0) {
         cs.dlog[n] = cs.done[c];
-        if (cs.prog && (cs.done[c] || (n + 1) % cs.progn == 0))
-            __hip_atomic_store(cs.prog, cs.done[c] ? -1 - cs.len[c] : n + 1, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_SYSTEM);
+        if (cs.stop && cs.done[c])
+            __hip_atomic_store(cs.stop, 1 + cs.len[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 

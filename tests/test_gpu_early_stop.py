@@ -125,3 +125,37 @@ def test_tests_apart_against_the_oracle(q, m, kw):
     if r["converged"]:
         o = oracle.lanczos_gs(m.t, m.U, m.nup, m.ndn)
         assert abs(r["e0"] - o["e0"]) <= 1e-10 * max(1.0, abs(o["e0"]))
+
+
+CHILD = """
+import ctypes, sys, time
+hip = ctypes.CDLL("libamdhip64.so")
+assert hip.hipSetDeviceFlags(ctypes.c_uint(4)) == 0      # hipDeviceScheduleBlockingSync
+import torch
+import paper_2305_18643_amd as q, synth
+m = synth.rect_cluster(4, 4, U=8.0, mu=4.0)
+b = q.sector_basis(16, 8, 7)
+kw = dict(max_iter=12, tol=0.0, want_vector=False, check_every=int(sys.argv[1]))
+q.lanczos_gs(m, b, **kw)
+w, c = time.perf_counter(), time.thread_time()
+for _ in range(3):
+    q.lanczos_gs(m, b, **kw)
+print("share", (time.thread_time() - c) / (time.perf_counter() - w))
+"""
+
+
+@pytest.mark.parametrize("check_every", [1, 4])
+def test_waits_block_where_the_program_asks(q, check_every):
+    """A program that has asked the runtime for blocking waits gets them: with
+    steps of 3 ms the calling thread sleeps for most of the call (polling the
+    events took all of it)."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", CHILD, str(check_every)], capture_output=True, text=True, timeout=100,
+                       cwd=root, env=dict(os.environ, PYTHONPATH=root))
+    assert r.returncode == 0, r.stderr
+    share = float(r.stdout.split("share")[1])
+    print(f"tests every {check_every} steps: the thread ran for {share:.2f} of the call", flush=True)
+    assert share < 0.5
