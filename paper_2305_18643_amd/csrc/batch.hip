@@ -572,7 +572,7 @@ static int run_round(qcm_engine *E) {
                                              j.md.u_uniform, 2 * j.md.nbond));
             hvb[ng + 1] = hvb[ng] + (int64_t)e.nvec * e.wgs;
             chb[ng + 1] = chb[ng] + (int64_t)e.nvec * e.nchunks;
-            cnb[ng + 1] = cnb[ng] + e.nvec;
+            cnb[ng + 1] = cnb[ng] + e.nvec * finish_parts(e.nchunks);
             ++ng;
         }
         n1[k + 1] = ng;

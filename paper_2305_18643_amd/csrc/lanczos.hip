@@ -445,7 +445,7 @@ static int step_t(Engine &e, int n, hipStream_t s) {
     if (e.fused) {
         // alpha and beta from the fused product's dots; the direct norm pass
         // only for chains whose beta the dots cannot resolve
-        ks_finish_fused<T, OneSrc><<<e.nvec, 256, 0, s>>>(src);
+        ks_finish_fused<T, OneSrc><<<e.nvec * finish_parts(e.nchunks), 256, 0, s>>>(src);
         if (e.nchunks > kFinishChunks) {
             ks_norm<T, OneSrc><<<nk, 256, 0, s>>>(src, 1);
             ks_finish<OneSrc><<<e.nvec, 256, 0, s>>>(src, 4);

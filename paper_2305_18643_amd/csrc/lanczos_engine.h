@@ -23,7 +23,8 @@ struct ChainState {
     double *b0sq;   // <phi|phi> of the start vector
     int32_t *len;   // number of steps recorded
     int32_t *done;  // chain stopped (breakdown or empty start)
-    int32_t *renorm;  // this step's beta needs the direct norm pass (see ks_finish)
+    int32_t *renorm;  // this step's beta needs the direct norm pass (see ks_finish), or
+                      // the chunks of it that are done (see ks_finish_fused)
     int32_t *dlog;    // [maxs] chain 0: whether it had stopped after each step
     int32_t *stop;    // chain 0, in host memory, or NULL: 1 + len once it has stopped
 };

@@ -805,11 +805,11 @@ __global__ void __launch_bounds__(256) ks_sub_prev(Src src) {
 }
 
 // the direct norm pass of one chunk by one workgroup: |x|^2, <v, x>, <vp, x>
-// with x = w - alpha_n v, summed over the 256 threads (every thread gets the sums)
+// with x = w - a v, a = alpha_n, summed over the 256 threads (every thread gets
+// the sums)
 template <typename T>
-__device__ __forceinline__ void chunk_norm(const BGroup &q, int64_t vec, int64_t base, double *sh,
-                                           double *t) {
-    const double a = q.cs.alpha[vec * q.cs.maxs + q.n];
+__device__ __forceinline__ void chunk_norm(const BGroup &q, int64_t vec, double a, int64_t base,
+                                           double *sh, double *t) {
     const int64_t off = vec * q.dim;
     const auto w = gp((const T *)q.w) + off;
     const auto v = gp((const T *)q.v) + off;
@@ -850,7 +850,7 @@ __global__ void __launch_bounds__(256) ks_norm(Src src, int cond) {
     const ChunkAt at = chunk_of(q, local);
     if (cond && !q.cs.renorm[at.vec]) return;
     double t[3];
-    chunk_norm<T>(q, at.vec, at.base, sh, t);
+    chunk_norm<T>(q, at.vec, q.cs.alpha[at.vec * q.cs.maxs + q.n], at.base, sh, t);
     if (threadIdx.x == 0) {
         double *pn = q.pn + at.vec * 3 * q.nchunks + at.c;
         pn[0] = t[0];
@@ -908,9 +908,16 @@ __device__ __forceinline__ void finish_beta(const ChainState &cs, int c, int n, 
 
 // Vectors of at most this many chunks take the direct norm pass, when a chain
 // asks for it, inside the finishing kernel: a step is then three launches
-// instead of five (2.4 + 3.6 us less on a 12-orbital sector), and the rare step
-// that needs the pass reads the vector with one workgroup per chain.
+// instead of five (2.4 + 3.6 us less on a 12-orbital sector).  A chain then has a
+// workgroup per chunk, each of which takes the sums of the dots by itself; more
+// of them would make that count.  Every step asks for it where alpha is more
+// than about 30 beta, as with a large constant in H: 120 steps of ten chains of
+// 10 orbitals (5,5) then take 4.8 ms in FP64, and 60 of one chain of 213,444
+// states 2.2 (12.9 and 18.0 with one workgroup per chain).
 constexpr int kFinishChunks = 32;
+__host__ __device__ inline int finish_parts(int nchunks) {
+    return nchunks <= kFinishChunks ? nchunks : 1;
+}
 
 // per-chain sums of the partials and the recurrence bookkeeping
 // mode 0: alpha_n; mode 1: reorthogonalisation terms, beta_n, breakdown, from
@@ -923,6 +930,7 @@ __global__ void __launch_bounds__(256) ks_finish(Src src, int mode) {
     int64_t local;
     const BGroup &q = src.at(blockIdx.x, &local);
     const int c = (int)local;
+    if (c >= q.nvec) return;
     const ChainState &cs = q.cs;
     const int n = q.n;
     if (mode == 0) {
@@ -969,16 +977,19 @@ __global__ void __launch_bounds__(256) ks_finish(Src src, int mode) {
 
 // modes 0 and 2 together, from the fused product's dots (same layout, q.na
 // partials per chain), unless the dots cannot resolve beta: then the direct
-// norm here (kFinishChunks), or by the norm pass for chains marked cs.renorm.
+// norm here (finish_parts workgroups per chain, a chunk each; the last one to
+// finish its chunk, counted in cs.renorm, takes the sums), or, for longer
+// vectors, by the norm pass for chains marked cs.renorm.
 // The array sums are block_sum's trees, one wave per array.
 template <typename T, class Src>
 __global__ void __launch_bounds__(256) ks_finish_fused(Src src) {
     __shared__ double sh[5 * 256];
     __shared__ double tot[5];
-    __shared__ int direct;
+    __shared__ int flag[2];   // direct norm wanted; this is the last workgroup
     int64_t local;
     const BGroup &q = src.at(blockIdx.x, &local);
-    const int c = (int)local;
+    const int parts = finish_parts(q.nchunks);
+    const int c = (int)(local / parts), part = (int)(local - (int64_t)c * parts);
     const ChainState &cs = q.cs;
     const int n = q.n, t = threadIdx.x, lane = t & 63;
     const double *p = q.pa + (int64_t)c * q.na;
@@ -992,32 +1003,47 @@ __global__ void __launch_bounds__(256) ks_finish_fused(Src src) {
         if (lane == 0) tot[a] = s;
     }
     __syncthreads();
+    const double a = tot[0];   // <v, w>
     if (t == 0) {
-        const double vw = tot[0], ww = tot[1], vv = tot[2];
+        const double ww = tot[1], vv = tot[2];
         const double pw = q.reorth ? tot[3] : 0.0, pv = q.reorth ? tot[4] : 0.0;
-        cs.alpha[(int64_t)c * cs.maxs + n] = vw;
-        cs.apre[c] = vw;
-        if (fabs(vw) > cs.amax[c]) cs.amax[c] = fabs(vw);
-        const double a = vw;
         const double s0 = fma(a * a, vv, fma(-2.0 * a, a, ww));
         const double s1 = q.reorth ? fma(-a, vv, a) : 0.0;
         const double s2 = q.reorth ? fma(-a, pv, pw) : 0.0;
         const bool rn = !(s0 > kDotRel * ww);
-        direct = rn && q.nchunks <= kFinishChunks;
-        cs.renorm[c] = rn && !direct;
-        if (!rn) finish_beta(cs, c, n, q.reorth, s0, s1, s2);
+        flag[0] = rn && q.nchunks <= kFinishChunks;
+        if (part == 0) {
+            cs.alpha[(int64_t)c * cs.maxs + n] = a;
+            cs.apre[c] = a;
+            if (fabs(a) > cs.amax[c]) cs.amax[c] = fabs(a);
+            if (q.nchunks > kFinishChunks) cs.renorm[c] = rn;
+            if (!rn) finish_beta(cs, c, n, q.reorth, s0, s1, s2);
+        }
     }
     __syncthreads();
-    if (!direct) return;
-    // thread k keeps the sums of chunk k (nchunks <= 256), as strided_sum would
-    double r[3] = {0.0, 0.0, 0.0}, x[3];
-    for (int k = 0; k < q.nchunks; ++k) {
-        chunk_norm<T>(q, c, (int64_t)k * kChunk, sh, x);
-        if (t == k)
-            for (int a = 0; a < 3; ++a) r[a] += x[a];
+    if (!flag[0]) return;
+    double x[3];
+    chunk_norm<T>(q, c, a, (int64_t)part * kChunk, sh, x);
+    if (parts == 1) {
+        if (t == 0) finish_beta(cs, c, n, q.reorth, x[0], x[1], x[2]);
+        return;
     }
-    for (int a = 0; a < 3; ++a) x[a] = a == 0 || q.reorth ? block_sum(r[a], sh) : 0.0;
-    if (t == 0) finish_beta(cs, c, n, q.reorth, x[0], x[1], x[2]);
+    double *pn = q.pn + (int64_t)c * 3 * q.nchunks;
+    if (t == 0) {
+        for (int k = 0; k < 3; ++k) pn[k * q.nchunks + part] = x[k];
+        const int before = __hip_atomic_fetch_add(cs.renorm + c, 1, __ATOMIC_ACQ_REL,
+                                                  __HIP_MEMORY_SCOPE_AGENT);
+        flag[1] = before == parts - 1;
+    }
+    __syncthreads();
+    if (!flag[1]) return;
+    const int m = q.nchunks;
+    for (int k = 0; k < 3; ++k)
+        x[k] = k == 0 || q.reorth ? block_sum(strided_sum(pn + k * m, m), sh) : 0.0;
+    if (t == 0) {
+        cs.renorm[c] = 0;
+        finish_beta(cs, c, n, q.reorth, x[0], x[1], x[2]);
+    }
 }
 
 // The two-pass product's partial arrays (three, five with
