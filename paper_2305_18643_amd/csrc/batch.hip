@@ -453,7 +453,7 @@ static int launch_round(qcm_engine *E, int ng, const int (&n1)[4], int na, int n
         for (int k = 0; k < 3; ++k) {
             const int64_t b0 = hvb[n1[k]], n = hvb[n1[k + 1]] - b0;
             const TabSrc src{G + n1[k], hv.begin + n1[k], n1[k + 1] - n1[k], b0};
-            if (n > 0) hv_form_launch<T>(src, k, big, (unsigned)n, kHvThreads, lds[k], s);
+            if (n > 0) hv_form_launch<T>(src, k, big, n, kHvThreads, lds[k], s);
         }
         // alpha and beta from the product's dots; the direct norm pass only
         // for chains whose beta the dots cannot resolve
@@ -462,7 +462,7 @@ static int launch_round(qcm_engine *E, int ng, const int (&n1)[4], int na, int n
             ks_norm<T, TabSrc><<<nk, 256, 0, s>>>(ch, 1);
             ks_finish<TabSrc><<<nn, 256, 0, s>>>(cn, 4);
         }
-        ks_update<T, TabSrc><<<nk * kUpdParts, 256, 0, s>>>(ch);
+        update_launch<T>(ch, nk, s);
     }
     if (nc > 0) kb_control<<<nc, 256, 0, s>>>(C, E->d_stat);
     QCM_LAUNCH_CHECK();

@@ -317,7 +317,7 @@ static int hv_launch_t(const HvOp &op, const void *v, void *w, int nvec, hipStre
             g.vp = v;   // not read: no subtraction
             g.v = v;
             g.w = w;
-            hv_step_launch<T>(OneSrc{g}, (unsigned)((int64_t)nvec * g.wgs),
+            hv_step_launch<T>(OneSrc{g}, (int64_t)nvec * g.wgs,
                               hv_lds(op.up.d, rows, g.rg, prec, op.md.nbytes, op.md.u_uniform,
                                      2 * op.md.nbond),
                               s);

@@ -200,21 +200,21 @@ template <typename T>
 __global__ void __launch_bounds__(256) k_psi(double *__restrict__ psi, const T *__restrict__ v,
                                              int64_t vec, int64_t n_el, int M,
                                              const double *__restrict__ svec) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n_el) return;
     const auto s = cp(svec);
-    const auto p = gp(v) + i;
-    double acc = 0.0;
-    int n = 0;
-    for (; n + 8 <= M; n += 8) {
-        T x[8];
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_el; i += (int64_t)gridDim.x * 256) {
+        const auto p = gp(v) + i;
+        double acc = 0.0;
+        int n = 0;
+        for (; n + 8 <= M; n += 8) {
+            T x[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = __builtin_nontemporal_load(p + (int64_t)(n + u) * vec);
+            for (int u = 0; u < 8; ++u) x[u] = __builtin_nontemporal_load(p + (int64_t)(n + u) * vec);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc = fma(s[n + u], (double)x[u], acc);
+            for (int u = 0; u < 8; ++u) acc = fma(s[n + u], (double)x[u], acc);
+        }
+        for (; n < M; ++n) acc = fma(s[n], (double)p[(int64_t)n * vec], acc);
+        psi[i] = acc;
     }
-    for (; n < M; ++n) acc = fma(s[n], (double)p[(int64_t)n * vec], acc);
-    psi[i] = acc;
 }
 
 // ---------------------------------------------------------------- side stream
@@ -403,7 +403,7 @@ static int step_t(Engine &e, int n, hipStream_t s) {
     const OneSrc src{engine_group(e, n)};
     const unsigned nk = (unsigned)e.nvec * e.nchunks;
     if (e.fused) {
-        hv_step_launch<T>(src, (unsigned)e.nvec * e.wgs,
+        hv_step_launch<T>(src, (int64_t)e.nvec * e.wgs,
                           hv_lds(e.op.up.d, e.rows, e.rg, e.prec, e.op.md.nbytes,
                                  e.op.md.u_uniform, 2 * e.op.md.nbond),
                           s);
@@ -458,7 +458,7 @@ static int step_t(Engine &e, int n, hipStream_t s) {
     if (e.op.split && e.lazy)
         e.pending = 1;   // the next step's in-row pass forms v_{n+1}
     else
-        ks_update<T, OneSrc><<<nk * kUpdParts, 256, 0, s>>>(src);
+        update_launch<T>(src, nk, s);
     QCM_LAUNCH_CHECK();
     // rotate: v_{n-1} <- v_n, v_n <- the new vector, next w <- old v_{n-1}
     int t = e.ivp;
@@ -504,7 +504,7 @@ static int settle_t(Engine &e, hipStream_t s) {
     g.v = e.vbuf[e.ivp];
     g.w = e.vbuf[e.iv];
     const OneSrc src{g};
-    ks_update<T, OneSrc><<<(unsigned)e.nvec * e.nchunks * kUpdParts, 256, 0, s>>>(src);
+    update_launch<T>(src, (int64_t)e.nvec * e.nchunks, s);
     QCM_LAUNCH_CHECK();
     return QCM_OK;
 }
@@ -827,7 +827,7 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
         e.pending = 0;
         const int have = std::min(nkeep, M);
         if (have) {
-            const unsigned g = (unsigned)ceil_div((size_t)dim, 256);
+            const unsigned g = (unsigned)std::min<size_t>(ceil_div((size_t)dim, 256), 1 << 23);
             const int64_t el = (int64_t)(vb / (o->prec == QCM_FP64 ? 8 : 4));
             if (o->prec == QCM_FP64)
                 k_psi<double><<<g, 256, 0, s>>>(psi, (const double *)keep, el, dim, have, svec);

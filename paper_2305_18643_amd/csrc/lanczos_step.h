@@ -109,11 +109,20 @@ struct TabSrc {
 };
 struct OneSrc {
     BGroup g;
+    int64_t base = 0;   // work item of workgroup 0
     __device__ __forceinline__ const BGroup &at(int64_t x, int64_t *local) const {
-        *local = x;
+        *local = x + base;
         return g;
     }
 };
+
+// Launches of work items in slices: a launch takes fewer than 2^32 threads.
+template <class Src, class F>
+inline void each_slice(Src src, int64_t items, int64_t threads, F &&launch) {
+    const int64_t most = 0xffffffffll / threads;
+    for (int64_t left = items; left > 0; left -= most, src.base += most)
+        launch(src, (unsigned)std::min(left, most));
+}
 
 inline void row_shape(int64_t d_up, int64_t d_dn, int prec, int32_t *rows, int32_t *nblk) {
     (void)prec;
@@ -740,23 +749,25 @@ inline unsigned hv_threads(int64_t d_up, int32_t rows, bool lut, bool dots) {
 
 // The fused product of one source of work, all of one form.
 template <typename T, class Src>
-inline void hv_form_launch(const Src &src, int form, bool big, unsigned wgs, unsigned threads,
+inline void hv_form_launch(const Src &all, int form, bool big, int64_t items, unsigned threads,
                            size_t lds, hipStream_t s) {
-    if (form == kHvOne && !big)
-        ks_hv<T, Src, kHvOne, false><<<wgs, threads, lds, s>>>(src);
-    else if (form == kHvOne)
-        ks_hv<T, Src, kHvOne, true><<<wgs, threads, lds, s>>>(src);
-    else if (form == kHvShort && !big)
-        ks_hv<T, Src, kHvShort, false><<<wgs, threads, lds, s>>>(src);
-    else if (form == kHvShort)
-        ks_hv<T, Src, kHvShort, true><<<wgs, threads, lds, s>>>(src);
-    else if (!big)
-        ks_hv<T, Src, kHvRows, false><<<wgs, threads, lds, s>>>(src);
-    else
-        ks_hv<T, Src, kHvRows, true><<<wgs, threads, lds, s>>>(src);
+    each_slice(all, items, threads, [&](const Src &src, unsigned wgs) {
+        if (form == kHvOne && !big)
+            ks_hv<T, Src, kHvOne, false><<<wgs, threads, lds, s>>>(src);
+        else if (form == kHvOne)
+            ks_hv<T, Src, kHvOne, true><<<wgs, threads, lds, s>>>(src);
+        else if (form == kHvShort && !big)
+            ks_hv<T, Src, kHvShort, false><<<wgs, threads, lds, s>>>(src);
+        else if (form == kHvShort)
+            ks_hv<T, Src, kHvShort, true><<<wgs, threads, lds, s>>>(src);
+        else if (!big)
+            ks_hv<T, Src, kHvRows, false><<<wgs, threads, lds, s>>>(src);
+        else
+            ks_hv<T, Src, kHvRows, true><<<wgs, threads, lds, s>>>(src);
+    });
 }
 template <typename T>
-inline void hv_step_launch(const OneSrc &src, unsigned wgs, size_t lds, hipStream_t s) {
+inline void hv_step_launch(const OneSrc &src, int64_t wgs, size_t lds, hipStream_t s) {
     const BGroup &g = src.g;
     hv_form_launch<T>(src, hv_form(g.d_up, g.rows), hv_big(g.dim, sizeof(T)), wgs,
                       hv_threads(g.d_up, g.rows, g.u_uniform < 0.0, g.pa != nullptr), lds, s);
@@ -1430,6 +1441,13 @@ __global__ void __launch_bounds__(kChainThreads) ks_chain(const OneSrc src, cons
         cs.done[c] = done;
         cs.len[c] = len;
     }
+}
+
+template <typename T, class Src>
+inline void update_launch(const Src &all, int64_t chunks, hipStream_t s) {
+    each_slice(all, chunks, 256 * kUpdParts, [&](const Src &src, unsigned n) {
+        ks_update<T, Src><<<n * kUpdParts, 256, 0, s>>>(src);
+    });
 }
 
 // psi += svec[n] v_n alone (the last replay step)
