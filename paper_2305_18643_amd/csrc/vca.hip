@@ -132,6 +132,7 @@ __global__ void __launch_bounds__(64) k_vca_k(int L, int R, const double *__rest
         Wm[e] = w;
     }
     wave_lds_sync();
+    double mx = 0.0;   // the largest part of an element
     for (int e = t; e < R * R; e += 64) {  // L(k) = diag(w') + Q^T W
         const int r = e / R, s = e % R;
         c64 l = {r == s ? poles[r] : 0.0, 0.0};
@@ -141,10 +142,26 @@ __global__ void __launch_bounds__(64) k_vca_k(int L, int R, const double *__rest
             l.im += q * Wm[i * R + s].im;
         }
         A[r * S + s] = l;
+        mx = fmax(mx, fmax(fabs(l.re), fabs(l.im)));
     }
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
     wave_lds_sync();
+    // elements far from 1 are scaled by a power of two, so that their squares
+    // neither vanish nor overflow
+    int sc = 0;
+    if (mx > 0.0 && isfinite(mx) && (mx < 0x1p-64 || mx > 0x1p64)) {
+        sc = ilogb(mx);
+        mx = ldexp(mx, -sc);
+        for (int e = t; e < R * R; e += 64) {
+            c64 *l = A + e / R * S + e % R;
+            *l = {ldexp(l->re, -sc), ldexp(l->im, -sc)};
+        }
+        wave_lds_sync();
+    }
     // Householder: column c's part below the subdiagonal is reflected away,
-    // leaving the subdiagonal's modulus in ee[c]
+    // leaving the subdiagonal's modulus in ee[c].  A part of less than 2^-70 of
+    // the largest element is dropped (1/beta of a much smaller one overflows).
+    const double drop = 0x1p-140 * mx * mx;
     for (int c = 0; c < R - 1; ++c) {
         const bool on = t > c && t < R;
         c64 x = {0.0, 0.0};
@@ -157,7 +174,7 @@ __global__ void __launch_bounds__(64) k_vca_k(int L, int R, const double *__rest
         const double h0 = x0.re * x0.re + x0.im * x0.im;
         const double a0 = sqrt(h0), nrm = sqrt(h0 + tail);
         if (t == 0) ee[c] = nrm;
-        if (!(tail > 0.0)) {   // nothing to reflect
+        if (!(tail > drop)) {   // nothing to reflect
             wave_lds_sync();
             continue;
         }
@@ -247,7 +264,7 @@ __global__ void __launch_bounds__(64) k_vca_k(int L, int R, const double *__rest
         if (t == 0) {
             double neg = 0.0;
             for (int i = 0; i < nneg; ++i) neg += bc[i * g];
-            per_k[k] = neg;
+            per_k[k] = ldexp(neg, sc);
         }
     } else if (t == 0) {
         per_k[k] = 0.0;

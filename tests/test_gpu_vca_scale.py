@@ -1,0 +1,46 @@
+"""The k sum of the pole formula where elements of L(k) are tiny beside others, or
+all of them far from 1: nearly decoupled poles, a matrix scaled by powers of
+ten, against numpy's eigvalsh.  Held to 8 R eps |L(k)|_F as at ordinary scales."""
+import numpy as np
+import pytest
+
+from oracle import vca as O
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(poles, Q, dt, bonds, ks):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2305_18643_amd as q
+    L, R = Q.shape
+    _, per = q.vca_omega(0.0, poles, Q, dt, bonds, ks)
+    for i, k in enumerate(ks):
+        Lk = np.diag(poles) + Q.T @ O.v_of_k(L, dt, bonds, k) @ Q
+        s = np.abs(Lk).max()
+        w = s * np.linalg.eigvalsh(Lk / s)
+        assert abs(per[i] - w[w < 0].sum()) <= 8 * R * 2.0 ** -53 * s * np.linalg.norm(Lk / s), (i, per[i])
+
+
+BONDS = [(0, 1, (1, 0, 0), -1.0), (1, 1, (0, 1, 0), 0.7)]
+
+
+@pytest.mark.parametrize("tiny", [1e-30, 1e-50, 1e-78, 1e-80, 1e-81, 1e-90, 1e-150, 0.0])
+@pytest.mark.parametrize("which", ["all", "first", "last"])
+def test_nearly_decoupled_poles(tiny, which):
+    rng = np.random.default_rng(41)
+    R = 9
+    Q = rng.normal(size=(2, R))
+    Q[:, {"all": slice(0, R), "first": slice(0, 5), "last": slice(4, R)}[which]] *= tiny
+    dt = np.array([[0.3, -1.0], [-1.0, 0.2]])
+    _check(rng.uniform(-4, 4, R), Q, dt, BONDS, rng.uniform(0, 1, (5, 3)))
+
+
+@pytest.mark.parametrize("scale", [1e-150, 1e-100, 1e-25, 1e-19, 1e19, 1e25, 1e100, 1e150])
+def test_scaled_matrix(scale):
+    rng = np.random.default_rng(42)
+    R = 12
+    dt = scale * np.array([[0.3, -1.0], [-1.0, 0.2]])
+    bonds = [(i, j, s, scale * t) for i, j, s, t in BONDS]
+    _check(scale * rng.uniform(-4, 4, R), rng.normal(size=(2, R)) / 3, dt, bonds, rng.uniform(0, 1, (5, 3)))
