@@ -75,7 +75,7 @@ struct VBond {
 // lane from LDS (broadcast reads that can be in flight together) instead of
 // by six dependent shuffles, and the eigenvalues, wanted only where negative,
 // share the lanes: with n of them, 64 / n points of each bracket per Sturm
-// count.  R = 24, 1,024 wave-vectors: 0.13 ms, against 2.7 ms as a parallel
+// count.  R = 24, 1,024 wave-vectors: 0.085 ms, against 2.7 ms as a parallel
 // Jacobi method on the real 48 x 48 form in one workgroup each.  Error of the
 // sum relative to |L|, rms: 7e-16 (R = 24) and 1.2e-15 (R = 64), Jacobi 1.4e-14
 // and 7.4e-14.
@@ -239,23 +239,31 @@ __global__ void __launch_bounds__(64) k_vca_k(int L, int R, const double *__rest
     wave_lds_sync();
     const double scale = fmax(fabs(lo), fabs(hi));
     lo -= 1e-15 * scale;
+    if (R <= 2) {   // in closed form
+        const double d1 = R == 2 ? dd[1] : dd[0], e2 = R == 2 ? ee[0] : 0.0;
+        const double m = 0.5 * (dd[0] + d1), r = 0.5 * (dd[0] - d1), h = sqrt(fma(r, r, e2));
+        const double neg = fmin(m - h, 0.0) + (R == 2 ? fmin(m + h, 0.0) : 0.0);
+        if (t == 0) per_k[k] = ldexp(neg, sc);
+        return;
+    }
     const int nneg = sturm_below(R, dd, ee, 0.0);
     double v = 0.0;
     if (nneg > 0) {
-        // lane e g + j tests point j of g in the bracket of eigenvalue e
+        // lane e g + j tests point j of g in the bracket of eigenvalue e, until no
+        // number lies between its ends
         const int g = 64 / nneg, e = t / g, j = t - e * g;
         double bl = lo, bh = 0.0;
         for (int it = 0; it < 64; ++it) {
-            const bool wide = e < nneg && bh - bl > 2e-17 * scale && bl < bl + 0.5 * (bh - bl);
-            if (!__any(wide)) break;
-            auto point = [&](int i) { return bl + (bh - bl) * (double)(i + 1) / (double)(g + 1); };
-            const unsigned long long m = __ballot(e < nneg && sturm_below(R, dd, ee, point(j)) > e);
+            const double mid = bl + 0.5 * (bh - bl);
+            if (!__any(e < nneg && bh - bl > 2e-17 * scale && bl < mid && mid < bh)) break;
+            const double at = bl + (bh - bl) * (double)(j + 1) / (double)(g + 1);
+            const unsigned long long m = __ballot(e < nneg && sturm_below(R, dd, ee, at) > e);
             const unsigned long long mine =
                 e < nneg ? (m >> (e * g)) & (g < 64 ? (1ull << g) - 1ull : ~0ull) : 0ull;
             const int first = mine ? __ffsll(mine) - 1 : g;
-            const double nl = first == 0 ? bl : point(first - 1);
-            bh = first == g ? bh : point(first);
-            bl = nl;
+            const double below = __shfl(at, e * g + first - 1), above = __shfl(at, e * g + first);
+            bl = first == 0 ? bl : below;
+            bh = first == g ? bh : above;
         }
         if (j == 0 && e < nneg) v = 0.5 * (bl + bh);
         wave_lds_sync();
