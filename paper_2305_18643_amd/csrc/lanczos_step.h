@@ -118,8 +118,10 @@ struct OneSrc {
 
 // Launches of work items in slices: a launch takes fewer than 2^32 threads.
 template <class Src, class F>
-inline void each_slice(Src src, int64_t items, int64_t threads, F &&launch) {
+inline void each_slice(const Src &all, int64_t items, int64_t threads, F &&launch) {
     const int64_t most = 0xffffffffll / threads;
+    if (items <= most) return launch(all, (unsigned)items);
+    Src src = all;
     for (int64_t left = items; left > 0; left -= most, src.base += most)
         launch(src, (unsigned)std::min(left, most));
 }
