@@ -744,8 +744,11 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
         for (; seen < ntest && !stop; ++seen) {
             if (seen > t && pairs) break;
             const hipEvent_t ev = side.done[(seen + (pairs ? 1 : 0)) % kTests];
-            // (a wait of the runtime's, so that it blocks or spins as the program chose)
-            const hipError_t q = seen <= t ? hipEventSynchronize(ev) : hipEventQuery(ev);
+            // a short poll (it answers sooner: 1 % of a ground state of 12 orbitals),
+            // then the runtime's own wait, which blocks or spins as the program chose
+            hipError_t q = hipEventQuery(ev);
+            for (int k = 0; k < 50 && q == hipErrorNotReady && seen <= t; ++k) q = hipEventQuery(ev);
+            if (q == hipErrorNotReady && seen <= t) q = hipEventSynchronize(ev);
             if (q == hipErrorNotReady) break;
             QCM_HIP(q);
             const GsTest *g = (const GsTest *)side.pinned + seen % kTests;

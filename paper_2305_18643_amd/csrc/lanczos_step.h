@@ -1001,8 +1001,8 @@ __global__ void __launch_bounds__(256) ks_finish_fused(Src src) {
     __shared__ int flag[2];   // direct norm wanted; this is the last workgroup
     int64_t local;
     const BGroup &q = src.at(blockIdx.x, &local);
-    const int parts = finish_parts(q.nchunks);
-    const int c = (int)(local / parts), part = (int)(local - (int64_t)c * parts);
+    const uint32_t parts = finish_parts(q.nchunks), x0 = (uint32_t)local;
+    const int c = parts == 1 ? x0 : x0 / parts, part = x0 - c * parts;
     const ChainState &cs = q.cs;
     const int n = q.n, t = threadIdx.x, lane = t & 63;
     const double *p = q.pa + (int64_t)c * q.na;
@@ -1046,7 +1046,7 @@ __global__ void __launch_bounds__(256) ks_finish_fused(Src src) {
         for (int k = 0; k < 3; ++k) pn[k * q.nchunks + part] = x[k];
         const int before = __hip_atomic_fetch_add(cs.renorm + c, 1, __ATOMIC_ACQ_REL,
                                                   __HIP_MEMORY_SCOPE_AGENT);
-        flag[1] = before == parts - 1;
+        flag[1] = before == (int)parts - 1;
     }
     __syncthreads();
     if (!flag[1]) return;
