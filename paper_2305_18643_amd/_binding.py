@@ -422,8 +422,13 @@ class HvPlan:
             pass
 
 
-# Vectors a ground-state call offers to keep, and the most bytes it offers
-_KEEP_VECTORS, _KEEP_BYTES = 160, 4 << 30
+# What a ground-state call offers for keeping its recurrence's vectors: room for
+# so many of them (every ground state measured, of 4 to 16 orbitals, took 24 to
+# 155 steps at the default tolerance; what is not kept is run again) and at most
+# this part of the card's free memory (4.5 GB of an empty card, less where other
+# work has filled it), looked up for offers above so many bytes; none where that
+# holds fewer than an eighth of them, which would save 6 % of the call at most.
+_KEEP_VECTORS, _KEEP_PART, _KEEP_LOOK = 160, 64, 64 << 20
 
 
 def _gs_workspace(torch, need, o, dim, device):
@@ -433,9 +438,11 @@ def _gs_workspace(torch, need, o, dim, device):
     for that, the bare workspace."""
     if o.want_vector:
         vec = -(-dim * (8 if o.prec == QCM_FP64 else 4) // 256) * 256
-        n = min(max(o.fixed_steps if o.fixed_steps > 0 else o.max_iter, 0) + 1, _KEEP_VECTORS)
-        n = min(n, _KEEP_BYTES // vec)
-        if n >= 4:
+        want = min(max(o.fixed_steps if o.fixed_steps > 0 else o.max_iter, 0) + 1, _KEEP_VECTORS)
+        n = want
+        if n * vec > _KEEP_LOOK:
+            n = min(n, max(torch.cuda.mem_get_info(device)[0] // _KEEP_PART, _KEEP_LOOK) // vec)
+        if n >= 4 and 8 * n >= want:
             try:
                 return _workspace(torch, need + 256 + n * vec, device)
             except torch.OutOfMemoryError:
@@ -446,7 +453,11 @@ def _gs_workspace(torch, need, o, dim, device):
 def lanczos_gs(model, basis: SectorBasis, *, max_iter=600, fixed_steps=0, want_vector=True,
                reorth=0, prec="fp64", check_every=1, tol=1e-12, btol=1e-13, seed=1, v0=None,
                stream=None, ws=None) -> dict:
-    """Lanczos ground state; returns e0, residuals, n_iter, flags, alpha, beta, psi."""
+    """Lanczos ground state; returns e0, residuals, n_iter, flags, alpha, beta, psi.  With a vector wanted
+    the workspace also has room for up to 160 of the recurrence's vectors, at
+    most 1/64 of the card's free memory (it goes back to torch's allocator when
+    the call returns), unless one is passed as ws (uint8); one of just the size
+    that qcm_lanczos_gs asks for keeps none."""
     torch = _torch()
     lib = load_library()
     m = as_model(model)
@@ -1006,7 +1017,11 @@ def sym_lanczos_gs(H: SymHamiltonian, *, max_iter=600, fixed_steps=0, want_vecto
                    check_every=1, tol=1e-12, btol=1e-13, seed=1, v0=None, stream=None,
                    ws=None) -> dict:
     """Lanczos ground state of a symmetry-adapted sector (FP64); the same
-    results as lanczos_gs, psi in the symmetry-adapted basis."""
+    results as lanczos_gs, psi in the symmetry-adapted basis.  With a vector wanted
+    the workspace also has room for up to 160 of the recurrence's vectors, at
+    most 1/64 of the card's free memory (it goes back to torch's allocator when
+    the call returns), unless one is passed as ws (uint8); one of just the size
+    that qcm_sym_lanczos_gs asks for keeps none."""
     torch = _torch()
     lib = load_library()
     o = LanczosOpts()
