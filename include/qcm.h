@@ -223,8 +223,9 @@ typedef struct qcm_gs_result {
  * paper's b_{n+1}^2.  The ground-state vector psi = sum_n s_n v_n is summed
  * from the vectors of the recurrence as far as the workspace keeps them (every
  * dim elements, rounded up to 256 bytes, beyond *ws_needed hold one more; at
- * least four, or none are kept) and otherwise rebuilt by a second identical
- * pass, with the same result bit for bit; it is then normalised.
+ * least four, or none are kept, nor where d_gs or d_v0 lies there) and otherwise
+ * rebuilt by a second identical pass, with the same result bit for bit; it is
+ * then normalised.
  *   The residual tests run on a side stream (default priority, waiting on
  * `stream` through events) beside the next step, with a little pinned host
  * memory; one such set per device is created the first time it is needed (one

@@ -659,6 +659,13 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
         nkeep = (int)std::min<size_t>((ws_bytes - at) / vb, (size_t)limit + 1);
     if (nkeep < 4) nkeep = 0;
     char *const keep = (char *)d_ws + at;
+    // (a caller may have put its own vectors past what the call needs)
+    auto within = [&](const void *p, size_t bytes) {
+        return p && (const char *)p < keep + nkeep * vb && keep < (const char *)p + bytes;
+    };
+    if (within(d_gs, sizeof(double) * (size_t)dim) ||
+        within(o->d_v0, (o->prec == QCM_FP64 ? 8 : 4) * (size_t)dim))
+        nkeep = 0;
     void *const ring[3] = {e.vbuf[0], e.vbuf[1], e.vbuf[2]};
     auto slot = [&](int n) -> void * { return n < nkeep ? keep + (size_t)n * vb : ring[n % 3]; };
     // v_n is in slot(n); the product of step n goes where v_{n+1} will be.  The
