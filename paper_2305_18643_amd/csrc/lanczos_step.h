@@ -297,6 +297,22 @@ constexpr int hv_waves() {
                               : (std::is_same<S, OneSrc>::value ? 4 : 8);
 }
 
+// With two columns per lane and an odd row length d the last lane redoes column
+// d - 2, with the hop count of its own tile, and stores it as the lane before
+// does.  In a row of 128 k + 1 columns that lane would be in a tile of its own,
+// whose hop count may be less than that column needs (which is in the tile before);
+// no sector has such rows.
+constexpr bool hv_rows_fit_pairs() {
+    for (int L = 1; L <= 32; ++L)
+        for (int N = 0; N <= L; ++N) {
+            int64_t d = 1;
+            for (int i = 1; i <= N; ++i) d = d * (L - N + i) / i;
+            if (d > 1 && d < 65536 && d % 128 == 1) return false;
+        }
+    return true;
+}
+static_assert(hv_rows_fit_pairs(), "a row of 128 k + 1 columns: its last lane stores another tile's column");
+
 template <typename T, class Src, int FORM, bool BIG>
 __global__ void __launch_bounds__(kHvThreads, (hv_waves<T, Src, FORM>())) ks_hv(Src src) {
     constexpr bool ONE = FORM == kHvOne;
