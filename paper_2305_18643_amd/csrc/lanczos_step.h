@@ -948,11 +948,20 @@ __host__ __device__ inline int finish_parts(int nchunks) {
     return nchunks <= kFinishChunks ? nchunks : 1;
 }
 
+// x = w - a v with a = <v, w>: s = |x|^2, <v, x>, <vp, x> from the dots d
+// (<v,w>, <w,w>, <v,v>, and with reorthogonalisation <vp,w>, <vp,v>); whether
+// |x|^2 needs the direct norm instead
+__device__ __forceinline__ bool dot_terms(const double *d, int reorth, double *s) {
+    const double a = d[0], ww = d[1], vv = d[2];
+    s[0] = fma(a * a, vv, fma(-2.0 * a, a, ww));
+    s[1] = reorth ? fma(-a, vv, a) : 0.0;
+    s[2] = reorth ? fma(-a, d[4], d[3]) : 0.0;
+    return !(s[0] > kDotRel * ww);
+}
+
 // per-chain sums of the partials and the recurrence bookkeeping
 // mode 0: alpha_n; mode 1: reorthogonalisation terms, beta_n, breakdown, from
-// the norm pass; mode 2: the same from the dots of the two-pass product
-// (pa: <v,w>, <w,w>, <v,v>, and with reorthogonalisation <vp,w>, <vp,v>);
-// mode 4: mode 1 for the chains marked cs.renorm.
+// the norm pass; mode 4: mode 1 for the chains marked cs.renorm.
 template <class Src>
 __global__ void __launch_bounds__(256) ks_finish(Src src, int mode) {
     __shared__ double sh[256];
@@ -974,24 +983,6 @@ __global__ void __launch_bounds__(256) ks_finish(Src src, int mode) {
         }
         return;
     }
-    if (mode == 2) {
-        const double *p = q.pa + (int64_t)c * q.na;
-        const double ww = block_sum(strided_sum(p + q.pstride, q.na), sh);
-        const double vv = block_sum(strided_sum(p + 2 * q.pstride, q.na), sh);
-        double pw = 0.0, pv = 0.0;
-        if (q.reorth) {
-            pw = block_sum(strided_sum(p + 3 * q.pstride, q.na), sh);
-            pv = block_sum(strided_sum(p + 4 * q.pstride, q.na), sh);
-        }
-        if (threadIdx.x != 0) return;
-        const double a = cs.apre[c];   // <v, w>
-        // x = w - a v: |x|^2, <v, x>, <vp, x> from the dots
-        const double s0 = fma(a * a, vv, fma(-2.0 * a, a, ww));
-        const double s1 = q.reorth ? fma(-a, vv, a) : 0.0;
-        const double s2 = q.reorth ? fma(-a, pv, pw) : 0.0;
-        finish_beta(cs, c, n, q.reorth, s0, s1, s2);
-        return;
-    }
     if (mode == 4 && !cs.renorm[c]) return;
     const double *p = q.pn + (int64_t)c * 3 * q.nchunks;
     const double s0 = block_sum(strided_sum(p, q.nchunks), sh);
@@ -1004,8 +995,8 @@ __global__ void __launch_bounds__(256) ks_finish(Src src, int mode) {
     finish_beta(cs, c, n, q.reorth, s0, s1, s2);
 }
 
-// modes 0 and 2 together, from the fused product's dots (same layout, q.na
-// partials per chain), unless the dots cannot resolve beta: then the direct
+// alpha_n and beta_n from the fused product's dots (q.na partials of each per
+// chain), unless the dots cannot resolve beta: then the direct
 // norm here (finish_parts workgroups per chain, a chunk each; the last one to
 // finish its chunk, counted in cs.renorm, takes the sums), or, for longer
 // vectors, by the norm pass for chains marked cs.renorm.
@@ -1034,19 +1025,15 @@ __global__ void __launch_bounds__(256) ks_finish_fused(Src src) {
     __syncthreads();
     const double a = tot[0];   // <v, w>
     if (t == 0) {
-        const double ww = tot[1], vv = tot[2];
-        const double pw = q.reorth ? tot[3] : 0.0, pv = q.reorth ? tot[4] : 0.0;
-        const double s0 = fma(a * a, vv, fma(-2.0 * a, a, ww));
-        const double s1 = q.reorth ? fma(-a, vv, a) : 0.0;
-        const double s2 = q.reorth ? fma(-a, pv, pw) : 0.0;
-        const bool rn = !(s0 > kDotRel * ww);
+        double s[3];
+        const bool rn = dot_terms(tot, q.reorth, s);
         flag[0] = rn && q.nchunks <= kFinishChunks;
         if (part == 0) {
             cs.alpha[(int64_t)c * cs.maxs + n] = a;
             cs.apre[c] = a;
             if (fabs(a) > cs.amax[c]) cs.amax[c] = fabs(a);
             if (q.nchunks > kFinishChunks) cs.renorm[c] = rn;
-            if (!rn) finish_beta(cs, c, n, q.reorth, s0, s1, s2);
+            if (!rn) finish_beta(cs, c, n, q.reorth, s[0], s[1], s[2]);
         }
     }
     __syncthreads();
@@ -1079,7 +1066,8 @@ __global__ void __launch_bounds__(256) ks_finish_fused(Src src) {
 // reorthogonalisation, of q.na values per chain) are summed in two launches:
 // ks_dots_stage sums contiguous ranges, one per workgroup of kDotBlocks, into
 // q.pn ([chain][array][kDotBlocks]); ks_finish_dots sums those in order and
-// records alpha_n and beta_n as ks_finish modes 0 and 2 do.  Each thread's
+// records alpha_n and beta_n as ks_finish_fused does (the direct norm a pass of
+// its own).  Each thread's
 // share is summed in index order and each block's by a fixed tree.
 constexpr int kDotBlocks = 64;
 
@@ -1134,20 +1122,13 @@ __global__ void __launch_bounds__(kDotBlocks) ks_finish_dots(Src src) {
         __syncthreads();
     }
     if (t != 0) return;
-    const double vw = sh[0][0], ww = sh[1][0], vv = sh[2][0];
-    const double pw = q.reorth ? sh[3][0] : 0.0, pv = q.reorth ? sh[4][0] : 0.0;
-    // mode 0: alpha_n = <v, w>
-    cs.alpha[(int64_t)c * cs.maxs + n] = vw;
-    cs.apre[c] = vw;
-    if (fabs(vw) > cs.amax[c]) cs.amax[c] = fabs(vw);
-    // mode 2: x = w - a v: |x|^2, <v, x>, <vp, x> from the dots (or the
-    // direct norm pass when they cannot resolve beta)
-    const double a = vw;
-    const double s0 = fma(a * a, vv, fma(-2.0 * a, a, ww));
-    const double s1 = q.reorth ? fma(-a, vv, a) : 0.0;
-    const double s2 = q.reorth ? fma(-a, pv, pw) : 0.0;
-    cs.renorm[c] = !(s0 > kDotRel * ww);
-    if (!cs.renorm[c]) finish_beta(cs, c, n, q.reorth, s0, s1, s2);
+    const double d[5] = {sh[0][0], sh[1][0], sh[2][0], sh[3][0], sh[4][0]};
+    cs.alpha[(int64_t)c * cs.maxs + n] = d[0];
+    cs.apre[c] = d[0];
+    if (fabs(d[0]) > cs.amax[c]) cs.amax[c] = fabs(d[0]);
+    double s3[3];
+    cs.renorm[c] = dot_terms(d, q.reorth, s3);
+    if (!cs.renorm[c]) finish_beta(cs, c, n, q.reorth, s3[0], s3[1], s3[2]);
 }
 
 // pass 3: w = (w - alpha v - c1 v - c2 vp) / beta_n; psi += svec[n] v (replay).
@@ -1392,14 +1373,14 @@ __global__ void __launch_bounds__(kChainThreads) ks_chain(const OneSrc src, cons
             flag[1] = done;
         };
         if (tid == 0) {
-            const double ww = tot[1], vv = tot[2];
             a = tot[0];
             al[n] = a;
             if (fabs(a) > amax) amax = fabs(a);
-            s0 = fma(a * a, vv, fma(-2.0 * a, a, ww));
-            s1 = q.reorth ? fma(-a, vv, a) : 0.0;
-            s2 = q.reorth ? fma(-a, tot[4], tot[3]) : 0.0;
-            flag[0] = !(s0 > kDotRel * ww);
+            double s[3];
+            flag[0] = dot_terms(tot, q.reorth, s);
+            s0 = s[0];
+            s1 = s[1];
+            s2 = s[2];
             sc[0] = a;
             if (!flag[0]) beta_of();
         }
