@@ -689,16 +689,18 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
     // The tests run on a side stream beside the steps, some of which are
     // enqueued past a test whose verdict is not known yet: such a step is wasted
     // if the verdict ends the recurrence, but changes nothing (its coefficients
-    // are not read).  Test t has status record t mod kTests.  A test after every
-    // step (or every second of a short one): launch t takes its theta_0 and test
-    // t - 1's estimate, side by side, and two tests' steps run ahead.  Tests
-    // further apart: launch t is the whole test (40 to 150 us), and as many steps
-    // run ahead as take about that long, so that neither the steps wait for it
-    // nor many are wasted (with the estimate left to the next launch, 20 steps
-    // apart, up to 40 were: 14 orbitals (7,7) 59.8 -> 52.5 ms; 2 steps apart, 12
-    // orbitals, whole tests 4.65 ms, pairs 4.39).
-    const int ahead = dim >= (1 << 24) ? 1 : dim >= (1 << 21) ? 2 : 4;
-    const bool pairs = every == 1 || 2 * every <= ahead;
+    // are not read).  Test t is launch t and has status record t mod kTests.
+    // Tests after every step, or faster than whole ones can be taken: launch t
+    // takes its theta_0 and, side by side, test t - 1's estimate, and two tests'
+    // steps run ahead.  Tests further apart: launch t is the whole test, and as
+    // many steps run ahead as take about that long, so that neither the steps
+    // wait for it nor many are wasted (with the estimate left to the next launch,
+    // 20 steps apart, up to 40 were: 14 orbitals (7,7) 59.8 -> 52.5 ms; tests 2
+    // steps apart, 12 orbitals, whole 4.65 ms, pairs 4.39; 10 apart up to step
+    // 1,000, whole 55 ms, pairs 37).  The times are those measured: a whole test
+    // 45 us at 30 steps, 100 at 140, a step 25 us at 0.85 M states, 3.3 ms at 166 M.
+    const double step_us = 20.0 + 20e-6 * (double)dim;
+    auto ahead_of = [&](int Mt) { return (int)ceil((30.0 + 0.5 * Mt) / step_us); };
     SideLease side;
     QCM_TRY(side.lease());
     // With fixed steps there are no tests, but a chain that stops early (its
@@ -724,14 +726,17 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
         e.cs.stop = (int32_t *)side.pinned;
     }
     int ntest = 0, seen = 0, nlaunch = 0, tm[kTests] = {0};
-    bool stop = false;
+    bool stop = false, pair[kTests] = {false};
     auto launch_test = [&](int Mt) -> int {
         const int k = nlaunch % kTests, kp = (nlaunch + kTests - 1) % kTests;
         QCM_HIP(hipEventRecord(side.ready[k], s));
         QCM_HIP(hipStreamWaitEvent(side.s, side.ready[k], 0));
-        if (pairs)
-            k_tridiag_test<<<nlaunch > 0 ? 2 : 1, 256, 0, side.s>>>(
-                e.cs.alpha, e.cs.beta, Mt, nlaunch > 0 ? tm[kp] : 0, o->tol, work,
+        // (from whole tests to pairs only: ahead_of grows with the steps)
+        const bool prev = nlaunch > 0 && pair[kp];
+        pair[k] = prev || every == 1 || every <= ahead_of(Mt);
+        if (pair[k])
+            k_tridiag_test<<<prev ? 2 : 1, 256, 0, side.s>>>(
+                e.cs.alpha, e.cs.beta, Mt, prev ? tm[kp] : 0, o->tol, work,
                 work + 5 * (size_t)limit, svec, status + kp, status + k, e.cs.dlog, e.cs.len,
                 (GsTest *)side.pinned + kp);
         else
@@ -746,11 +751,12 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
         return QCM_OK;
     };
     // the verdicts of the tests in order, until one ends the recurrence: those up
-    // to t are waited for, later ones (whole tests) taken if they are there
+    // to t are waited for, later ones (of whole tests) taken if they are there
     auto verdicts = [&](int t) -> int {
         for (; seen < ntest && !stop; ++seen) {
-            if (seen > t && pairs) break;
-            const hipEvent_t ev = side.done[(seen + (pairs ? 1 : 0)) % kTests];
+            const bool p = pair[seen % kTests];
+            if (seen > t && p) break;
+            const hipEvent_t ev = side.done[(seen + (p ? 1 : 0)) % kTests];   // its verdict's launch
             // a short poll (it answers sooner: 1 % of a ground state of 12 orbitals),
             // then the runtime's own wait, which blocks or spins as the program chose
             hipError_t q = hipEventQuery(ev);
@@ -794,13 +800,15 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
         }
         if (check) QCM_TRY(launch_test(n + 1));
         if (last) {
-            if (pairs) QCM_TRY(launch_test(0));
+            if (pair[(nlaunch - 1) % kTests]) QCM_TRY(launch_test(0));
             QCM_TRY(verdicts(ntest - 1));
-        } else if (pairs) {
-            QCM_TRY(verdicts(ntest - 3));
         } else {
-            int t = seen;   // the first test less than `ahead` steps back
-            while (t < ntest && tm[t % kTests] <= n + 1 - ahead) ++t;
+            // waited for: of pairs the last but two, of whole tests those as many
+            // steps back as may run ahead
+            int t = std::max(seen, ntest - 2);
+            while (t < ntest && !pair[t % kTests] &&
+                   tm[t % kTests] <= n + 1 - ahead_of(tm[t % kTests]))
+                ++t;
             QCM_TRY(verdicts(t - 1));
         }
     }
