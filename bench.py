@@ -10,7 +10,9 @@ the time per product.
 
 Printed: one JSON line with the metric, the roofline of the product against
 the HBM peak, the CPU oracle timed on a bounded sample of rows, and the FP32-
-vector product and a Lanczos step on the same sector.
+vector product and a Lanczos step on the same sector.  The accuracy records of
+single jobs and requests (some 20 KB) are summarised there and written to the
+file that --records names.
 """
 from __future__ import annotations
 
@@ -57,7 +59,55 @@ def parse():
     p.add_argument("--serve-rates", default="1,2,4",
                    help="arrival rates as multiples of the one-at-a-time FP64 rate")
     p.add_argument("--serve-budget-gib", type=float, default=64.0, help="engine pool (GiB)")
+    p.add_argument("--records", default="", help="file for the accuracy records of single jobs")
     return p.parse_args()
+
+
+RECORDS = ("per_job", "per_request")
+
+
+def split_records(out):
+    """out without the lists of per-job records, and those by their place."""
+    if not isinstance(out, dict):
+        return out, {}
+    line, recs = {}, {}
+    for k, v in out.items():
+        if k in RECORDS:
+            recs[k] = v
+            continue
+        line[k], r = split_records(v)
+        if r:
+            recs[k] = r
+    return line, recs
+
+
+def rounded(x, digits=6):
+    """Floats of an extra section to so many digits (energies to 13)."""
+    if isinstance(x, float):
+        return float(f"{x:.{digits}g}")
+    if isinstance(x, dict):
+        return {k: rounded(v, 13 if k in ("e0", "omega") else 6) for k, v in x.items()}
+    if isinstance(x, list):
+        return [rounded(v, digits) for v in x]
+    return x
+
+
+def bench_line(out, most=7800):
+    """The printed line, short enough for a reader of 8,000 characters (sections
+    that do not fit leave their name), and all records."""
+    line, recs = split_records(out)
+    line = {k: rounded(v) if isinstance(v, dict) else v for k, v in line.items()}
+    keep = ("config", "roofline", "cpu_baseline")
+    text = json.dumps(line)
+    while len(text) > most:
+        k = max((k for k, v in line.items() if isinstance(v, dict) and k not in keep),
+                key=lambda k: len(json.dumps(line[k])), default=None)
+        if k is None:
+            break
+        recs[k] = out[k]
+        line[k] = "in the file of --records"
+        text = json.dumps(line)
+    return text, recs
 
 
 def measured_traffic(U: float, name="hv_4x4_fp64_hbm_traffic.txt",
@@ -261,7 +311,11 @@ def main():
                                             "sample": f"every 32nd row ({len(rows1)} rows), "
                                                       f"{dt1:.1f} s"}}
         del vh
-    print(json.dumps(out), flush=True)
+    text, recs = bench_line(out)
+    if args.records:
+        with open(args.records, "w") as f:
+            json.dump(recs, f)
+    print(text, flush=True)
 
 
 Z_GRID = None
@@ -385,7 +439,7 @@ def oracle_accuracy(models, results_by_prec, idx, z, np, gf_steps=100):
     for prec in results_by_prec:
         for key, sel in (("all", recs), ("exhausted", [r for r in recs if r["oracle_chains_exhausted"]]),
                          ("truncated", [r for r in recs if not r["oracle_chains_exhausted"]])):
-            if not sel:
+            if not sel or (key != "all" and len(sel) == len(recs)):   # as "all"
                 continue
             summ[f"{prec}_{key}"] = {
                 "jobs": len(sel),
@@ -718,9 +772,6 @@ def batched_section(args, torch, q, synth, np):
     fb = sum(floor_bytes(m, r, 8) for m, r in zip(ms, res["fp64"]))
     out["one_at_a_time_fp64"] = {"s": round(dt, 3), "solves_per_s": round(len(ms) / dt, 2),
                                  "GBps_floor": round(fb / dt / 1e9, 1)}
-    out["floor_bytes"] = ("3 s d per Lanczos step (read v_n, v_{n-1}, write v_{n+1}) over the "
-                          "ground-state recurrence and its replay and every chain step, summed "
-                          "over the solves and divided by the wall time")
     out["speedup_fp32v_engine"] = round(dt / out["engine_fp32v"]["s"], 2)
     out["speedup_fp64_engine"] = round(dt / out["engine_fp64"]["s"], 2)
     # the FP64 engine equals the single-solve calls bit for bit
