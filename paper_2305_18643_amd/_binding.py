@@ -431,6 +431,15 @@ class HvPlan:
 _KEEP_VECTORS, _KEEP_PART, _KEEP_LOOK = 160, 64, 64 << 20
 
 
+def _free_bytes(torch, device):
+    """Bytes a call could still take: free ones, and those torch's allocator holds
+    unused (13 us; without these a program whose large buffers are back in
+    the allocator would keep next to nothing)."""
+    s = torch.cuda.memory_stats_as_nested_dict(device)
+    held = s["reserved_bytes"]["all"]["current"] - s["allocated_bytes"]["all"]["current"] if s else 0
+    return torch.cuda.mem_get_info(device)[0] + held
+
+
 def _gs_workspace(torch, need, o, dim, device):
     """The workspace of a ground-state call: what it needs and, with a vector
     wanted, room to keep the recurrence's vectors (the call then sums the ground
@@ -441,7 +450,7 @@ def _gs_workspace(torch, need, o, dim, device):
         want = min(max(o.fixed_steps if o.fixed_steps > 0 else o.max_iter, 0) + 1, _KEEP_VECTORS)
         n = want
         if n * vec > _KEEP_LOOK:
-            n = min(n, max(torch.cuda.mem_get_info(device)[0] // _KEEP_PART, _KEEP_LOOK) // vec)
+            n = min(n, max(_free_bytes(torch, device) // _KEEP_PART, _KEEP_LOOK) // vec)
         if n >= 4 and 8 * n >= want:
             try:
                 return _workspace(torch, need + 256 + n * vec, device)

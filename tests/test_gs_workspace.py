@@ -14,8 +14,9 @@ class OutOfMemory(Exception):
     pass
 
 
-def _torch(free, limit=None):
-    """A stand-in whose empty() hands back the number of bytes asked for."""
+def _torch(free, limit=None, held=0):
+    """A stand-in whose empty() hands back the number of bytes asked for; held:
+    bytes in its allocator that no tensor uses."""
     looked = []
 
     def empty(n, dtype=None, device=None):
@@ -26,8 +27,11 @@ def _torch(free, limit=None):
     def info(device=None):
         looked.append(device)
         return free, 288 << 30
+
+    def stats(device=None):
+        return {"reserved_bytes": {"all": {"current": (5 << 30) + held}}, "allocated_bytes": {"all": {"current": 5 << 30}}}
     return SimpleNamespace(empty=empty, uint8=None, OutOfMemoryError=OutOfMemory,
-                           cuda=SimpleNamespace(mem_get_info=info), looked=looked)
+                           cuda=SimpleNamespace(mem_get_info=info, memory_stats_as_nested_dict=stats), looked=looked)
 
 
 def _o(prec=B.QCM_FP64, want=1, max_iter=600, fixed=0):
@@ -56,6 +60,11 @@ def test_a_small_part_of_the_free_memory(free, dim, prec):
     extra = B._gs_workspace(t, NEED, _o(prec), dim, "cuda:0") - NEED
     assert extra <= max(free // 64, 64 << 20) + 512
     assert t.looked == [] or t.looked == ["cuda:0"]
+
+
+def test_memory_held_by_the_allocator_is_free():
+    assert _kept(_torch(0, held=283 << 30), _o(), 11778624) == _kept(_torch(283 << 30), _o(), 11778624) == 50
+    assert _kept(_torch(83 << 30, held=200 << 30), _o(), 11778624) == 50
 
 
 def test_small_offers_do_not_look():
