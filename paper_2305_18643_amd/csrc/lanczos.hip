@@ -222,7 +222,7 @@ __global__ void __launch_bounds__(256) k_psi(double *__restrict__ psi, const T *
 struct SideRes {
     int dev = -1;
     hipStream_t s = nullptr;
-    hipEvent_t ev[2 * SideLease::kEv] = {};
+    hipEvent_t ev[2 * SideLease::kEv + 2] = {};
     void *pinned = nullptr;
 };
 static std::mutex g_side_mu;
@@ -244,12 +244,14 @@ int SideLease::lease() {
         SideRes *n = new SideRes();
         n->dev = dev;
         hipError_t e = hipStreamCreateWithFlags(&n->s, hipStreamNonBlocking);
-        for (int k = 0; k < 2 * kEv && e == hipSuccess; ++k)
-            e = hipEventCreateWithFlags(&n->ev[k], hipEventDisableTiming);
+        for (int k = 0; k < 2 * kEv + 2 && e == hipSuccess; ++k)
+            e = hipEventCreateWithFlags(&n->ev[k], k < 2 * kEv ? hipEventDisableTiming
+                                                               : hipEventDisableTiming |
+                                                                     hipEventDisableSystemFence);
         if (e == hipSuccess) e = hipHostMalloc(&n->pinned, kSidePinned, hipHostMallocDefault);
         if (e != hipSuccess) {
             if (n->pinned) (void)hipHostFree(n->pinned);
-            for (int k = 0; k < 2 * kEv; ++k)
+            for (int k = 0; k < 2 * kEv + 2; ++k)
                 if (n->ev[k]) (void)hipEventDestroy(n->ev[k]);
             if (n->s) (void)hipStreamDestroy(n->s);
             delete n;
@@ -262,6 +264,7 @@ int SideLease::lease() {
         ready[k] = r->ev[k];
         done[k] = r->ev[kEv + k];
     }
+    for (int k = 0; k < 2; ++k) mark[k] = r->ev[2 * kEv + k];
     pinned = r->pinned;
     return QCM_OK;
 }
@@ -787,8 +790,8 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
             if (last) {
                 QCM_HIP(hipStreamSynchronize(s));
             } else if ((n + 1) % (dim >= (1 << 24) ? 1 : n < 16 ? 2 : 8) == 0) {
-                QCM_HIP(hipEventRecord(side.done[nmark % 2], s));
-                if (nmark++ > 0) QCM_HIP(hipEventSynchronize(side.done[nmark % 2]));
+                QCM_HIP(hipEventRecord(side.mark[nmark % 2], s));
+                if (nmark++ > 0) QCM_HIP(hipEventSynchronize(side.mark[nmark % 2]));
             }
             M = n + 1;
             if (*stopped) {

@@ -98,6 +98,7 @@ struct SideLease {
     hipStream_t s = nullptr;
     static constexpr int kEv = 4;
     hipEvent_t ready[kEv] = {}, done[kEv] = {};
+    hipEvent_t mark[2] = {};   // without a system fence: cheaper, where a late look does no harm
     void *pinned = nullptr;   // kSidePinned bytes
     SideRes *r = nullptr;
     SideLease() = default;
