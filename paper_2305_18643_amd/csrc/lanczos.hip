@@ -763,7 +763,7 @@ int gs_run(const char *fn, const GsSetup &setup, int64_t dim, const qcm_lanczos_
             // a short poll (it answers sooner: 1 % of a ground state of 12 orbitals),
             // then the runtime's own wait, which blocks or spins as the program chose
             hipError_t q = hipEventQuery(ev);
-            for (int k = 0; k < 50 && q == hipErrorNotReady && seen <= t; ++k) q = hipEventQuery(ev);
+            for (int k = 0; k < 300 && q == hipErrorNotReady && seen <= t; ++k) q = hipEventQuery(ev);
             if (q == hipErrorNotReady && seen <= t) q = hipEventSynchronize(ev);
             if (q == hipErrorNotReady) break;
             QCM_HIP(q);

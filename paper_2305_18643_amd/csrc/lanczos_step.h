@@ -742,8 +742,8 @@ __global__ void __launch_bounds__(kHvThreads, (hv_waves<T, Src, FORM>())) ks_hv(
             if (lane == 0) q.pa[vec * q.na + (ONE ? row0 + j : wg) + a * q.pstride] = sum;
         }
     };
-    if (ONE && q.rg == 1)
-        sets(std::integral_constant<int, 1>{});
+    if ((ONE && q.rg == 1) || (FORM == kHvShort && q.rows * du <= 64))
+        sets(std::integral_constant<int, 1>{});   // (short: a lane per element)
     else
         sets(std::integral_constant<int, kSide>{});
 }
@@ -756,7 +756,8 @@ inline bool hv_big(int64_t dim, size_t s) { return dim * (int64_t)s >= ((int64_t
 // waves run half empty (8 orbitals (1,4), 10,714 vectors: 79 us with five, 62);
 // but at least the 256 of the dots, if there are any.  A tiny sector in many
 // vectors is one workgroup per vector and bound by the waves it starts: 4
-// orbitals (2,2), 166,666 vectors, 1082 us with eight waves each, 170 with one.
+// orbitals (2,2), 166,666 vectors, 1082 us with eight waves each, 170 with one
+// and pairs, 140 with one and a lane per element where a block has at most 64.
 // Two waves where sums of U are staged (256 entries per eight orbitals).
 inline unsigned hv_threads(int64_t d_up, int32_t rows, bool lut, bool dots) {
     if (hv_form(d_up, rows) != kHvShort) return kHvThreads;
