@@ -267,9 +267,10 @@ typedef double f64x4_t __attribute__((ext_vector_type(4), aligned(8)));
 // the size or storage type, 142 VALU and 107 SALU instructions per 64
 // elements; a variant whose neighbours all came from L2 ran no faster), then,
 // for FP64 rows of 14 orbitals, the traffic of the neighbour rows between L2
-// and memory.  Measured: 14-site chain (7,7) FP64 177 -> 99 us a product,
-// ten chains of its (7,6) sector in FP32 1117 -> 538 us; 12-site ladder (6,6)
-// 40 -> 11.6 us; ten chains of a 10-orbital impurity in FP32 21 -> 10 us.
+// and memory.  Measured, the kernel alone on the same vectors again: 14-site
+// chain (7,7) FP64 183 -> 102 us (a call between others 200 -> 116), ten chains
+// of its (7,6) sector in FP32 1119 -> 566 us; 12-site ladder (6,6) FP64 40 -> 11.4
+// us; ten vectors of a 10-orbital impurity in FP32 21 -> 9.4 us.
 // Kept out: four rows side by side, neighbours loaded before the in-row hops
 // (loads return in order, so the entries then wait for them; and the
 // registers cost more in occupancy than the overlap gains in FP32).

@@ -97,8 +97,9 @@ void basis_from_tables(const SpinTables &up, const SpinTables &dn, qcm_basis *ou
 SpinTables spin_from_basis(const qcm_basis *b, int spin);
 
 // ---------------------------------------------------------------- Hamiltonian tables
-// Model data on the device and the per-spin hopping lists (ELL layout: slot-major,
-// entry s of state i at [s * d + i]).
+// Model data on the device and the per-spin hopping lists: of the up strings slot
+// by slot (entry s of state i at [s * d + i]), of the down strings row by row
+// ([i * width + s]).
 struct ModelDev {
     int32_t L;
     int32_t nbond;        // undirected bonds with t_ab != 0, a < b
