@@ -143,7 +143,7 @@ __host__ __device__ inline int pk_width(int W) { return (W + 3) / 4 * 4; }
 // direction is allowed: the occupied end moves to the empty end.  The entry
 // for row string x is the column label of the string with the electron moved
 // and the element t_ab times (-1)^(occupied orbitals strictly between a, b).
-__global__ void k_build_hops(int64_t d, int rowmajor, int W, int L, int l_lo, int l_hi,
+__global__ void k_build_hops(int64_t d, int W, int L, int l_lo, int l_hi,
                              const uint32_t *__restrict__ states,
                              const int32_t *__restrict__ rlo, const int32_t *__restrict__ rhi,
                              int nbond, const int32_t *__restrict__ ba,
@@ -165,7 +165,7 @@ __global__ void k_build_hops(int64_t d, int rowmajor, int W, int L, int l_lo, in
         uint32_t y = x ^ ma ^ mb;
         uint32_t between = ((mb - 1u) & ~(ma | (ma - 1u)));  // a < b: bits a+1..b-1
         int m = __popc(x & between);
-        const int64_t at = rowmajor ? i * W + n : (int64_t)n * d + i;
+        const int64_t at = (int64_t)n * d + i;
         const int32_t c = spin_rank(rlo, rhi, l_lo, l_hi, y);
         col[at] = c;
         coef[at] = (m & 1) ? -bt[k] : bt[k];
@@ -175,13 +175,63 @@ __global__ void k_build_hops(int64_t d, int rowmajor, int W, int L, int l_lo, in
     // the hop count, and above it the largest count of the 64 states of the wave
     int mx = n;
     for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o));
-    nh[i] = rowmajor ? n : (n | (mx << 16));
+    nh[i] = n | (mx << 16);
     // packed entries past the hops: the zero slot after a row
     if (pk)
         for (int s = n; s < pk_width(W); ++s) pk[(int64_t)s * d + i] = (uint32_t)d;
     double e = 0.0;
     for (int byte = 0; byte < nbytes; ++byte) e += tlut[byte * 256 + ((x >> (8 * byte)) & 255u)];
     ediag[i] = e;
+}
+
+// The same lists row by row, G lanes on a row, one bond each: a row's entries are
+// then stored side by side.  One row per thread stores to 64 lines at a time,
+// two to three times as long (20 orbitals, 184,756 strings: a plan 80 -> 56 us).
+constexpr int kHopRows = 4;   // rows of a group of lanes, which keeps its bonds
+template <int G>
+__global__ void __launch_bounds__(256)
+    k_build_hops_rows(int64_t d, int W, int l_lo, int l_hi, const uint32_t *__restrict__ states,
+                      const int32_t *__restrict__ rlo, const int32_t *__restrict__ rhi, int nbond,
+                      const int32_t *__restrict__ ba, const int32_t *__restrict__ bb,
+                      const double *__restrict__ bt, const double *__restrict__ tlut, int nbytes,
+                      int32_t *__restrict__ nh, int32_t *__restrict__ col,
+                      double *__restrict__ coef, double *__restrict__ ediag) {
+    const int lane = threadIdx.x & 63, sub = lane % G, grp = lane / G;
+    const int64_t i0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) / G * kHopRows;
+    struct Bond {
+        uint32_t ma, mb;
+        double t;
+    };
+    auto bond = [&](int k) {
+        Bond b{0, 0, 0.0};
+        if (k < nbond) b = {1u << ba[k], 1u << bb[k], bt[k]};
+        return b;
+    };
+    const Bond first = bond(sub);
+    for (int r = 0; r < kHopRows; ++r) {
+        const int64_t i = i0 + r;
+        const bool in = i < d;
+        const uint32_t x = in ? states[i] : 0u;
+        int n = 0;
+        for (int k0 = 0; k0 < nbond; k0 += G) {
+            const Bond b = k0 == 0 ? first : bond(k0 + sub);
+            const bool hop = ((x & b.ma) != 0) != ((x & b.mb) != 0);
+            const unsigned long long m =
+                __ballot(hop) >> (grp * G) & (G < 64 ? (1ull << (G % 64)) - 1ull : ~0ull);
+            if (hop) {
+                const int neg = __popc(x & ((b.mb - 1u) & ~(b.ma | (b.ma - 1u)))) & 1;   // a < b
+                const int64_t at = i * W + n + __popcll(m & ((1ull << sub) - 1ull));
+                col[at] = spin_rank(rlo, rhi, l_lo, l_hi, x ^ b.ma ^ b.mb);
+                coef[at] = neg ? -b.t : b.t;
+            }
+            n += __popcll(m);
+        }
+        if (!in || sub) continue;
+        nh[i] = n;
+        double e = 0.0;
+        for (int byte = 0; byte < nbytes; ++byte) e += tlut[byte * 256 + ((x >> (8 * byte)) & 255u)];
+        ediag[i] = e;
+    }
 }
 
 int build_hop_tables(const ModelDev &md, const SpinTables &st, Carver &cv, HopTables *ht,
@@ -199,11 +249,29 @@ int build_hop_tables(const ModelDev &md, const SpinTables &st, Carver &cv, HopTa
     ht->pk = (!rowmajor && st.d < 65536) ? cv.take<uint32_t>((size_t)pk_width(W) * st.d) : nullptr;
     if (!cv.base) return QCM_OK;
     const int B = 256;
-    k_build_hops<<<ceil_div(st.d, B), B, 0, s>>>(st.d, ht->rowmajor, W, st.L, st.l_lo, st.l_hi, st.states,
+    if (rowmajor) {
+        auto rows = [&](auto g_) {
+            constexpr int G = decltype(g_)::value;
+            k_build_hops_rows<G><<<ceil_div(ceil_div((size_t)st.d, kHopRows) * G, B), B, 0, s>>>(
+                st.d, W, st.l_lo, st.l_hi, st.states, st.rank_lo, st.rank_hi, nbond_host, md.bond_a,
+                md.bond_b, md.bond_t, md.tlut, md.nbytes, ht->nh, ht->col, ht->coef, ht->ediag);
+        };
+        if (nbond_host <= 8)
+            rows(std::integral_constant<int, 8>{});
+        else if (nbond_host <= 16)
+            rows(std::integral_constant<int, 16>{});
+        else if (nbond_host <= 32)
+            rows(std::integral_constant<int, 32>{});
+        else
+            rows(std::integral_constant<int, 64>{});
+        QCM_LAUNCH_CHECK();
+        return QCM_OK;
+    }
+    k_build_hops<<<ceil_div(st.d, B), B, 0, s>>>(st.d, W, st.L, st.l_lo, st.l_hi, st.states,
                                                   st.rank_lo, st.rank_hi, nbond_host, md.bond_a,
                                                   md.bond_b, md.bond_t, md.tlut, md.nbytes,
                                                   ht->nh, ht->col, ht->coef, ht->ediag,
-                                                  rowmajor ? nullptr : ht->pk);
+                                                  ht->pk);
     QCM_LAUNCH_CHECK();
     return QCM_OK;
 }
