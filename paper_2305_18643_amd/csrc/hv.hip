@@ -143,7 +143,7 @@ __host__ __device__ inline int pk_width(int W) { return (W + 3) / 4 * 4; }
 // direction is allowed: the occupied end moves to the empty end.  The entry
 // for row string x is the column label of the string with the electron moved
 // and the element t_ab times (-1)^(occupied orbitals strictly between a, b).
-__global__ void k_build_hops(int64_t d, int W, int L, int l_lo, int l_hi,
+__global__ void k_build_hops(int64_t d, int pk_slots, int W, int L, int l_lo, int l_hi,
                              const uint32_t *__restrict__ states,
                              const int32_t *__restrict__ rlo, const int32_t *__restrict__ rhi,
                              int nbond, const int32_t *__restrict__ ba,
@@ -175,7 +175,7 @@ __global__ void k_build_hops(int64_t d, int W, int L, int l_lo, int l_hi,
     // the hop count, and above it the largest count of the 64 states of the wave
     int mx = n;
     for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o));
-    nh[i] = n | (mx << 16);
+    nh[i] = pk_slots ? (n | (mx << 16)) : n;
     // packed entries past the hops: the zero slot after a row
     if (pk)
         for (int s = n; s < pk_width(W); ++s) pk[(int64_t)s * d + i] = (uint32_t)d;
@@ -249,7 +249,7 @@ int build_hop_tables(const ModelDev &md, const SpinTables &st, Carver &cv, HopTa
     ht->pk = (!rowmajor && st.d < 65536) ? cv.take<uint32_t>((size_t)pk_width(W) * st.d) : nullptr;
     if (!cv.base) return QCM_OK;
     const int B = 256;
-    if (rowmajor) {
+    if (rowmajor == 1) {
         auto rows = [&](auto g_) {
             constexpr int G = decltype(g_)::value;
             k_build_hops_rows<G><<<ceil_div(ceil_div((size_t)st.d, kHopRows) * G, B), B, 0, s>>>(
@@ -267,7 +267,7 @@ int build_hop_tables(const ModelDev &md, const SpinTables &st, Carver &cv, HopTa
         QCM_LAUNCH_CHECK();
         return QCM_OK;
     }
-    k_build_hops<<<ceil_div(st.d, B), B, 0, s>>>(st.d, W, st.L, st.l_lo, st.l_hi, st.states,
+    k_build_hops<<<ceil_div(st.d, B), B, 0, s>>>(st.d, rowmajor == 0, W, st.L, st.l_lo, st.l_hi, st.states,
                                                   st.rank_lo, st.rank_hi, nbond_host, md.bond_a,
                                                   md.bond_b, md.bond_t, md.tlut, md.nbytes,
                                                   ht->nh, ht->col, ht->coef, ht->ediag,
@@ -458,7 +458,7 @@ int hv_setup(const qcm_model *m, const qcm_basis *b, Carver &cv, HvOp *op, hipSt
     op->dim = b->dim;
     int nb = count_bonds(m);
     QCM_TRY(build_hop_tables(op->md, op->up, cv, &op->hu, s, nb));
-    QCM_TRY(build_hop_tables(op->md, op->dn, cv, &op->hd, s, nb, 1));
+    QCM_TRY(build_hop_tables(op->md, op->dn, cv, &op->hd, s, nb, dn_layout(b->d_up)));
     op->split = 0;
     if (split_applies(m, b->n_up, b->d_up, b->d_dn)) QCM_TRY(split_prepare(m, *op, cv, s));
     return QCM_OK;

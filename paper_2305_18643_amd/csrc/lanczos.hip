@@ -366,6 +366,7 @@ void group_tables(const HvOp &op, BGroup *g) {
     g->cfd = op.hd.coef;
     g->wu = (op.hu.width + 3) / 4 * 4;   // slots of the packed list
     g->wd = op.hd.width;
+    g->dslot = op.hd.rowmajor != 1;
     g->ulut = op.md.ulut;
     g->pku = op.hu.pk;
     g->ctab = op.md.ctab;

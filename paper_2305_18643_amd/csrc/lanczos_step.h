@@ -54,7 +54,7 @@ struct BGroup {
     const uint32_t *su, *sd;
     const double *eu, *ed;
     const int32_t *nhu, *nhd, *cold;
-    const double *cfd;     // down hops, row-major: hop s of row i at i * wd + s
+    const double *cfd;     // down hops, row by row (hop s of row i at i * wd + s) or dslot
     const double *ulut;
     const uint32_t *pku;   // packed up hops (HopTables::pk)
     const double *ctab;    // hop coefficients by index (+-t_ab)
@@ -62,6 +62,7 @@ struct BGroup {
     int32_t nbytes;
     int32_t nctab;
     int32_t wu, wd;    // widths of the hop lists
+    int32_t dslot;     // down hops slot by slot: hop s of row i at s * d_dn + i
     int32_t rg;        // rows a product workgroup takes side by side (hv_one; else 1)
     int32_t wgs;       // product workgroups per vector
     int32_t t_uniform; // every bond has the same t (a coefficient is +-ctab[0])
@@ -170,6 +171,13 @@ inline int32_t side_rows(int64_t d_up, int32_t rows, int prec) {
 // down-hop lists.
 enum { kHvRows = 0, kHvOne = 1, kHvShort = 2 };
 constexpr int kShortRow = 48;
+// The layout of the down-hop lists of a sector with one up string: slot by slot,
+// as a lane has a row of its own and consecutive lanes then read side by side.
+// Row by row each lane streams its own list, of which the L2 keeps nothing once
+// the lists of the waves in flight exceed it (24 orbitals (0,12), 2,704,156 rows:
+// a product 447 us row by row, 152 slot by slot).  Rows of more strings share a
+// list, and slot by slot lose as often as they gain.
+inline int dn_layout(int64_t d_up) { return d_up == 1 ? 2 : 1; }
 inline int hv_form(int64_t d_up, int32_t rows) {
     return hv_one(d_up, rows) ? kHvOne : d_up <= kShortRow ? kHvShort : kHvRows;
 }
@@ -568,10 +576,32 @@ __global__ void __launch_bounds__(kHvThreads, (hv_waves<T, Src, FORM>())) ks_hv(
                 else
                     return buf_load<T>(rv, (j * du + c) * (int)sizeof(T), 0);
             };
-            // whole groups of four hops, then the last one to three together
+            if (RG == 1 && q.dslot) {   // (a single up string)
+#pragma unroll
+                for (int r = 0; r < RG; ++r) {
+                    const int n = nhr[r];
+                    auto pc = gp(q.cold) + idn[r];
+                    auto pf = gp(q.cfd) + idn[r];
+                    int t = 0;
+                    for (; t + 4 <= n; t += 4, pc += 4 * d_dn, pf += 4 * d_dn) {
+                        double co[4];
+                        T x[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            co[u] = pf[u * d_dn];
+                            x[u] = neighbour(pc[u * d_dn]);
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) acc[r][0] = fma(co[u], (double)x[u], acc[r][0]);
+                    }
+                    for (; t < n; ++t, pc += d_dn, pf += d_dn)
+                        acc[r][0] = fma(*pf, (double)neighbour(*pc), acc[r][0]);
+                }
+            }
+            // row by row: whole groups of four hops, then the last one to three together
 #pragma unroll
             for (int r = 0; r < RG; ++r) {
-                const int n = nhr[r], nt = n & ~3;
+                const int n = RG == 1 && q.dslot ? 0 : nhr[r], nt = n & ~3;
                 for (int t = 0; t < nt; t += 4) {
                     const i32x4_t cc = *(gptr<const i32x4_t>)(cl[r] + t);
                     const f64x4_t co = *(gptr<const f64x4_t>)(cf[r] + t);
@@ -743,7 +773,7 @@ __global__ void __launch_bounds__(kHvThreads, (hv_waves<T, Src, FORM>())) ks_hv(
             if (lane == 0) q.pa[vec * q.na + (ONE ? row0 + j : wg) + a * q.pstride] = sum;
         }
     };
-    if ((ONE && q.rg == 1) || (FORM == kHvShort && q.rows * du <= 64))
+    if ((ONE && q.rg == 1) || (FORM == kHvShort && (q.rows * du <= 64 || q.dslot)))
         sets(std::integral_constant<int, 1>{});   // (short: a lane per element)
     else
         sets(std::integral_constant<int, kSide>{});
@@ -1253,8 +1283,9 @@ __global__ void __launch_bounds__(kChainThreads) ks_chain(const OneSrc src, cons
         const int n = q.nhd[i];
         nd[i] = n;
         for (int s = 0; s < wd; ++s) {
-            cl[i * wd + s] = s < n ? q.cold[i * q.wd + s] * st : dn * st;
-            cf[i * wd + s] = s < n ? q.cfd[i * q.wd + s] : 0.0;
+            const int at = q.dslot ? s * dn + i : i * q.wd + s;
+            cl[i * wd + s] = s < n ? q.cold[at] * st : dn * st;
+            cf[i * wd + s] = s < n ? q.cfd[at] : 0.0;
         }
     }
     for (int k = tid; k < 3 * vlen; k += NT) bvp[k] = T(0);

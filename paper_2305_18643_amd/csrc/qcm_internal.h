@@ -119,7 +119,8 @@ struct ModelDev {
 struct HopTables {
     int64_t d;
     int32_t width;        // ELL width (max hops per state)
-    int32_t rowmajor;     // 0: entry s of state i at [s * d + i]; 1: at [i * width + s]
+    int32_t rowmajor;     // 0: entry s of state i at [s * d + i]; 1: at [i * width + s];
+                          // 2: as 0, without packed entries, nh the plain count
     int32_t *nh;          // [d] number of hops of each state (slot-major layout: in the low 16
                           // bits, the largest count of its 64 consecutive states above)
     int32_t *col;         // [width * d]
