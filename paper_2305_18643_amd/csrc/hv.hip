@@ -187,17 +187,29 @@ __global__ void k_build_hops(int64_t d, int pk_slots, int W, int L, int l_lo, in
 // The same lists row by row, G lanes on a row, one bond each: a row's entries are
 // then stored side by side.  One row per thread stores to 64 lines at a time,
 // two to three times as long (20 orbitals, 184,756 strings: a plan 80 -> 56 us).
-constexpr int kHopRows = 4;   // rows of a group of lanes, which keeps its bonds
+// A group of lanes takes four rows, so that it reads its bonds once, or as many
+// as keep the launch under 2^32 threads.
+constexpr int hop_rows(int64_t d, int G) {
+    const int64_t r = (d * G + (1ll << 31) - 1) >> 31;
+    return r < 4 ? 4 : (int)r;
+}
+constexpr int64_t hop_blocks(int64_t d, int G) {
+    const int64_t groups = (d + hop_rows(d, G) - 1) / hop_rows(d, G);
+    return (groups * G + 255) / 256;
+}
+static_assert(hop_blocks(0x7fffffff, 64) * 256 < 1ll << 32 && hop_blocks(1ll << 27, 64) * 256 < 1ll << 32 &&
+                  hop_blocks(300540195, 64) * 256 < 1ll << 32 && hop_blocks(601080390, 32) * 256 < 1ll << 32,
+              "a launch takes fewer than 2^32 threads");
 template <int G>
 __global__ void __launch_bounds__(256)
-    k_build_hops_rows(int64_t d, int W, int l_lo, int l_hi, const uint32_t *__restrict__ states,
+    k_build_hops_rows(int64_t d, int rows, int W, int l_lo, int l_hi, const uint32_t *__restrict__ states,
                       const int32_t *__restrict__ rlo, const int32_t *__restrict__ rhi, int nbond,
                       const int32_t *__restrict__ ba, const int32_t *__restrict__ bb,
                       const double *__restrict__ bt, const double *__restrict__ tlut, int nbytes,
                       int32_t *__restrict__ nh, int32_t *__restrict__ col,
                       double *__restrict__ coef, double *__restrict__ ediag) {
     const int lane = threadIdx.x & 63, sub = lane % G, grp = lane / G;
-    const int64_t i0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) / G * kHopRows;
+    const int64_t i0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) / G * rows;
     struct Bond {
         uint32_t ma, mb;
         double t;
@@ -208,7 +220,7 @@ __global__ void __launch_bounds__(256)
         return b;
     };
     const Bond first = bond(sub);
-    for (int r = 0; r < kHopRows; ++r) {
+    for (int r = 0; r < rows; ++r) {
         const int64_t i = i0 + r;
         const bool in = i < d;
         const uint32_t x = in ? states[i] : 0u;
@@ -252,8 +264,8 @@ int build_hop_tables(const ModelDev &md, const SpinTables &st, Carver &cv, HopTa
     if (rowmajor == 1) {
         auto rows = [&](auto g_) {
             constexpr int G = decltype(g_)::value;
-            k_build_hops_rows<G><<<ceil_div(ceil_div((size_t)st.d, kHopRows) * G, B), B, 0, s>>>(
-                st.d, W, st.l_lo, st.l_hi, st.states, st.rank_lo, st.rank_hi, nbond_host, md.bond_a,
+            k_build_hops_rows<G><<<(unsigned)hop_blocks(st.d, G), B, 0, s>>>(
+                st.d, hop_rows(st.d, G), W, st.l_lo, st.l_hi, st.states, st.rank_lo, st.rank_hi, nbond_host, md.bond_a,
                 md.bond_b, md.bond_t, md.tlut, md.nbytes, ht->nh, ht->col, ht->coef, ht->ediag);
         };
         if (nbond_host <= 8)

@@ -99,7 +99,7 @@ SpinTables spin_from_basis(const qcm_basis *b, int spin);
 // ---------------------------------------------------------------- Hamiltonian tables
 // Model data on the device and the per-spin hopping lists: of the up strings slot
 // by slot (entry s of state i at [s * d + i]), of the down strings row by row
-// ([i * width + s]).
+// ([i * width + s]; a sector of a single up string: slot by slot, dn_layout).
 struct ModelDev {
     int32_t L;
     int32_t nbond;        // undirected bonds with t_ab != 0, a < b
